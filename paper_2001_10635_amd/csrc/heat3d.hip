@@ -27,6 +27,15 @@
 // halo (4 cells on each cut face, one per stage) is recomputed, not
 // exchanged.
 //
+// z chunks.  A grid whose x-y tiles leave compute units idle is also cut along
+// z: a block sweeps the LZ output planes of its chunk with 4 more planes past
+// each cut end (one per level), as if that piece were a grid of its own.  The
+// mirror planes the sweep's ends then make are wrong at a cut end, but each
+// level carries that error one plane inwards, so the 4 halo planes absorb it
+// and every stored plane has the bits of the uncut sweep.  The launcher takes
+// the cut only where it shortens the launch (heat_z_chunks): 200 x 180 x 150
+// FP32 has 64 tiles of both sides for 256 compute units.
+//
 // Boundaries without per-cell tests:
 //   - y faces: ghost rows load the mirror image of the grid (even
 //     reflection, repeated for grids thinner than the halo).  The mirror
@@ -68,7 +77,8 @@ struct HeatCtx {
     const T* src;
     T* dst;
     int64_t plane;       // nx * ny
-    int nz;
+    int nz;              // planes of this block's sweep (a chunk with its halo planes)
+    int zo, ze;          // output planes [zo, ze) of the sweep
     int lane, w, wm, wp; // wave index and the waves above / below (clamped)
     int xl;              // x index this lane loads (mirror-mapped), valid if xload
     bool xload;          // lane loads a grid cell (else it holds 0)
@@ -157,7 +167,7 @@ __device__ __forceinline__ void copy_rows(T (&d)[P], const T (&s)[P]) {
 // q = z - 1 - LV.  Levels run in every iteration: before their first plane
 // and after their last one they compute values nobody reads (they land in
 // ring slots, pipes and LDS rows that are rewritten before their next use)
-// and store nothing.  STEADY: the caller guarantees 0 <= q < nz and no
+// and store nothing.  STEADY: the caller guarantees zo <= q < ze and no
 // mirror copy due, so the uniform tests drop out.
 template <int LV, int PH, bool STEADY, bool ZT, class T, int P, int WV>
 __device__ __forceinline__ void heat_level(HeatRegs<T, P>& R, HeatLds<T, WV>& L,
@@ -193,7 +203,7 @@ __device__ __forceinline__ void heat_level(HeatRegs<T, P>& R, HeatLds<T, WV>& L,
         }
     } else {
         T* out = c.dst + (int64_t)q * c.plane;
-        const bool live = STEADY || (q >= 0 && q < c.nz);
+        const bool live = STEADY || (q >= c.zo && q < c.ze);
         T nv[P];
         heat_apply<T, P>(nv, cur, zm, zp, E.up[3], E.dn[3], y, c.cw[3], c.m6cw[3]);
 #pragma unroll
@@ -238,17 +248,25 @@ __device__ __forceinline__ void heat_group(HeatRegs<T, P>& R, HeatLds<T, WV>& L,
     heat_iter<5, STEADY, ZT>(R, L, c, rows, z0 + 5);
 }
 
-// Whole z sweep, iterations z = 0 .. nz + 3 (rounded up to whole groups:
+// Whole z sweep, iterations z = 0 .. ze + 3 (rounded up to whole groups:
 // the extra iterations compute nothing that is stored).  A first group with
-// the boundary tests, steady groups while each of their iterations z has
-// 5 <= z and z + 3 < nz, then the rest with the tests again.
-template <bool ZT, class T, int P, int WV>
+// the boundary tests (two when the first output plane is zo = 4: iteration z
+// stores plane z - 4), steady groups while each of their iterations z has
+// zo + 4 <= z, 5 <= z and z + 3 < nz (so z - 4 < ze), then the rest with the
+// tests again.
+template <bool CUT, bool ZT, class T, int P, int WV>
 __device__ __forceinline__ void heat_sweep(HeatRegs<T, P>& R, HeatLds<T, WV>& L, HeatCtx<T>& c,
                                            const HeatRows<T, P>& rows) {
-    heat_group<false, ZT>(R, L, c, rows, 0);
-    int z = 6;
+    int z = 0;
+    if constexpr (CUT) {
+        const int z1 = c.zo > 0 ? 12 : 6;
+        for (; z < z1; z += 6) heat_group<false, ZT>(R, L, c, rows, z);
+    } else {
+        heat_group<false, ZT>(R, L, c, rows, 0);
+        z = 6;
+    }
     for (; z + 6 <= c.nz - 3; z += 6) heat_group<true, ZT>(R, L, c, rows, z);
-    for (; z < c.nz + 4; z += 6) heat_group<false, ZT>(R, L, c, rows, z);
+    for (; z < c.ze + 4; z += 6) heat_group<false, ZT>(R, L, c, rows, z);
 }
 
 // Even reflection of grid index g into [0, n) (period 2n).
@@ -258,15 +276,23 @@ __device__ __forceinline__ int64_t mirror_index(int64_t g, int64_t n) {
     return r < n ? r : 2 * n - 1 - r;
 }
 
-template <class T, int P, int WV>
+// CUT: the sweep is cut into z chunks (an instance of its own: the chunk's
+// bounds cost the uncut sweep two scalar registers more than it has, 2.5% at
+// 1000^3).
+template <class T, int P, int WV, bool CUT>
 __global__ __launch_bounds__(WAVE * WV) void heat3d_kernel(HeatPass a) {
     __shared__ HeatLds<T, WV> L;
     const int64_t b = blockIdx.x;
     const int64_t g = (b & 7) * (int64_t)a.per_xcd + (b >> 3);
     const int64_t tiles = (int64_t)a.TX * a.TY;
-    if (g >= a.sides * tiles) return;
-    const int side = (int)(g / tiles);
-    const int64_t t = g - side * tiles;
+    const int64_t per_side = CUT ? tiles * a.ZC : tiles;
+    if (g >= a.sides * per_side) return;
+    const int side = (int)(g / per_side);
+    int64_t t = g - side * per_side, zc = 0;
+    if constexpr (CUT) {
+        zc = t / tiles;
+        t -= zc * tiles;
+    }
     const int64_t by = t / a.TX, bx = t - by * a.TX;
 
     HeatCtx<T> c;
@@ -274,6 +300,20 @@ __global__ __launch_bounds__(WAVE * WV) void heat3d_kernel(HeatPass a) {
     c.dst = (T*)a.dst[side];
     c.plane = a.nx * a.ny;
     c.nz = (int)a.nz;
+    c.zo = 0;
+    c.ze = c.nz;
+    if constexpr (CUT) {
+        // the chunk's output planes [zs, zt) of the grid; its sweep starts at
+        // plane zb and ends before plane ze
+        const int64_t zs = zc * a.LZ, zt = zs + a.LZ < a.nz ? zs + a.LZ : a.nz;
+        const int64_t zb = zs > 0 ? zs - HEAT_R : 0;
+        const int64_t ze = zt + HEAT_R < a.nz ? zt + HEAT_R : a.nz;
+        c.src += zb * c.plane;
+        c.dst += zb * c.plane;
+        c.nz = (int)(ze - zb);
+        c.zo = (int)(zs - zb);
+        c.ze = (int)(zt - zb);
+    }
     c.lane = threadIdx.x & (WAVE - 1);
     c.w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     c.wm = c.w > 0 ? c.w - 1 : c.w;
@@ -333,8 +373,8 @@ __global__ __launch_bounds__(WAVE * WV) void heat3d_kernel(HeatPass a) {
     heat_load<T, P, WV>(R.t0[2], c, rows, c.nz > 2 ? 2 : c.nz - 1);
     copy_rows(R.t0[5], R.t0[0]);
 
-    if (c.ztile) heat_sweep<true>(R, L, c, rows);
-    else heat_sweep<false>(R, L, c, rows);
+    if (c.ztile) heat_sweep<CUT, true>(R, L, c, rows);
+    else heat_sweep<CUT, false>(R, L, c, rows);
     report_status(a.status, c.bits);
 }
 
@@ -364,7 +404,16 @@ hipError_t launch_center_radius(int dtype, const void* lo, const void* hi, int64
 
 template <class T, int P, int WV>
 static hipError_t go_heat(const HeatPass& a, int64_t grid, hipStream_t s) {
-    hipLaunchKernelGGL((heat3d_kernel<T, P, WV>), dim3((unsigned)grid), dim3(WAVE * WV), 0, s, a);
+    if (a.ZC > 1) {
+        if constexpr (P == HEAT_CUT_ROWS) {
+            hipLaunchKernelGGL((heat3d_kernel<T, P, WV, true>), dim3((unsigned)grid),
+                               dim3(WAVE * WV), 0, s, a);
+            return hipGetLastError();
+        }
+        return hipErrorInvalidValue;
+    }
+    hipLaunchKernelGGL((heat3d_kernel<T, P, WV, false>), dim3((unsigned)grid), dim3(WAVE * WV), 0,
+                       s, a);
     return hipGetLastError();
 }
 

@@ -78,7 +78,8 @@ bool gb_has_E(int E);
 // One RK4 step of the 3-D heat grid for `sides` independent states
 // (lower / upper, or center / half-width).  Tiles are x-y columns of 64 by
 // WV * P cells streaming through z; TX * TY tiles per side, each writing its
-// OX by OY output cells (64 - 8 and WV * P - 8: a 4-cell halo per cut face).
+// OX by OY output cells (64 - 8 and WV * P - 8: a 4-cell halo per cut face) of
+// the ZC chunks of LZ >= 4 planes the sweep is cut into (ZC = 1: LZ = nz).
 struct HeatPass {
     const void* src[2];
     void* dst[2];
@@ -86,6 +87,7 @@ struct HeatPass {
     int32_t TX, TY, OX, OY;
     int32_t sides;
     int32_t per_xcd;    // tiles per XCD in the blockIdx -> tile map
+    int64_t ZC, LZ;     // z chunks per tile, output planes of a chunk
     double a;           // alpha / dx^2
     double h2, dt, dt6;
     // level j of a step updates w <- y + cw[j] (s - 6 w), cw[j] = a dt / (4 - j)
@@ -96,6 +98,7 @@ struct HeatPass {
 hipError_t launch_heat3d(int dtype, int P, int WV, const HeatPass& a, int64_t grid,
                          hipStream_t stream);
 bool heat_has_shape(int dtype, int P, int WV);
+constexpr int HEAT_CUT_ROWS = 2;   // rows per wave of the shape built with z chunks
 // c = (lo + hi) / 2, r = (hi - lo) / 2 elementwise (growth-bound start).
 hipError_t launch_center_radius(int dtype, const void* lo, const void* hi, int64_t n, void* c,
                                 void* r, hipStream_t stream);

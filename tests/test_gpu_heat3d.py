@@ -77,6 +77,26 @@ def test_heat3d_tile_shape_invariance_is_bitwise(rc, dtype):
         assert np.array_equal(a, outs[0][0]) and np.array_equal(b, outs[0][1])
 
 
+@pytest.mark.parametrize("dtype", [np.float64, np.float32], ids=["f64", "f32"])
+@pytest.mark.parametrize("grid", [(3, 3, 8), (3, 3, 9), (5, 4, 13), (57, 25, 97), (64, 32, 200),
+                                  (130, 3, 61)], ids=lambda g: "x".join(map(str, g)))
+def test_heat3d_z_chunks_match_oracle(rc, grid, dtype):
+    """Grids of few x-y tiles, whose z sweep is cut into chunks (from 4 planes
+    each, the last one shorter): cut ends, the first and last chunk's real
+    faces, and the halo planes between."""
+    prm, lo, hi, dt = heat_case(grid, dtype, seed=100 + sum(grid))
+    for nsteps in (1, 4):
+        o_lo, o_hi = oracle.embed_rk4(oracle.HEAT3D, prm, lo.astype(np.float64),
+                                      hi.astype(np.float64), dt=dt, nsteps=nsteps)
+        for P in ROWS[dtype]:
+            rc.set_option("heat.P", P)
+            say(f"heat3d chunks {grid} {np.dtype(dtype).name} P={P} steps={nsteps}")
+            g_lo, g_hi, st = run_embed(rc, prm, lo, hi, dt, nsteps)
+            assert st == R.REACH_OK
+            assert_rel(g_lo, o_lo, RTOL[np.dtype(dtype)], f"lower P={P}")
+            assert_rel(g_hi, o_hi, RTOL[np.dtype(dtype)], f"upper P={P}")
+
+
 def test_heat3d_resume_alias_and_zero_steps(rc):
     prm, lo, hi, dt = heat_case((90, 40, 11), np.float64, seed=42)
     say("heat3d resume")
