@@ -47,26 +47,63 @@ __device__ __forceinline__ double dpp64(double x) {
 __device__ __forceinline__ double from_left(double x) { return dpp64<DPP_WAVE_SHR1>(x); }
 __device__ __forceinline__ double from_right(double x) { return dpp64<DPP_WAVE_SHL1>(x); }
 
+// Lane l receives x of lane l+1; lane 63 keeps `last` (a shift without a source
+// lane leaves its destination unwritten), so no select follows the shift.
+__device__ __forceinline__ float from_right_or(float x, float last) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(last), __float_as_int(x),
+                                                      DPP_WAVE_SHL1, 0xF, 0xF, false));
+}
+__device__ __forceinline__ double from_right_or(double x, double last) {
+    const uint64_t xi = (uint64_t)__double_as_longlong(x);
+    const uint64_t li = (uint64_t)__double_as_longlong(last);
+    const int lo = __builtin_amdgcn_update_dpp((int)(uint32_t)li, (int)(uint32_t)xi, DPP_WAVE_SHL1,
+                                               0xF, 0xF, false);
+    const int hi = __builtin_amdgcn_update_dpp((int)(uint32_t)(li >> 32), (int)(uint32_t)(xi >> 32),
+                                               DPP_WAVE_SHL1, 0xF, 0xF, false);
+    return __longlong_as_double((long long)(((uint64_t)(uint32_t)hi << 32) | (uint32_t)lo));
+}
+
 __device__ __forceinline__ float fmaT(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
 __device__ __forceinline__ double fmaT(double a, double b, double c) { return __builtin_fma(a, b, c); }
 __device__ __forceinline__ float minT(float a, float b) { return __builtin_fminf(a, b); }
 __device__ __forceinline__ double minT(double a, double b) { return __builtin_fmin(a, b); }
+
+// min with an operand that came through a lane shift: the compiler cannot see
+// that the value is no signalling NaN and would put a max(x, x) before the min
+// (in the dependent chain of every stage).
+__device__ __forceinline__ float min_shifted(float a, float b) {
+    float r;
+    asm("v_min_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+    return r;
+}
+__device__ __forceinline__ double min_shifted(double a, double b) {
+    double r;
+    asm("v_min_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+    return r;
+}
 
 template <class T> __device__ __forceinline__ T neg_inf();
 template <> __device__ __forceinline__ float neg_inf<float>() { return -__builtin_inff(); }
 template <> __device__ __forceinline__ double neg_inf<double>() { return -__builtin_inf(); }
 
 // ------------------------------------------------------------- systems --
-// Kind tags (match the C ABI) and input modes.
-enum { K_CTM = 1, K_RD = 2, K_LIN3 = 3 };
-enum { IN_SCALAR = 0, IN_CELL = 1 };
+// Kind tags (match the C ABI) and input modes.  K_LIN3C and K_LIN3M are the
+// LIN3 embedding with the signs of its couplings known (both sides per wave):
+//   C  neither neighbour's term crosses to the other side,
+//   M  the left neighbour's does, the right one's does not.
+// The other sign patterns become these two by exchanging the sides of every
+// odd cell (see embed_tile_kernel).
+enum { K_CTM = 1, K_RD = 2, K_LIN3 = 3, K_LIN3C = 13, K_LIN3M = 14 };
+enum { IN_SCALAR = 0, IN_CELL = 1, IN_ALT = 2 };
 
 // Per-launch system constants, already converted to the kernel's type.
 template <class T> struct SysPrm {
     T a0, a1, a2, a3, a4;   // CTM: v, w, c*w, q  RD: 1/h^2, 2/h^2  LIN3: aL, aD, aR, b
 };
 
-// Inputs seen by one lane: scalar (same for every cell) or one per cell.
+// Inputs seen by one lane: scalar (same for every cell), one per cell, or one
+// for the even and one for the odd slots (IN_ALT: a scalar input in a LIN3
+// wave, which may exchange the sides of its odd cells).
 template <class T, int E, int S, int MODE> struct Inputs;
 template <class T, int E, int S> struct Inputs<T, E, S, IN_SCALAR> {
     T u[S];
@@ -75,6 +112,10 @@ template <class T, int E, int S> struct Inputs<T, E, S, IN_SCALAR> {
 template <class T, int E, int S> struct Inputs<T, E, S, IN_CELL> {
     T u[S][E];
     __device__ __forceinline__ T at(int s, int e) const { return u[s][e]; }
+};
+template <class T, int E, int S> struct Inputs<T, E, S, IN_ALT> {
+    T u[S][2];
+    __device__ __forceinline__ T at(int s, int e) const { return u[s][e & 1]; }
 };
 
 // Stage update applied to cell e of side s once its derivative k is known.
@@ -139,126 +180,215 @@ __device__ __forceinline__ Mask<E, true, END, ONE> chain_end_mask(int64_t n_rel)
     return M;
 }
 
+// Ghost value of a system past the chain's right end.
+template <int KIND, class T> __device__ __forceinline__ T ghost() {
+    if constexpr (KIND == K_CTM) return neg_inf<T>();
+    else return T(0);
+}
+
+// What a lane holds of its neighbour lanes' edge cells, for the stage input at
+// hand: r, the first cell of lane l+1, and l, the last cell of lane l-1.  For the
+// CTM r is the supply w (c - y) of that cell, and l is not used: the left lane
+// hands over its outgoing flux.
+template <class T, int S> struct Edges {
+    T l[S], r[S];
+};
+
+// Whether a stage hands its edge cells on as soon as they are known: not in the
+// widest windows, where the values held meanwhile cost registers and the inner
+// cells cover the shifts anyway.
+template <class T, int E> constexpr bool early_edges() { return E * sizeof(T) <= 128; }
+
+template <int KIND, class T, int E, int S, bool END>
+__device__ __forceinline__ void get_edges(Edges<T, S>& c, const T (&in)[E], int s,
+                                          const SysPrm<T>& P) {
+    if constexpr (KIND == K_CTM) {
+        // END: lane 63 keeps the ghost's supply from first_edges
+        const T sup = fmaT(-P.a1, in[0], P.a2);
+        c.r[s] = END ? from_right_or(sup, c.r[s]) : from_right(sup);
+    } else {
+        c.l[s] = from_left(in[E - 1]);
+        c.r[s] = from_right(in[0]);
+    }
+}
+
+// Before the first get_edges.
+template <int KIND, class T, int S>
+__device__ __forceinline__ void first_edges(Edges<T, S>& c, const SysPrm<T>& P) {
+    if constexpr (KIND == K_CTM) {
+#pragma unroll
+        for (int s = 0; s < S; ++s) c.r[s] = fmaT(-P.a1, neg_inf<T>(), P.a2);
+    }
+}
+
 // One RK4 stage for all cells of the lane, for every side s < S.
 //   in  : the stage input (y for stage 1, t otherwise)
+//   c   : the neighbour lanes' edge cells of `in`; on return those of the next
+//         stage's input (early_edges; else read here)
 // For S == 2 the sides are (lower, upper) of the embedding; for S == 1 the
-// kernel integrates f itself (Monte Carlo).
+// kernel integrates f itself (Monte Carlo) or one side of a cooperative chain.
+//
+// The lane's two edge cells are computed first and (early_edges) handed to the
+// neighbour lanes at once, so that the lane shifts (two moves of a double, each
+// waiting for the cell's update) run while the inner cells are computed instead
+// of holding up the next stage.  A wave alone on its SIMD, as on every chain too
+// short to fill the chip, has nothing else to issue meanwhile (RD FP64, 4 cells
+// a lane: 0.30 -> 0.25 us a step).
 template <int KIND, int STAGE, class T, int E, int S, int MODE, bool MASKED, bool END, bool ONE>
 __device__ __forceinline__ void rk_stage(T (&y)[S][E], T (&acc)[S][E], T (&t)[S][E],
                                          const SysPrm<T>& P, const Inputs<T, E, S, MODE>& U,
-                                         const Steps<T>& st, const Mask<E, MASKED, END, ONE>& M)
+                                         const Steps<T>& st, const Mask<E, MASKED, END, ONE>& M,
+                                         Edges<T, S>& c)
 {
     T (&in)[S][E] = (STAGE == 1) ? y : t;
+    T (&out)[S][E] = (STAGE == 4) ? y : t;
+    constexpr bool FIX = Mask<E, MASKED, END, ONE>::template indexed<T>();
+    constexpr bool EARLY = !FIX && early_edges<T, E>();
+    if constexpr (!EARLY) {
+#pragma unroll
+        for (int s = 0; s < S; ++s) get_edges<KIND, T, E, S, END>(c, in[s], s, P);
+    }
+    const auto put = [&](int s, int e, T k) {
+        rk_update<STAGE>(k, y[s][e], acc[s][e], t[s][e], st);
+        if (M.template per_cell<T>() && !M.ok(e)) out[s][e] = ghost<KIND, T>();
+    };
+    // the masked slot (Monte Carlo)
+    const auto finish = [&](int s) {
+        if constexpr (FIX) M.fix(out[s], ghost<KIND, T>());
+    };
     if constexpr (KIND == K_CTM) {
-        // Flux form: F_e = min(v y_e, w (c - y_{e+1}), q) = min(v y_e, wc - w y_{e+1}, q),
+        // Flux form: F_e = min(v y_e, w (c - y_{e+1}), q) = min(demand of e,
+        // supply of e+1) with demand min(v y, q) and supply wc - w y,
         // k_e = F_{e-1} - F_e.  Right ghost past the chain's end is -inf, so
-        // the supply term becomes +inf (free outflow); the flux into the
-        // window's first cell arrives from the left lane, 0 at lane 0 (zero
-        // inflow into cell 0).
+        // its supply is +inf (free outflow); the flux into the window's first
+        // cell arrives from the left lane, 0 at lane 0 (zero inflow into cell 0).
         const T v = P.a0, w = P.a1, wc = P.a2, q = P.a3;
-        const bool last_lane = (threadIdx.x & (WAVE - 1)) == WAVE - 1;
+        const auto flux = [&](T ye, T yr) { return minT(minT(v * ye, q), fmaT(-w, yr, wc)); };
 #pragma unroll
         for (int s = 0; s < S; ++s) {
-            T rn = from_right(in[s][0]);
-            if (END) rn = last_lane ? neg_inf<T>() : rn;
-            const T Flast = minT(minT(v * in[s][E - 1], fmaT(-w, rn, wc)), q);
-            T Fprev = from_left(Flast);
+            const T o0 = in[s][0], oE = in[s][E - 1];
+            const T Fout = min_shifted(minT(v * oE, q), c.r[s]);
+            const T Fin = from_left(Fout);
+            const T F0 = E > 1 ? flux(o0, in[s][1]) : Fout;
+            T Fprev = F0;
+            const T FE = E > 2 ? flux(in[s][E - 2], oE) : F0;   // into the last cell
+            if constexpr (E > 1) put(s, E - 1, FE - Fout);
+            put(s, 0, Fin - F0);
+            if constexpr (EARLY) get_edges<KIND, T, E, S, END>(c, out[s], s, P);
 #pragma unroll
-            for (int e = 0; e < E; ++e) {
-                const T F = (e == E - 1) ? Flast : minT(minT(v * in[s][e], fmaT(-w, in[s][e + 1], wc)), q);
+            for (int e = 1; e < E - 1; ++e) {
+                const T F = (e == E - 2) ? FE : flux(in[s][e], in[s][e + 1]);
                 const T k = Fprev - F;
                 Fprev = F;
-                if (STAGE == 4) {
-                    rk_update<4>(k, y[s][e], acc[s][e], t[s][e], st);
-                    if (M.template per_cell<T>() && !M.ok(e)) y[s][e] = neg_inf<T>();
-                } else {
-                    rk_update<STAGE>(k, y[s][e], acc[s][e], t[s][e], st);
-                    if (M.template per_cell<T>() && !M.ok(e)) t[s][e] = neg_inf<T>();
-                }
+                put(s, e, k);
             }
-            if constexpr (MASKED) M.fix(STAGE == 4 ? y[s] : t[s], neg_inf<T>());
+            finish(s);
         }
-    } else if constexpr (KIND == K_RD) {
-        // k = (y_{e-1} - 2 y_e + y_{e+1}) / h^2 - y_e^3 + u, Dirichlet ghosts 0,
-        // regrouped into four fused operations:
-        //   k = (y_{e-1} + y_{e+1}) / h^2 + (u - y_e (y_e^2 + 2 / h^2)).
-        const T ih2 = P.a0, two_ih2 = P.a1;
+    } else if constexpr (KIND == K_RD || S == 1) {
+        const auto f = [&](int s, int e, T left, T mid, T right) {
+            if constexpr (KIND == K_RD) {
+                // k = (y_{e-1} - 2 y_e + y_{e+1}) / h^2 - y_e^3 + u, Dirichlet
+                // ghosts 0, regrouped into four fused operations:
+                //   k = (y_{e-1} + y_{e+1}) / h^2 + (u - y_e (y_e^2 + 2 / h^2)).
+                const T loc = fmaT(-mid, fmaT(mid, mid, P.a1), U.at(s, e));
+                return fmaT(left + right, P.a0, loc);
+            } else {
+                // LIN3, f = aL y_{e-1} + aD y_e + aR y_{e+1} + b u
+                return fmaT(P.a3, U.at(s, e), fmaT(P.a2, right, fmaT(P.a1, mid, P.a0 * left)));
+            }
+        };
 #pragma unroll
         for (int s = 0; s < S; ++s) {
-            const T ln = from_left(in[s][E - 1]);
-            const T rn = from_right(in[s][0]);
-            T left = ln;
-#pragma unroll
-            for (int e = 0; e < E; ++e) {
-                const T mid = in[s][e];
-                const T right = (e == E - 1) ? rn : in[s][e + 1];
-                const T loc = fmaT(-mid, fmaT(mid, mid, two_ih2), U.at(s, e));
-                const T k = fmaT(left + right, ih2, loc);
-                left = mid;
-                if (STAGE == 4) {
-                    rk_update<4>(k, y[s][e], acc[s][e], t[s][e], st);
-                    if (M.template per_cell<T>() && !M.ok(e)) y[s][e] = T(0);
-                } else {
-                    rk_update<STAGE>(k, y[s][e], acc[s][e], t[s][e], st);
-                    if (M.template per_cell<T>() && !M.ok(e)) t[s][e] = T(0);
-                }
+            const T o0 = in[s][0], oE = in[s][E - 1];
+            if constexpr (E == 1) {
+                put(s, 0, f(s, 0, c.l[s], o0, c.r[s]));
+            } else {
+                const T k0 = f(s, 0, c.l[s], o0, in[s][1]);
+                const T kE = f(s, E - 1, in[s][E - 2], oE, c.r[s]);
+                put(s, 0, k0);
+                put(s, E - 1, kE);
             }
-            if constexpr (MASKED) M.fix(STAGE == 4 ? y[s] : t[s], T(0));
+            if constexpr (EARLY) get_edges<KIND, T, E, S, END>(c, out[s], s, P);
+            T left = o0;
+#pragma unroll
+            for (int e = 1; e < E - 1; ++e) {
+                const T mid = in[s][e];
+                const T k = f(s, e, left, mid, (e == E - 2) ? oE : in[s][e + 1]);
+                left = mid;
+                put(s, e, k);
+            }
+            finish(s);
         }
     } else {
-        // LIN3.  S == 1: f = aL y_{e-1} + aD y_e + aR y_{e+1} + b u.
-        // S == 2: d(x, p, xh, ph) with the sign split of aL, aR, b; both sides
-        // of a cell are computed from the old values before either is updated.
+        // LIN3 embedding, d(x, p, xh, ph) with the sign split of aL, aR, b; both
+        // sides of a cell are computed from the old values before either is
+        // updated.
+        static_assert(S == 2, "the coupled chain holds both sides");
         const T aL = P.a0, aD = P.a1, aR = P.a2, b = P.a3;
-        T ln[S], rn[S], left[S];
-#pragma unroll
-        for (int s = 0; s < S; ++s) {
-            ln[s] = from_left(in[s][E - 1]);
-            rn[s] = from_right(in[s][0]);
-            left[s] = ln[s];
-        }
-#pragma unroll
-        for (int e = 0; e < E; ++e) {
-            T mid[S], right[S], k[S];
-#pragma unroll
-            for (int s = 0; s < S; ++s) {
-                mid[s] = in[s][e];
-                right[s] = (e == E - 1) ? rn[s] : in[s][e + 1];
-            }
-            if constexpr (S == 1) {
-                k[0] = fmaT(b, U.at(0, e), fmaT(aR, right[0], fmaT(aD, mid[0], aL * left[0])));
-            } else {
+        const auto d = [&](int s, int e, const T (&left)[2], const T (&mid)[2],
+                           const T (&right)[2]) {
+            const int o = 1 - s;
+            T k = aD * mid[s];
+            if constexpr (KIND == K_LIN3) {
                 const T aLp = aL > T(0) ? aL : T(0), aLn = aL < T(0) ? aL : T(0);
                 const T aRp = aR > T(0) ? aR : T(0), aRn = aR < T(0) ? aR : T(0);
                 const T bp = b > T(0) ? b : T(0), bn = b < T(0) ? b : T(0);
-#pragma unroll
-                for (int s = 0; s < 2; ++s) {
-                    const int o = 1 - s;
-                    T acc0 = aD * mid[s];
-                    acc0 = fmaT(aLp, left[s], acc0);
-                    acc0 = fmaT(aLn, left[o], acc0);
-                    acc0 = fmaT(aRp, right[s], acc0);
-                    acc0 = fmaT(aRn, right[o], acc0);
-                    acc0 = fmaT(bp, U.at(s, e), acc0);
-                    k[s] = fmaT(bn, U.at(o, e), acc0);
-                }
+                k = fmaT(aLp, left[s], k);
+                k = fmaT(aLn, left[o], k);
+                k = fmaT(aRp, right[s], k);
+                k = fmaT(aRn, right[o], k);
+                k = fmaT(bp, U.at(s, e), k);
+                return fmaT(bn, U.at(o, e), k);
+            } else {
+                // the terms with a nonzero coefficient, in the same order; U
+                // holds the input of the side that b selects
+                k = fmaT(aL, left[KIND == K_LIN3M ? o : s], k);
+                k = fmaT(aR, right[s], k);
+                return fmaT(b, U.at(s, e), k);
             }
+        };
+        T o0[2], oE[2], k0[2], kE[2];
 #pragma unroll
-            for (int s = 0; s < S; ++s) {
+        for (int s = 0; s < 2; ++s) {
+            o0[s] = in[s][0];
+            oE[s] = in[s][E - 1];
+        }
+        if constexpr (E == 1) {
+#pragma unroll
+            for (int s = 0; s < 2; ++s) k0[s] = d(s, 0, c.l, o0, c.r);
+        } else {
+            const T i1[2] = {in[0][1], in[1][1]}, iE[2] = {in[0][E - 2], in[1][E - 2]};
+#pragma unroll
+            for (int s = 0; s < 2; ++s) {
+                k0[s] = d(s, 0, c.l, o0, i1);
+                kE[s] = d(s, E - 1, iE, oE, c.r);
+            }
+        }
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+            put(s, 0, k0[s]);
+            if constexpr (E > 1) put(s, E - 1, kE[s]);
+        }
+#pragma unroll
+        for (int s = 0; s < 2; ++s)
+            if constexpr (EARLY) get_edges<KIND, T, E, S, END>(c, out[s], s, P);
+        T left[2] = {o0[0], o0[1]};
+#pragma unroll
+        for (int e = 1; e < E - 1; ++e) {
+            const T mid[2] = {in[0][e], in[1][e]};
+            T right[2], k[2];
+#pragma unroll
+            for (int s = 0; s < 2; ++s) right[s] = (e == E - 2) ? oE[s] : in[s][e + 1];
+#pragma unroll
+            for (int s = 0; s < 2; ++s) k[s] = d(s, e, left, mid, right);
+#pragma unroll
+            for (int s = 0; s < 2; ++s) {
                 left[s] = mid[s];
-                if (STAGE == 4) {
-                    rk_update<4>(k[s], y[s][e], acc[s][e], t[s][e], st);
-                    if (M.template per_cell<T>() && !M.ok(e)) y[s][e] = T(0);
-                } else {
-                    rk_update<STAGE>(k[s], y[s][e], acc[s][e], t[s][e], st);
-                    if (M.template per_cell<T>() && !M.ok(e)) t[s][e] = T(0);
-                }
+                put(s, e, k[s]);
             }
         }
-        if constexpr (MASKED) {
 #pragma unroll
-            for (int s = 0; s < S; ++s) M.fix(STAGE == 4 ? y[s] : t[s], T(0));
-        }
+        for (int s = 0; s < 2; ++s) finish(s);
     }
 }
 
@@ -269,18 +399,18 @@ __device__ __forceinline__ void rk4_steps(T (&y)[S][E], int64_t nsteps, const Sy
                                           const Mask<E, MASKED, END, ONE>& M)
 {
     T acc[S][E], t[S][E];
-    for (int64_t k = 0; k < nsteps; ++k) {
-        rk_stage<KIND, 1>(y, acc, t, P, U, st, M);
-        rk_stage<KIND, 2>(y, acc, t, P, U, st, M);
-        rk_stage<KIND, 3>(y, acc, t, P, U, st, M);
-        rk_stage<KIND, 4>(y, acc, t, P, U, st, M);
+    Edges<T, S> c;
+    first_edges<KIND>(c, P);
+    if constexpr (early_edges<T, E>()) {
+#pragma unroll
+        for (int s = 0; s < S; ++s) get_edges<KIND, T, E, S, END>(c, y[s], s, P);
     }
-}
-
-// Ghost value of a system past the chain's right end.
-template <int KIND, class T> __device__ __forceinline__ T ghost() {
-    if constexpr (KIND == K_CTM) return neg_inf<T>();
-    else return T(0);
+    for (int64_t k = 0; k < nsteps; ++k) {
+        rk_stage<KIND, 1>(y, acc, t, P, U, st, M, c);
+        rk_stage<KIND, 2>(y, acc, t, P, U, st, M, c);
+        rk_stage<KIND, 3>(y, acc, t, P, U, st, M, c);
+        rk_stage<KIND, 4>(y, acc, t, P, U, st, M, c);
+    }
 }
 
 // ------------------------------------------------------------ status --

@@ -13,9 +13,9 @@ enum { STATUS_NONFINITE = 1, STATUS_ORDER = 2 };
 void kernel_params(int kind, const double* prm, double out[5]);
 
 // One HBM pass of the embedding: `ksteps` RK4 steps on every tile.
-// Tile w reads cells [w*OUT, w*OUT + 64E) of src and writes the cells it
-// owns to dst: [0, 64E - H) for tile 0, [w*OUT + H, w*OUT + 64E - H) for
-// the others, up to n for the tile whose window reaches the chain's end.
+// Tile w reads cells [w*OUT, w*OUT + 64E) of src (the last of several tiles
+// [n - 64E, n)) and writes the cells it owns to dst: [0, 64E - H) for tile 0,
+// [w*OUT + H, w*OUT + 64E - H) for the others, up to n for the last one.
 struct EmbedPass {
     const void* src_lo;
     const void* src_hi;
@@ -28,7 +28,7 @@ struct EmbedPass {
     int64_t OUT;      // tile stride (64E - 2H); 0 when W == 1
     int64_t ksteps;   // RK4 steps this pass
     int32_t H;        // halo cells per cut edge (4 * steps per pass)
-    int32_t aligned;  // every array 16-byte aligned
+    int32_t alt;      // LIN3: the sides of odd cells exchanged (set by launch_embed)
     int32_t check;    // last pass: report non-finite / lower > upper
     int32_t per_xcd;  // tiles per XCD in the blockIdx -> tile map
     int32_t nt;       // non-temporal global accesses (a pass whose data is not reused soon)
@@ -42,10 +42,11 @@ struct EmbedPass {
 // does not instantiate.
 // S: sides per wave (2 = lower and upper together, 1 = one side per wave;
 // 1 only for the cooperative CTM and RD chains).  W counts tiles per side.
-// pair (S = 1, W = 1 only): one block of two waves, lower and upper, that
-// also checks lower <= upper (no order-check launch needed); grid unused.
-hipError_t launch_embed(int kind, int mode, int dtype, int E, int S, bool pair,
-                        const EmbedPass& a, int64_t grid, hipStream_t stream);
+// pair (S = 1): blocks of two waves, the lower and the upper side of a window,
+// that with a.check also check lower <= upper (the call's last pass; grid and
+// a.per_xcd then count W blocks).
+hipError_t launch_embed(int kind, int mode, int dtype, int E, int S, bool pair, EmbedPass a,
+                        int64_t grid, hipStream_t stream);
 bool embed_has_shape(int kind, int dtype, int E, int S);
 int embed_max_E(int dtype, int S);
 // Flags lower > upper anywhere in a finished box.

@@ -277,8 +277,6 @@ reach_status chains_only(reach_ctx* c, const reach_system* s, const char* what) 
 
 void kernel_prm(const reach_system* s, double out[5]) { kernel_params(s->kind, s->prm, out); }
 
-bool aligned16(const void* p) { return ((uintptr_t)p & 15u) == 0; }
-
 int ceil_pow2_E(int64_t n) {
     int E = 1;
     while ((int64_t)64 * E < n) E *= 2;
@@ -324,16 +322,125 @@ TuneEntry tuned(const reach_ctx* c, int kind, int dtype, int64_t n, bool cell_in
 }
 
 int smallest_E(int kind, int dtype, int S, int64_t n) {
-    for (int E : {1, 2, 4, 8, 12, 16, 24, 28, 32, 48, 64})
+    for (int E : {1, 2, 4, 6, 8, 12, 16, 20, 24, 28, 32, 48, 64})
         if (embed_has_shape(kind, dtype, E, S) && (int64_t)64 * E >= n) return E;
     return 0;
 }
 
+// A multi-window plan's windows: steps per pass K, halo, stride, count.
+void set_windows(EmbedPlan* p, int E, int S, int64_t K, int64_t n, int64_t nsteps) {
+    const int64_t span = (int64_t)64 * E;
+    p->E = E;
+    p->S = S;
+    p->K = (int)K;
+    p->H = (int)(4 * K);
+    p->OUT = span - 2 * p->H;
+    p->W = (n <= span) ? 1 : 1 + (n - span + p->OUT - 1) / p->OUT;
+    p->passes = (nsteps + K - 1) / K;
+}
+
+// Estimated time of one RK4 step (microseconds) of a chain whose windows do not
+// fill the chip several times over, at E cells per lane and K steps per pass
+// (measured on MI355X, chains of 12000 to 10^6 cells):
+//   - a wave with its SIMD to itself takes c E + 0.06 us per step, c the issue
+//     time of one cell (both sides for S = 2); the launch waits for the SIMDs
+//     that hold the most waves, so r waves cost r c E;
+//   - every pass costs 2.5 us of launch, first loads and last stores, plus the
+//     reading and writing of the state at 7 TB/s (the waves of so few rounds
+//     load, compute and store at the same time, so this is not hidden).
+// Windows of more than 256 registers run one to a SIMD; they count only where
+// no SIMD gets a second one.
+double step_us(int kind, int dtype, bool cell_in, int S, int E, int64_t K, int64_t n,
+               int64_t simds) {
+    const int64_t span = (int64_t)64 * E;
+    if (8 * K >= span) return 1e300;
+    const int64_t OUT = span - 8 * K;
+    const int64_t W = n <= span ? 1 : 1 + (n - span + OUT - 1) / OUT;
+    const int64_t r = ((S == 1 ? 2 : 1) * W + simds - 1) / simds;
+    const bool f64 = dtype == REACH_F64;
+    const int wide = S == 2 ? (f64 ? (cell_in ? 8 : 12) : 16)
+                            : (f64 ? (cell_in ? 24 : 28) : 48);
+    if (E > wide && r > 1) return 1e300;
+    const double c = kind == REACH_LIN3 ? 0.0765 : kind == REACH_RD ? 0.0438 : f64 ? 0.051 : 0.040;
+    const double bytes = (double)n * (f64 ? 8.0 : 4.0) * (cell_in ? 6.0 : 4.0);
+    return (double)r * c * E + 0.06 + (2.5 + bytes / 7.0e6) / (double)K;
+}
+
+// The shape of the least estimated step time, at K steps per pass (K = 0: the
+// best K as well, up to 64).
+TuneEntry fastest_shape(int kind, int dtype, bool cell_in, int64_t n, int64_t simds, int64_t K) {
+    const int S = kind == REACH_LIN3 ? 2 : 1;
+    TuneEntry best{0, 0, S};
+    double t_best = 1e300;
+    for (int E : {1, 2, 4, 6, 8, 12, 16, 20, 24, 28, 32, 48, 64}) {
+        if (!embed_has_shape(kind, dtype, E, S)) continue;
+        const int64_t top = std::min<int64_t>(64, 8 * E - 1);
+        for (int64_t k = K ? K : std::min<int64_t>(4, top); k <= (K ? K : top); ++k) {
+            const double t = step_us(kind, dtype, cell_in, S, E, k, n, simds);
+            if (t < t_best) { t_best = t; best.E = E; best.K = (int)k; }
+        }
+    }
+    return best;
+}
+
+// The estimate decides on chains whose default windows put at most 8 waves on a
+// SIMD; longer ones keep the shapes measured at 2^26 and 2^31 cells (there the
+// rounds run into each other and the last one weighs little).
+bool estimated(int kind, int dtype, bool cell_in, int64_t n, int64_t simds) {
+    const TuneEntry d = default_tune(kind, dtype, cell_in, n);
+    const int64_t OUT = (int64_t)64 * d.E - 8 * d.K;
+    return (d.S == 1 ? 2 : 1) * (n / OUT) <= 8 * simds;
+}
+
+// Runs of at most this many steps keep a chain that one window holds in one
+// window (no workspace, one launch): splitting it would save a few microseconds.
+constexpr int64_t kSplitSteps = 8;
+
+// Default shape of a multi-window run of many steps.
+TuneEntry default_shape(const reach_ctx* c, int kind, int dtype, bool cell_in, int64_t n) {
+    const int64_t simds = (int64_t)4 * c->cus;
+    if (kind != REACH_HEAT3D && estimated(kind, dtype, cell_in, n, simds)) {
+        const TuneEntry t = fastest_shape(kind, dtype, cell_in, n, simds, 0);
+        if (t.E) return t;
+    }
+    return default_tune(kind, dtype, cell_in, n);
+}
+
+// split: the caller has the workspace of a multi-pass run, so that a chain may
+// be cut into more windows and passes than the fewest.
 reach_status plan_embed(reach_ctx* c, const reach_system* s, reach_dtype dtype, int64_t nsteps,
-                        EmbedPlan* p) {
+                        EmbedPlan* p, bool split = true) {
     const int64_t n = s->n;
+    const bool cell_in = s->n_in > 1;
     const int64_t oE = opt_get(c, "embed.E"), oK = opt_get(c, "embed.K"), oS = opt_get(c, "embed.S");
-    const TuneEntry te = tuned(c, s->kind, dtype, n, s->n_in > 1);
+    const bool tuned_here = c->tune.count({s->kind, dtype, n_bucket(n), cell_in ? 1 : 0}) != 0;
+    const int64_t simds = (int64_t)4 * c->cus;
+    if (split && !oE && !oK && !oS && !tuned_here &&
+        estimated(s->kind, dtype, cell_in, n, simds)) {
+        const int one = smallest_E(s->kind, dtype, s->kind == REACH_LIN3 ? 2 : 1, n);
+        if (!one || nsteps > kSplitSteps) {
+            // the best K for many steps gives the pass count; the steps are
+            // spread evenly over the passes, and the shape is the best for those
+            const TuneEntry t = fastest_shape(s->kind, dtype, cell_in, n, simds, 0);
+            const int64_t steps = std::max<int64_t>(nsteps, 1);
+            const int64_t passes = (steps + t.K - 1) / t.K;
+            const int64_t K = (steps + passes - 1) / passes;
+            const TuneEntry u = fastest_shape(s->kind, dtype, cell_in, n, simds, K);
+            // one window: the launch once, padding selects (a third more
+            // instructions) unless the chain fills it
+            const double c1 = step_us(s->kind, dtype, cell_in, t.S, one ? one : 1, 1, 1, simds);
+            const double one_us =
+                one ? 2.5 + (double)steps * (c1 - 2.5) * (n == (int64_t)64 * one ? 1.0 : 1.33)
+                    : 1e300;
+            const double many_us =
+                (double)steps * step_us(s->kind, dtype, cell_in, t.S, u.E, K, n, simds);
+            if (u.E && many_us < one_us) {
+                set_windows(p, u.E, u.S, K, n, nsteps);
+                if (p->W > 1) return REACH_OK;
+            }
+        }
+    }
+    const TuneEntry te = tuned(c, s->kind, dtype, n, cell_in);
     int S = oS ? (int)oS : (oE ? (s->kind == REACH_LIN3 ? 2 : te.S) : te.S);
     if (s->kind == REACH_LIN3 && S == 1)
         return fail(c, REACH_E_INVAL, "the coupled LIN3 chain needs both sides per wave");
@@ -364,11 +471,7 @@ reach_status plan_embed(reach_ctx* c, const reach_system* s, reach_dtype dtype, 
         const int64_t passes = (nsteps + K - 1) / K;
         K = (int)((nsteps + passes - 1) / passes);
     }
-    p->K = K;
-    p->H = 4 * K;
-    p->OUT = span - 2 * p->H;
-    p->W = (n <= span) ? 1 : 1 + (n - span + p->OUT - 1) / p->OUT;
-    p->passes = (nsteps + K - 1) / K;
+    set_windows(p, E, S, K, n, nsteps);
     return REACH_OK;
 }
 
@@ -618,8 +721,9 @@ reach_status autotune_heat3d(reach_ctx* c, const reach_system* s, reach_dtype dt
 size_t embed_ws_bytes(reach_ctx* c, const reach_system* s, reach_dtype dtype) {
     if (s->kind == REACH_HEAT3D) return (size_t)2 * (size_t)s->n * dsize(dtype);
     EmbedPlan p;
-    if (plan_embed(c, s, dtype, 2 * (int64_t)std::max(1, (int)opt_get(c, "embed.K")), &p) != REACH_OK)
-        return (size_t)-1;
+    // enough for a run of any length: a long one may cut a chain that a short
+    // one keeps in one window
+    if (plan_embed(c, s, dtype, (int64_t)1 << 20, &p) != REACH_OK) return (size_t)-1;
     if (p.W == 1) return 0;
     return (size_t)2 * (size_t)s->n * dsize(dtype);
 }
@@ -861,7 +965,8 @@ reach_status reach_embed_rk4(reach_ctx* c, const reach_system* s, reach_dtype dt
     if (s->kind == REACH_HEAT3D)
         return embed_heat3d(c, s, dtype, x_lo, x_hi, dt, nsteps, r_lo, r_hi, ws, ws_bytes, hs);
     EmbedPlan pl;
-    st = plan_embed(c, s, dtype, nsteps, &pl);
+    const bool have_ws = ws && ws_bytes >= 2 * bytes;
+    st = plan_embed(c, s, dtype, nsteps, &pl, have_ws);
     if (st != REACH_OK) return st;
     log_call(c, "\"call\": \"embed\", \"kind\": %d, \"dtype\": \"%s\", \"n\": %lld, "
                 "\"nsteps\": %lld, \"E\": %d, \"K\": %d, \"S\": %d, \"tiles\": %lld, "
@@ -889,19 +994,11 @@ reach_status reach_embed_rk4(reach_ctx* c, const reach_system* s, reach_dtype dt
     EmbedPass a{};
     a.p_lo = p_lo; a.p_hi = p_hi;
     a.n = s->n; a.W = pl.W; a.OUT = pl.OUT; a.H = pl.H;
-    a.aligned = aligned16(x_lo) && aligned16(x_hi) && aligned16(r_lo) && aligned16(r_hi) &&
-                (!need_ws || (aligned16(w_lo) && aligned16(w_hi)));
-    const int64_t tiles = pl.S == 1 ? 2 * pl.W : pl.W;
-    a.per_xcd = (int32_t)((tiles + 7) / 8);
     kernel_prm(s, a.prm);
     a.h2 = dt / 2.0; a.dt = dt; a.dt6 = dt / 6.0;
     a.status = c->status;
     const int mode = s->n_in > 1 ? 1 : 0;   // per-cell inputs
     if (s->n_in == 0) { a.p_lo = nullptr; a.p_hi = nullptr; }
-    const int64_t grid = 8 * (int64_t)a.per_xcd;
-    // one window, one side per wave: both waves in one block, which checks
-    // the order itself
-    const bool pair = pl.S == 1 && pl.W == 1;
     int64_t done = 0;
     for (int64_t p = 0; p < pl.passes; ++p) {
         a.src_lo = lo_of[io[p].first];
@@ -913,15 +1010,16 @@ reach_status reach_embed_rk4(reach_ctx* c, const reach_system* s, reach_dtype dt
         // a one-step pass is a pure stream: its reads and writes bypass the
         // caches' retention (non-temporal), 1.8% faster at 2^26 cells
         a.nt = a.ksteps == 1 ? 1 : 0;
+        // one side per wave: the last pass has both sides of a window in one
+        // block, which checks the order
+        const bool pair = pl.S == 1 && a.check;
+        const int64_t tiles = pl.S == 1 && !pair ? 2 * pl.W : pl.W;
+        a.per_xcd = (int32_t)((tiles + 7) / 8);
+        const int64_t grid = 8 * (int64_t)a.per_xcd;
         hipError_t e = launch_embed(s->kind, mode, dtype == REACH_F64 ? 0 : 1, pl.E, pl.S, pair,
                                     a, grid, hs);
         if (e != hipSuccess) return hip_fail(c, e, "embedding kernel launch");
         done += a.ksteps;
-    }
-    if (pl.S == 1 && !pair) {
-        hipError_t e = launch_order_check(dtype == REACH_F64 ? 0 : 1, lo_of[io.back().second],
-                                          hi_of[io.back().second], s->n, c->status, hs);
-        if (e != hipSuccess) return hip_fail(c, e, "order check launch");
     }
     if (final_copy) {
         HIPCHK(c, hipMemcpyAsync(r_lo, w_lo, bytes, hipMemcpyDeviceToDevice, hs));
@@ -1027,11 +1125,12 @@ reach_status reach_autotune_embed(reach_ctx* c, const reach_system* s, reach_dty
                          [](const auto& a, const auto& b) { return a.first < b.first; });
         std::vector<TuneEntry> finals;
         for (size_t q = 0; q < scan.size() && q < 4; ++q) finals.push_back(scan[q].second);
-        const TuneEntry d = default_tune(s->kind, dtype, s->n_in > 1, s->n);
+        const TuneEntry d = default_shape(c, s->kind, dtype, s->n_in > 1, s->n);
         bool have_d = false;
         for (const auto& f : finals) have_d |= (f.E == d.E && f.K == d.K && f.S == d.S);
+        // (a default of a K between the scanned ones is timed with the finals)
         for (const auto& q : scan)
-            if (!have_d && q.second.E == d.E && q.second.K == d.K && q.second.S == d.S) {
+            if (!have_d && q.second.E == d.E && q.second.S == d.S && 8 * d.K < 64 * d.E) {
                 finals.push_back(d);
                 have_d = true;
             }
