@@ -1,115 +1,113 @@
 // Contraction / growth-bound reachable box on gfx950 (PIRK Sec. 2.1,
 // Algorithm 2).
 //
-// Two RK4 runs share every launch: tiles [0, W) integrate the center of the
-// box with the system's own f at the center input, tiles [W, 2W) integrate the
-// half-width with the linear growth dynamics r' = C r + |b| [p], C the
-// tridiagonal contraction matrix.  Each wave holds one run's window in
-// registers, exactly like the one-side embedding tiles (same per-cell code,
-// same temporal blocking and halos).  The first pass forms c = (lo + hi) / 2 or
-// r = (hi - lo) / 2 as it loads the box; a final elementwise kernel writes
-// [c - r, c + r].
+// Two RK4 runs share every launch: a block's first wave integrates the center
+// of the box with the system's own f at the center input, its second wave the
+// half-width of the same window with the linear growth dynamics
+// r' = C r + |b| [p], C the tridiagonal contraction matrix.  Each wave holds one
+// run's window in registers, exactly like the one-side embedding tiles (same
+// per-cell code, transfers, temporal blocking and halos).  The first pass forms
+// c = (lo + hi) / 2 or r = (hi - lo) / 2 as it loads the box.  In the last pass
+// the two waves exchange their windows through LDS and write [c - r, c + r]
+// themselves: a separate combining kernel reads c and r and writes the box
+// again, 64 bytes per FP64 cell (it remains for calls whose result arrays
+// overlap what the last pass still reads).
 #include <algorithm>
 
-#include "dev.hpp"
 #include "kernels.hpp"
+#include "tile_io.hpp"
 
 namespace reach {
 
-template <class T> struct Vec16g;
-template <> struct Vec16g<double> { typedef double type __attribute__((ext_vector_type(2))); };
-template <> struct Vec16g<float> { typedef float type __attribute__((ext_vector_type(4))); };
-
-// Cells [ts, ts + 64E) of src into registers, cells >= n get `fill`.
-template <class T, int E>
-__device__ __forceinline__ void gb_load(T (&dst)[E], const T* __restrict__ src, int64_t ts,
-                                        int64_t n, T fill) {
-    const int lane = threadIdx.x;
-#pragma unroll
-    for (int e = 0; e < E; ++e) {
-        const int64_t g = ts + (int64_t)lane * E + e;
-        dst[e] = (g < n) ? src[g] : fill;
-    }
-}
-
 template <int KIND, class T, int E, int MODE>
-__global__ __launch_bounds__(64) void gb_tile_kernel(GbPass a) {
-    const int lane = threadIdx.x;
+__global__ __launch_bounds__(2 * WAVE, E * sizeof(T) <= 192 ? 2 : 1)
+void gb_tile_kernel(GbPass a) {
+    using IO = TileIO<T, E>;
+    constexpr int ROW = IO::STAGED ? IO::ROW : E;
+    constexpr int LDS = IO::STAGED ? IO::LDS_ELEMS : WAVE * E;
+    __shared__ __attribute__((aligned(16))) T lds[2 * LDS];
+    const int lane = threadIdx.x & (WAVE - 1);
+    const int side = (int)(threadIdx.x / WAVE);      // 0: center run, 1: half-width run
     const int64_t b = blockIdx.x;
-    const int64_t g = (b & 7) * (int64_t)a.per_xcd + (b >> 3);
-    if (g >= 2 * a.W) return;
-    const int side = g >= a.W ? 1 : 0;          // 0: center run, 1: half-width run
-    const int64_t w = g - side * a.W;
+    const int64_t w = (b & 7) * (int64_t)a.per_xcd + (b >> 3);
+    if (w >= a.W) return;
+    T* const my_lds = lds + side * LDS;
+    // the last of several windows ends with the chain (see embed_tile_kernel)
     const int64_t span = (int64_t)WAVE * E;
-    const int64_t ts = w * a.OUT;
+    const int64_t ts = w == a.W - 1 && w > 0 ? a.n - span : w * a.OUT;
     const bool reaches_end = ts + span >= a.n;
+    const bool fast = ts + span <= a.n;
+    const int64_t left = a.n - (ts + (int64_t)lane * E);
+    const int nvalid = (int)(left < 0 ? 0 : (left > E ? E : left));
 
+    // center p = (lo + hi) / 2 or half-width (hi - lo) / 2 of an interval
+    const auto part = [side](T lo, T hi) { return side == 0 ? (lo + hi) / T(2) : (hi - lo) / T(2); };
+    const T out = side == 0 ? ghost<KIND, T>() : T(0);   // cells past the chain
     T y[1][E];
     if (a.first) {
-        // c = (lo + hi) / 2, r = (hi - lo) / 2 (ghost cells: the center run's
-        // ghost, radius 0)
-        T lo[E], hi[E];
-        gb_load<T, E>(lo, (const T*)a.x_lo, ts, a.n, T(0));
-        gb_load<T, E>(hi, (const T*)a.x_hi, ts, a.n, T(0));
+        T hi[E];
+        IO::load(y[0], (const T*)a.x_lo, ts, a.n, T(0), fast, a.nt, my_lds);
+        IO::load(hi, (const T*)a.x_hi, ts, a.n, T(0), fast, a.nt, my_lds);
 #pragma unroll
-        for (int e = 0; e < E; ++e) {
-            const int64_t c = ts + (int64_t)lane * E + e;
-            if (side == 0) y[0][e] = (c < a.n) ? (lo[e] + hi[e]) / T(2) : ghost<KIND, T>();
-            else y[0][e] = (c < a.n) ? (hi[e] - lo[e]) / T(2) : T(0);
-        }
+        for (int e = 0; e < E; ++e) y[0][e] = e < nvalid ? part(y[0][e], hi[e]) : out;
     } else {
-        const T* src = (const T*)(side == 0 ? a.src_c : a.src_r);
-        gb_load<T, E>(y[0], src, ts, a.n, side == 0 ? ghost<KIND, T>() : T(0));
+        IO::load(y[0], (const T*)(side == 0 ? a.src_c : a.src_r), ts, a.n, out, fast, a.nt, my_lds);
     }
 
-    // inputs: center p* = (p_lo + p_hi) / 2, half-width [p] = (p_hi - p_lo) / 2
     Inputs<T, E, 1, MODE> U;
     const T* pl = (const T*)a.p_lo;
     const T* ph = (const T*)a.p_hi;
     if constexpr (MODE == IN_SCALAR) {
-        if (pl) U.u[0] = side == 0 ? (pl[0] + ph[0]) / T(2) : (ph[0] - pl[0]) / T(2);
-        else U.u[0] = T(0);
+        U.u[0] = pl ? part(pl[0], ph[0]) : T(0);
     } else {
+        T hi[E];
+        IO::load(U.u[0], pl, ts, a.n, T(0), fast, false, my_lds);
+        IO::load(hi, ph, ts, a.n, T(0), fast, false, my_lds);
 #pragma unroll
-        for (int e = 0; e < E; ++e) {
-            const int64_t c = ts + (int64_t)lane * E + e;
-            T u = T(0);
-            if (c < a.n) u = side == 0 ? (pl[c] + ph[c]) / T(2) : (ph[c] - pl[c]) / T(2);
-            U.u[0][e] = u;
-        }
+        for (int e = 0; e < E; ++e) U.u[0][e] = part(U.u[0][e], hi[e]);
     }
     const Steps<T> st = {(T)a.h2, (T)a.dt, (T)a.dt6};
-    const int64_t left = a.n - (ts + (int64_t)lane * E);
-    const int nvalid = (int)(left < 0 ? 0 : (left > E ? E : left));
+    const SysPrm<T> P = make_prm<T>(side == 0 ? a.prm : a.prm_r);
 
+    const Mask<E, false, false> inner{E};
+    const Mask<E, false, true> end{E};
+    const Mask<E, true, true> padded{nvalid};
     if (side == 0) {
-        const SysPrm<T> P = {(T)a.prm[0], (T)a.prm[1], (T)a.prm[2], (T)a.prm[3], (T)a.prm[4]};
-        if (reaches_end) {
-            Mask<E, true, true> M{nvalid};
-            rk4_steps<KIND, T, E, 1, MODE>(y, a.ksteps, P, U, st, M);
-        } else {
-            Mask<E, false, false> M{E};
-            rk4_steps<KIND, T, E, 1, MODE>(y, a.ksteps, P, U, st, M);
-        }
+        if (!fast) rk4_steps<KIND, T, E, 1, MODE>(y, a.ksteps, P, U, st, padded);
+        else if (KIND == K_CTM && reaches_end) rk4_steps<KIND, T, E, 1, MODE>(y, a.ksteps, P, U, st, end);
+        else rk4_steps<KIND, T, E, 1, MODE>(y, a.ksteps, P, U, st, inner);
     } else {
-        const SysPrm<T> P = {(T)a.prm_r[0], (T)a.prm_r[1], (T)a.prm_r[2], (T)a.prm_r[3], T(0)};
-        if (reaches_end) {
-            Mask<E, true, true> M{nvalid};
-            rk4_steps<K_LIN3, T, E, 1, MODE>(y, a.ksteps, P, U, st, M);
-        } else {
-            Mask<E, false, false> M{E};
-            rk4_steps<K_LIN3, T, E, 1, MODE>(y, a.ksteps, P, U, st, M);
-        }
+        if (!fast) rk4_steps<K_LIN3, T, E, 1, MODE>(y, a.ksteps, P, U, st, padded);
+        else rk4_steps<K_LIN3, T, E, 1, MODE>(y, a.ksteps, P, U, st, inner);
     }
 
-    const int olo = (w == 0) ? 0 : a.H;
+    const int olo = (w == 0) ? 0 : a.H + (int)(w * a.OUT - ts);
     const int ohi = reaches_end ? (int)(a.n - ts) : (int)(span - a.H);
-    T* dst = (T*)(side == 0 ? a.dst_c : a.dst_r);
+    if (!a.last) {
+        IO::store(y[0], (T*)(side == 0 ? a.dst_c : a.dst_r), ts, olo, ohi, fast, a.nt, my_lds);
+        return;
+    }
+    // [c - r, c + r]: the center wave writes the lower vector, the other the upper
+#pragma unroll
+    for (int e = 0; e < E; ++e) my_lds[lane * ROW + e] = y[0][e];
+    __syncthreads();
+    const T* const other = lds + (1 - side) * LDS;
+    unsigned bits = 0;
 #pragma unroll
     for (int e = 0; e < E; ++e) {
+        const T o = other[lane * ROW + e];
+        const T c = side == 0 ? y[0][e] : o, r = side == 0 ? o : y[0][e];
+        const T lo = c - r, hi = c + r;
         const int el = lane * E + e;
-        if (el >= olo && el < ohi) dst[ts + el] = y[0][e];
+        if (el >= olo && el < ohi) {
+            if (!finiteT(lo) || !finiteT(hi)) bits |= ST_NONFINITE;
+            if (lo > hi) bits |= ST_ORDER;
+        }
+        y[0][e] = side == 0 ? lo : hi;
     }
+    __syncthreads();   // both have read before the rows stage the stores
+    IO::store(y[0], (T*)(side == 0 ? a.r_lo : a.r_hi), ts, olo, ohi, fast, a.nt, my_lds);
+    report_status(a.status, bits);
 }
 
 template <class T>
@@ -131,7 +129,7 @@ __global__ __launch_bounds__(256) void gb_combine_kernel(const T* __restrict__ c
 
 template <int KIND, class T, int E, int MODE>
 static hipError_t go_gb(const GbPass& a, int64_t grid, hipStream_t s) {
-    hipLaunchKernelGGL((gb_tile_kernel<KIND, T, E, MODE>), dim3((unsigned)grid), dim3(WAVE), 0,
+    hipLaunchKernelGGL((gb_tile_kernel<KIND, T, E, MODE>), dim3((unsigned)grid), dim3(2 * WAVE), 0,
                        s, a);
     return hipGetLastError();
 }
@@ -140,9 +138,12 @@ template <int KIND, class T, int MODE>
 static hipError_t gb_by_E(int E, const GbPass& a, int64_t grid, hipStream_t s) {
     switch (E) {
         case 1: return go_gb<KIND, T, 1, MODE>(a, grid, s);
+        case 2: return go_gb<KIND, T, 2, MODE>(a, grid, s);
         case 4: return go_gb<KIND, T, 4, MODE>(a, grid, s);
         case 8: return go_gb<KIND, T, 8, MODE>(a, grid, s);
+        case 12: return go_gb<KIND, T, 12, MODE>(a, grid, s);
         case 16: return go_gb<KIND, T, 16, MODE>(a, grid, s);
+        case 20: return go_gb<KIND, T, 20, MODE>(a, grid, s);
         case 24: return go_gb<KIND, T, 24, MODE>(a, grid, s);
         case 28: return go_gb<KIND, T, 28, MODE>(a, grid, s);
         case 32: return go_gb<KIND, T, 32, MODE>(a, grid, s);
@@ -151,7 +152,8 @@ static hipError_t gb_by_E(int E, const GbPass& a, int64_t grid, hipStream_t s) {
 }
 
 bool gb_has_E(int E) {
-    return E == 1 || E == 4 || E == 8 || E == 16 || E == 24 || E == 28 || E == 32;
+    return E == 1 || E == 2 || E == 4 || E == 8 || E == 12 || E == 16 || E == 20 || E == 24 ||
+           E == 28 || E == 32;
 }
 
 hipError_t launch_gb(int kind, int mode, int dtype, int E, const GbPass& a, int64_t grid,

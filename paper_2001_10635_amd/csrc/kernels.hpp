@@ -53,8 +53,9 @@ int embed_max_E(int dtype, int S);
 hipError_t launch_order_check(int dtype, const void* lo, const void* hi, int64_t n,
                               unsigned int* status, hipStream_t stream);
 
-// One pass of the growth-bound method: tiles [0, W) advance the center, tiles
-// [W, 2W) the half-width; `first` forms them from the box (x_lo, x_hi).
+// One pass of the growth-bound method: W blocks of two waves, which advance the
+// center and the half-width of a window; `first` forms them from the box
+// (x_lo, x_hi), `last` writes the box (r_lo, r_hi) instead of (dst_c, dst_r).
 struct GbPass {
     const void* x_lo;
     const void* x_hi;
@@ -65,7 +66,10 @@ struct GbPass {
     const void* p_lo;
     const void* p_hi;
     int64_t n, W, OUT, ksteps;
-    int32_t H, first, per_xcd, pad;
+    int32_t H, first, last, per_xcd, nt;
+    void* r_lo;
+    void* r_hi;
+    unsigned int* status;
     double prm[5];     // the system (kernel_params)
     double prm_r[5];   // the growth dynamics: {C_sub, C_diag, C_sup, |b|}
     double h2, dt, dt6;

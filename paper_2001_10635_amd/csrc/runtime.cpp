@@ -300,8 +300,17 @@ struct EmbedPlan {
 // and size.
 TuneEntry default_tune(int kind, int dtype, bool cell_in, int64_t n) {
     if (kind == REACH_HEAT3D) return TuneEntry{2, 1, 1};   // rows per wave, 16 waves per block
-    if (kind == REACH_LIN3) return dtype == REACH_F64 ? TuneEntry{12, 12, 2} : TuneEntry{16, 8, 2};
-    if (dtype == REACH_F32) return TuneEntry{48, 12, 1};
+    // LIN3, 2^24 cells, us per step: FP64 per-cell inputs 43.2 at 12 cells (over
+    // 256 VGPRs there) and 32.1 at 8, scalar 29.0 at 12 and 30.8 at 8; FP32
+    // scalar 22.5 at 16 and 23.4 at 12, per-cell 23.9 and 23.4
+    if (kind == REACH_LIN3) {
+        if (dtype == REACH_F64) return cell_in ? TuneEntry{8, 10, 2} : TuneEntry{12, 12, 2};
+        return cell_in ? TuneEntry{12, 10, 2} : TuneEntry{16, 12, 2};
+    }
+    // FP32 instructions of different waves overlap, so three waves per SIMD at
+    // 32 cells beat two at 48: CTM 2^27 153 against 175 us per step, RD 2^25 37.4
+    // against 43.3 (per-cell inputs: 41.4 at 24, 42.7 at 32)
+    if (dtype == REACH_F32) return cell_in ? TuneEntry{24, 12, 1} : TuneEntry{32, 12, 1};
     // RD with shared inputs fits 28 cells per lane in 256 VGPRs (the CTM
     // chain and per-cell inputs need more there).  The wider tile pays on
     // long chains (2^26: 1.5% faster); below that its fewer waves leave a
@@ -367,13 +376,15 @@ double step_us(int kind, int dtype, bool cell_in, int S, int E, int64_t K, int64
 }
 
 // The shape of the least estimated step time, at K steps per pass (K = 0: the
-// best K as well, up to 64).
-TuneEntry fastest_shape(int kind, int dtype, bool cell_in, int64_t n, int64_t simds, int64_t K) {
+// best K as well, up to 64), among the embedding's shapes or (gb) the growth
+// bound's.
+TuneEntry fastest_shape(int kind, int dtype, bool cell_in, int64_t n, int64_t simds, int64_t K,
+                        bool gb = false) {
     const int S = kind == REACH_LIN3 ? 2 : 1;
     TuneEntry best{0, 0, S};
     double t_best = 1e300;
     for (int E : {1, 2, 4, 6, 8, 12, 16, 20, 24, 28, 32, 48, 64}) {
-        if (!embed_has_shape(kind, dtype, E, S)) continue;
+        if (gb ? !gb_has_E(E) : !embed_has_shape(kind, dtype, E, S)) continue;
         const int64_t top = std::min<int64_t>(64, 8 * E - 1);
         for (int64_t k = K ? K : std::min<int64_t>(4, top); k <= (K ? K : top); ++k) {
             const double t = step_us(kind, dtype, cell_in, S, E, k, n, simds);
@@ -1287,20 +1298,42 @@ reach_status reach_growth_bound(reach_ctx* c, const reach_system* s, reach_dtype
     hipStream_t hs = (hipStream_t)stream;
     if (s->kind == REACH_HEAT3D)
         return gb_heat3d(c, s, dtype, x_lo, x_hi, dt, nsteps, r_lo, r_hi, ws, hs);
-    // plan: one side per wave, as the one-side embedding tiles
+    // plan: the windows of the one-side embedding tiles (both runs cost a cell
+    // what an RD cell costs; K_LIN3's own embedding runs both sides per wave, so
+    // its shapes are not asked for)
     int E = (int)opt_get(c, "gb.E");
     int K = (int)opt_get(c, "gb.K");
     if (E && !gb_has_E(E)) return fail(c, REACH_E_INVAL, "gb.E = %d not built", E);
     const int64_t n = s->n;
+    const bool cell_in = s->n_in > 1;
+    const int like = s->kind == REACH_CTM ? REACH_CTM : REACH_RD;
     bool single = false;
     if (!E) {
-        for (int e : {1, 4, 8, 16, 24, 28, 32})
-            if ((int64_t)64 * e >= n) { E = e; break; }
-        if (E && !K) single = true;
-        // FP64 with shared inputs fits 28 cells per lane in 256 VGPRs (two
-        // waves per SIMD; per-cell inputs need more there), which pays on long
-        // chains only (see default_tune)
-        if (!E) E = dtype == REACH_F64 ? (s->n_in > 1 || n < ((int64_t)1 << 26) ? 24 : 28) : 32;
+        int one = 0;
+        for (int e : {1, 2, 4, 8, 12, 16, 20, 24, 28, 32})
+            if ((int64_t)64 * e >= n) { one = e; break; }
+        const int64_t simds = (int64_t)4 * c->cus;
+        TuneEntry t{0, 0, 1};
+        if (!K && nsteps > 0 && estimated(like, dtype, cell_in, n, simds)) {
+            t = fastest_shape(like, dtype, cell_in, n, simds, 0, true);
+            const int64_t passes = (nsteps + t.K - 1) / t.K;
+            t.K = (int)((nsteps + passes - 1) / passes);
+            t = fastest_shape(like, dtype, cell_in, n, simds, t.K, true);
+            if ((int64_t)64 * t.E >= n) t.E = 0;   // one window: no passes at all
+            else if (one && nsteps <= kSplitSteps) t.E = 0;
+        }
+        if (t.E) {
+            E = t.E;
+            K = t.K;
+        } else if (one) {
+            E = one;
+            single = !K;
+        } else {
+            // FP64 with shared inputs fits 28 cells per lane in 256 VGPRs (two
+            // waves per SIMD; per-cell inputs need more there), which pays on
+            // long chains only (see default_tune)
+            E = dtype == REACH_F64 ? (cell_in || n < ((int64_t)1 << 26) ? 24 : 28) : 32;
+        }
     } else if ((int64_t)64 * E >= n && !K) {
         single = true;
     }
@@ -1329,8 +1362,24 @@ reach_status reach_growth_bound(reach_ctx* c, const reach_system* s, reach_dtype
         a.W = (n <= span) ? 1 : 1 + (n - span + a.OUT - 1) / a.OUT;
         passes = std::max<int64_t>(1, (nsteps + K - 1) / K);
     }
-    a.per_xcd = (int32_t)((2 * a.W + 7) / 8);
+    a.per_xcd = (int32_t)((a.W + 7) / 8);
     const int64_t grid = 8 * (int64_t)a.per_xcd;
+    // The last pass writes the box itself unless the result arrays overlap what
+    // other windows still read then (per-cell inputs; in a run of one pass the
+    // box): such a call combines in a kernel of its own.
+    const auto overlap = [](const void* p, size_t np, const void* q, size_t nq) {
+        return p && (const char*)p < (const char*)q + nq && (const char*)q < (const char*)p + np;
+    };
+    const size_t in_bytes = (size_t)s->n_in * dsize(dtype);
+    bool fused = true;
+    if (a.W > 1)
+        for (const void* q : {(const void*)r_lo, (const void*)r_hi}) {
+            fused &= !overlap(a.p_lo, in_bytes, q, bytes) && !overlap(a.p_hi, in_bytes, q, bytes);
+            if (passes == 1)
+                fused &= !overlap(x_lo, bytes, q, bytes) && !overlap(x_hi, bytes, q, bytes);
+        }
+    a.r_lo = r_lo; a.r_hi = r_hi;
+    a.status = c->status;
     log_call(c, "\"call\": \"growth_bound\", \"kind\": %d, \"dtype\": \"%s\", \"n\": %lld, "
                 "\"nsteps\": %lld, \"E\": %d, \"K\": %d, \"tiles\": %lld, \"passes\": %lld",
              s->kind, dtype_name(dtype), (long long)n, (long long)nsteps, E, K,
@@ -1345,6 +1394,7 @@ reach_status reach_growth_bound(reach_ctx* c, const reach_system* s, reach_dtype
         char* dst = ((passes - 1 - p) % 2 == 0) ? A : B;
         char* src = ((passes - 1 - p) % 2 == 0) ? B : A;
         a.first = (p == 0) ? 1 : 0;
+        a.last = fused && p == passes - 1 ? 1 : 0;
         a.src_c = src; a.src_r = src + bytes;
         a.dst_c = dst; a.dst_r = dst + bytes;
         a.ksteps = std::min<int64_t>(K, nsteps - done);
@@ -1352,6 +1402,7 @@ reach_status reach_growth_bound(reach_ctx* c, const reach_system* s, reach_dtype
         if (e != hipSuccess) return hip_fail(c, e, "growth-bound kernel launch");
         done += a.ksteps;
     }
+    if (fused) return REACH_OK;
     hipError_t e = launch_gb_combine(dt_id, A, A + bytes, n, r_lo, r_hi, c->status, hs);
     if (e != hipSuccess) return hip_fail(c, e, "growth-bound combine launch");
     return REACH_OK;

@@ -147,3 +147,28 @@ def test_calls_without_a_workspace_still_run(rc, variant, n, nsteps):
                           x_lo, x_hi)
         assert rc.sync() == R.REACH_OK
         assert np.array_equal(to_host(x_lo), ref[0]) and np.array_equal(to_host(x_hi), ref[1])
+
+
+@pytest.mark.parametrize("variant", ["ctm", "rd_cell", "lin3"])
+@pytest.mark.parametrize("n", [60, 700, 5001])
+@pytest.mark.parametrize("nsteps", [0, 1, 9, 70])
+def test_gb_results_over_its_inputs(rc, variant, n, nsteps):
+    """Growth bound into the box's own arrays, and into an array that a per-cell
+    input shares: the same bits as into arrays of its own (passes that write
+    the box themselves, and those that leave it to the combining kernel)."""
+    kind, prm, lo, hi, pl, ph, dt = make_case(variant, n, np.float64, seed=n + nsteps)
+    dev = lambda a: None if a is None else to_dev(a)
+    x_lo, x_hi, p_lo, p_hi = dev(lo), dev(hi), dev(pl), dev(ph)
+    say(f"gb aliases {variant} n={n} N={nsteps}")
+    a_lo, a_hi = rc.growth_bound(kind, prm, x_lo, x_hi, dt, nsteps, p_lo=p_lo, p_hi=p_hi)
+    assert rc.sync() == R.REACH_OK
+    y_lo, y_hi = x_lo.clone(), x_hi.clone()
+    rc.growth_bound(kind, prm, y_lo, y_hi, dt, nsteps, p_lo=p_lo, p_hi=p_hi, r_lo=y_lo, r_hi=y_hi)
+    assert rc.sync() == R.REACH_OK
+    assert torch.equal(y_lo, a_lo) and torch.equal(y_hi, a_hi)
+    if variant == "rd_cell":
+        q_lo, q_hi = p_lo.clone(), p_hi.clone()
+        rc.growth_bound(kind, prm, x_lo, x_hi, dt, nsteps, p_lo=q_lo, p_hi=q_hi, r_lo=q_lo,
+                        r_hi=q_hi)
+        assert rc.sync() == R.REACH_OK
+        assert torch.equal(q_lo, a_lo) and torch.equal(q_hi, a_hi)
