@@ -134,8 +134,7 @@ __device__ __forceinline__ void rk_update(T k, T& y, T& acc, T& t, const Steps<T
 //   PAD : the window runs past cell n-1; cells at or beyond n hold the
 //         boundary's ghost value at every stage (nvalid cells of this lane are
 //         inside the chain): a select per cell.
-//   ONE : (with PAD; the Monte Carlo kernel, whose every wave may pad) only
-//         cell n, the right neighbour of cell n-1, is set to the ghost after
+//   ONE : (with PAD; waves that hold one side or sample) only cell n, the right neighbour of cell n-1, is set to the ghost after
 //         each stage: slot `en` of the lane holding it, en the same in every
 //         lane, so one indexed register move per stage replaces the per-cell
 //         selects.  Cells beyond n then hold values that reach no cell of the

@@ -123,8 +123,12 @@ void embed_tile_kernel(EmbedPass a) {
                 Mask<E, false, false> M{E};
                 rk4_steps<KIND, T, E, S, MODE>(y, a.ksteps, P, U, st, M);
             }
+        } else if constexpr (S == 1) {
+            // a single window, longer than the chain
+            const auto M = chain_end_mask<E, true, true>(a.n - ts);
+            rk4_steps<KIND, T, E, S, MODE>(y, a.ksteps, P, U, st, M);
         } else {
-            Mask<E, true, true> M{nvalid};   // a single window, longer than the chain
+            Mask<E, true, true> M{nvalid};
             rk4_steps<KIND, T, E, S, MODE>(y, a.ksteps, P, U, st, M);
         }
     } else {

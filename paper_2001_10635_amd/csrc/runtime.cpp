@@ -405,6 +405,7 @@ bool estimated(int kind, int dtype, bool cell_in, int64_t n, int64_t simds) {
 
 // Runs of at most this many steps keep a chain that one window holds in one
 // window (no workspace, one launch): splitting it would save a few microseconds.
+// A tube of many short runs does split it.
 constexpr int64_t kSplitSteps = 8;
 
 // Default shape of a multi-window run of many steps.
@@ -418,9 +419,10 @@ TuneEntry default_shape(const reach_ctx* c, int kind, int dtype, bool cell_in, i
 }
 
 // split: the caller has the workspace of a multi-pass run, so that a chain may
-// be cut into more windows and passes than the fewest.
+// be cut into more windows and passes than the fewest; one_steps: the longest
+// run that keeps a chain one window holds in that window.
 reach_status plan_embed(reach_ctx* c, const reach_system* s, reach_dtype dtype, int64_t nsteps,
-                        EmbedPlan* p, bool split = true) {
+                        EmbedPlan* p, bool split = true, int64_t one_steps = kSplitSteps) {
     const int64_t n = s->n;
     const bool cell_in = s->n_in > 1;
     const int64_t oE = opt_get(c, "embed.E"), oK = opt_get(c, "embed.K"), oS = opt_get(c, "embed.S");
@@ -429,7 +431,7 @@ reach_status plan_embed(reach_ctx* c, const reach_system* s, reach_dtype dtype, 
     if (split && !oE && !oK && !oS && !tuned_here &&
         estimated(s->kind, dtype, cell_in, n, simds)) {
         const int one = smallest_E(s->kind, dtype, s->kind == REACH_LIN3 ? 2 : 1, n);
-        if (!one || nsteps > kSplitSteps) {
+        if (!one || nsteps > one_steps) {
             // the best K for many steps gives the pass count; the steps are
             // spread evenly over the passes, and the shape is the best for those
             const TuneEntry t = fastest_shape(s->kind, dtype, cell_in, n, simds, 0);
@@ -953,10 +955,11 @@ reach_status reach_sync(reach_ctx* c, void* stream) {
     return REACH_OK;
 }
 
-reach_status reach_embed_rk4(reach_ctx* c, const reach_system* s, reach_dtype dtype,
-                             const void* x_lo, const void* x_hi, const void* p_lo,
-                             const void* p_hi, double t0, double dt, int64_t nsteps, void* r_lo,
-                             void* r_hi, void* ws, size_t ws_bytes, void* stream) {
+static reach_status embed_run(reach_ctx* c, const reach_system* s, reach_dtype dtype,
+                              const void* x_lo, const void* x_hi, const void* p_lo,
+                              const void* p_hi, double t0, double dt, int64_t nsteps, void* r_lo,
+                              void* r_hi, void* ws, size_t ws_bytes, void* stream,
+                              int64_t one_steps) {
     if (!c) return REACH_E_INVAL;
     reach_status st = check_system(c, s, dtype);
     if (st != REACH_OK) return st;
@@ -977,7 +980,7 @@ reach_status reach_embed_rk4(reach_ctx* c, const reach_system* s, reach_dtype dt
         return embed_heat3d(c, s, dtype, x_lo, x_hi, dt, nsteps, r_lo, r_hi, ws, ws_bytes, hs);
     EmbedPlan pl;
     const bool have_ws = ws && ws_bytes >= 2 * bytes;
-    st = plan_embed(c, s, dtype, nsteps, &pl, have_ws);
+    st = plan_embed(c, s, dtype, nsteps, &pl, have_ws, one_steps);
     if (st != REACH_OK) return st;
     log_call(c, "\"call\": \"embed\", \"kind\": %d, \"dtype\": \"%s\", \"n\": %lld, "
                 "\"nsteps\": %lld, \"E\": %d, \"K\": %d, \"S\": %d, \"tiles\": %lld, "
@@ -1039,6 +1042,13 @@ reach_status reach_embed_rk4(reach_ctx* c, const reach_system* s, reach_dtype dt
     return REACH_OK;
 }
 
+reach_status reach_embed_rk4(reach_ctx* c, const reach_system* s, reach_dtype dtype,
+                             const void* x_lo, const void* x_hi, const void* p_lo,
+                             const void* p_hi, double t0, double dt, int64_t nsteps, void* r_lo,
+                             void* r_hi, void* ws, size_t ws_bytes, void* stream) {
+    return embed_run(c, s, dtype, x_lo, x_hi, p_lo, p_hi, t0, dt, nsteps, r_lo, r_hi, ws, ws_bytes,
+                     stream, kSplitSteps);
+}
 
 reach_status reach_embed_rk4_tube(reach_ctx* c, const reach_system* s, reach_dtype dtype,
                                   const void* x_lo, const void* x_hi, const void* p_lo,
@@ -1060,8 +1070,8 @@ reach_status reach_embed_rk4_tube(reach_ctx* c, const reach_system* s, reach_dty
         void* dhi = (char*)tube_hi + (size_t)k * bytes;
         // each slot continues from the previous one: resumed runs are bitwise
         // the same as one run
-        st = reach_embed_rk4(c, s, dtype, src_lo, src_hi, p_lo, p_hi, t0 + (double)(k * every) * dt,
-                             dt, every, dlo, dhi, ws, ws_bytes, stream);
+        st = embed_run(c, s, dtype, src_lo, src_hi, p_lo, p_hi, t0 + (double)(k * every) * dt, dt,
+                       every, dlo, dhi, ws, ws_bytes, stream, slots > 1 ? 1 : kSplitSteps);
         if (st != REACH_OK) return st;
         src_lo = dlo;
         src_hi = dhi;
