@@ -113,31 +113,32 @@ struct McArgs {
     const void* x_hi;
     const void* p_lo;
     const void* p_hi;
-    void* part_min;     // [nw][E][64] interleaved partials of the kernel's type
+    void* part_min;     // [workgroups][n] partials of the kernel's type
     void* part_max;
     int64_t n;
     int64_t n_in;
     int64_t nsteps;
     int64_t s0;
     int64_t m;
-    int64_t nw;         // resident waves (= grid)
+    int64_t nw;         // resident waves
     uint64_t seed;
-    int32_t aligned;
+    int32_t L;          // lanes of a sample in the segment layout, 0: plain layout
+    int32_t spw;        // samples per wave (segment layout: at most 64 / L)
     double prm[5];
     double h2, dt, dt6;
 };
 hipError_t launch_mc(int kind, int mode, int dtype, int E, const McArgs& a, hipStream_t stream);
-// r_min / r_max [n] from the partials of `nw` <= kMcMaxWaves waves of which
-// every group-th slot holds a partial (mc_kernel folds each workgroup's waves
-// into the group's first slot: group = mc_waves_per_group(); one wave per
-// slot: group = 1).  The partials are overwritten (chunk results are written in
+// r_min / r_max [n] from np <= kMcMaxWaves partials; E = 0: vectors of n cells,
+// one per workgroup of mc_kernel (kMcWavesPerGroup waves); E > 0: one per wave,
+// [e][lane] blocks.  The partials are overwritten (chunk results are written in
 // place); reports non-finite values.
 constexpr int64_t kMcMaxWaves = 4096;
-hipError_t launch_mc_reduce(int dtype, int E, void* part_min, void* part_max,
-                            int64_t nw, int64_t group, int64_t n, void* r_min, void* r_max,
-                            unsigned int* status, hipStream_t stream);
-int mc_waves_per_group();
-bool mc_has_E(int dtype, int E);
+constexpr int kMcWavesPerGroup = 4;
+hipError_t launch_mc_reduce(int dtype, int E, void* part_min, void* part_max, int64_t np,
+                            int64_t n, void* r_min, void* r_max, unsigned int* status,
+                            hipStream_t stream);
+bool mc_has_plain(int dtype, int E);      // cells per lane built, 64 E = n
+bool mc_has_segments(int dtype, int E);
 int mc_max_E(int dtype);
 
 // Batch / serving descriptor of one FP64 query (n <= 512).

@@ -1,0 +1,10 @@
+// Monte Carlo kernels of the RD chain in FP64 (see mc_kernel.hpp).
+#include "mc_kernel.hpp"
+
+namespace reach {
+
+hipError_t launch_mc_rd_f64(int mode, int E, const McArgs& a, hipStream_t s) {
+    return mode ? by_E<K_RD, double, IN_CELL>(E, a, s) : by_E<K_RD, double, IN_SCALAR>(E, a, s);
+}
+
+}  // namespace reach

@@ -753,10 +753,75 @@ int64_t mc_waves(const reach_ctx* c, int64_t m) {
     return std::max<int64_t>(1, std::min<int64_t>(std::min(w, kMcMaxWaves), m));
 }
 
+// Room for one partial of 64 E values per wave; the kernel writes one of n values
+// per workgroup of kMcWavesPerGroup waves, so every plan of mc_plan fits.
 size_t mc_ws_bytes(const reach_ctx* c, const reach_system* s, reach_dtype dtype, int64_t m) {
     const int E = mc_E(dtype, s->n);
     if (E < 0) return (size_t)-1;
     return (size_t)2 * (size_t)mc_waves(c, m) * (size_t)(64 * E) * dsize(dtype);
+}
+
+struct McPlan {
+    int E = 1;
+    int L = 0;          // lanes of a sample (segment layout), 0: plain layout
+    int spw = 1;        // samples per wave
+    int64_t nw = 1;     // resident waves
+};
+
+// Cells per lane and samples per wave by the least estimated time, in issued
+// instructions per SIMD: a stage costs c E and a fixed part (lane shifts, and
+// in the segment layout the boundary selects), a sample's draws one Philox
+// block (about 440 instructions' time) per four cells.  A sample spread thin (one
+// cell per lane) has the shortest chain of stages, which decides while each SIMD
+// has at most one wave; with more samples the fixed part counts, and wide lanes
+// with several samples to a wave are cheaper (CTM FP64 n = 64, 13000 samples:
+// 8 cells per lane and 8 samples per wave).
+McPlan mc_plan(const reach_ctx* c, int kind, int dtype, bool cell_in, int64_t n, int64_t m,
+               int64_t nsteps) {
+    const double simds = 4.0 * c->cus;
+    const bool f64 = dtype == 0;
+    const double cc = kind == REACH_CTM && f64 ? 6.75 : 5.75;
+    const double word = f64 ? 2.0 : 1.0;   // registers a lane shift or a select moves
+    McPlan best;
+    double t_best = 1e300;
+    for (int E = 1; E <= mc_max_E(dtype); ++E) {
+        const int64_t L = (n + E - 1) / E;
+        if (L > 64) continue;
+        const bool plain = n == 64 * E && mc_has_plain(dtype, E);
+        if (!plain && !(mc_has_segments(dtype, E) && n >= (int64_t)(E - 1) * L)) continue;
+        const int64_t spw = plain ? 1 : 64 / L;
+        const double waves = (double)((m + spw - 1) / spw);
+        const double stage = cc * E + (plain ? 2.0 : 6.0) * word;
+        const double blocks = (plain && E % 4 == 0 ? E / 4 : E == 1 ? 1 : E / 4 + 1) +
+                              (cell_in ? E / 4 + 1 : 0);
+        const double one = 4.0 * (double)nsteps * stage + 440.0 * blocks;
+        // a lone wave waits for its own results at every stage
+        const double alone = one + 4.0 * (double)nsteps * 15.0;
+        // a launch ends with the SIMD that holds the most waves; lanes of more
+        // than 208 registers of state leave room for one wave only
+        const int regs = (cell_in ? 4 : 3) * E * (f64 ? 2 : 1);
+        const double t = std::max(alone, std::ceil(waves / simds) * one) * (regs > 208 ? 1.4 : 1.0);
+        if (t < t_best) {
+            t_best = t;
+            best.E = E;
+            best.L = plain ? 0 : (int)L;
+            best.spw = (int)spw;
+        }
+    }
+    if (t_best >= 1e300) {   // FP32, n just past 3840: the widest lanes, select per cell
+        best.E = mc_E(dtype, n);
+        best.L = 0;
+        best.spw = 1;
+    }
+    // four waves per SIMD: as many as pay where the registers leave room for them
+    // (short lanes spend their time waiting, and FP32 instructions of different
+    // waves overlap), and where they do not, shorter waves to even out the end
+    // of the launch (CTM FP32 n = 4096, 16384 samples: 4.08 ms at two, 3.91 at four)
+    int64_t w = opt_get(c, "mc.waves");
+    if (w <= 0) w = (int64_t)c->cus * 16;
+    best.nw = std::max<int64_t>(
+        1, std::min<int64_t>(std::min(w, kMcMaxWaves), (m + best.spw - 1) / best.spw));
+    return best;
 }
 
 
@@ -1214,8 +1279,7 @@ reach_status reach_montecarlo_range(reach_ctx* c, const reach_system* s, reach_d
     if (nsteps < 0) return fail(c, REACH_E_INVAL, "nsteps < 0");
     if (m < 1) return fail(c, REACH_E_INVAL, "m must be >= 1");
     if (s0 < 0) return fail(c, REACH_E_INVAL, "s0 must be >= 0");
-    const int E = mc_E(dtype, s->n);
-    if (E < 0)
+    if (mc_E(dtype, s->n) < 0)
         return fail(c, REACH_E_UNSUPPORTED, "Monte Carlo holds a sample in one wave: n <= %d",
                     64 * mc_max_E(dtype));
     const size_t need = mc_ws_bytes(c, s, dtype, m);
@@ -1223,24 +1287,28 @@ reach_status reach_montecarlo_range(reach_ctx* c, const reach_system* s, reach_d
     HIPCHK(c, hipSetDevice(c->device));
     McArgs a{};
     a.x_lo = x_lo; a.x_hi = x_hi; a.p_lo = p_lo; a.p_hi = p_hi;
-    a.nw = mc_waves(c, m);
+    const int mode = s->n_in > 1 ? 1 : 0;
+    const int dt_id = dtype == REACH_F64 ? 0 : 1;
+    const McPlan pl = mc_plan(c, s->kind, dt_id, mode == 1, s->n, m, nsteps);
+    a.nw = pl.nw;
+    a.L = pl.L;
+    a.spw = pl.spw;
     a.part_min = ws;
     a.part_max = (char*)ws + need / 2;
     a.n = s->n; a.n_in = s->n_in; a.nsteps = nsteps; a.s0 = s0; a.m = m; a.seed = seed;
-    a.aligned = 1;
     kernel_prm(s, a.prm);
     a.h2 = dt / 2.0; a.dt = dt; a.dt6 = dt / 6.0;
-    const int mode = s->n_in > 1 ? 1 : 0;
-    const int dt_id = dtype == REACH_F64 ? 0 : 1;
     hipStream_t hs = (hipStream_t)stream;
     log_call(c, "\"call\": \"montecarlo\", \"kind\": %d, \"dtype\": \"%s\", \"n\": %lld, "
-                "\"nsteps\": %lld, \"s0\": %lld, \"m\": %lld, \"E\": %d, \"waves\": %lld",
+                "\"nsteps\": %lld, \"s0\": %lld, \"m\": %lld, \"E\": %d, \"samples_per_wave\": %d, "
+                "\"waves\": %lld",
              s->kind, dtype_name(dtype), (long long)s->n, (long long)nsteps, (long long)s0,
-             (long long)m, E, (long long)a.nw);
-    hipError_t e = launch_mc(s->kind, mode, dt_id, E, a, hs);
+             (long long)m, pl.E, pl.spw, (long long)a.nw);
+    hipError_t e = launch_mc(s->kind, mode, dt_id, pl.E, a, hs);
     if (e != hipSuccess) return hip_fail(c, e, "Monte Carlo kernel launch");
-    e = launch_mc_reduce(dt_id, E, a.part_min, a.part_max, a.nw, mc_waves_per_group(), s->n, r_min,
-                         r_max, c->status, hs);
+    e = launch_mc_reduce(dt_id, 0, a.part_min, a.part_max,
+                         (a.nw + kMcWavesPerGroup - 1) / kMcWavesPerGroup, s->n, r_min, r_max,
+                         c->status, hs);
     if (e != hipSuccess) return hip_fail(c, e, "Monte Carlo reduction launch");
     return REACH_OK;
 }
