@@ -269,12 +269,17 @@ __device__ __forceinline__ unsigned run_query_kind(const QDesc& d, int side) {
 // steps, a member's lanes masked off once its own steps are done.  Per cell
 // this is the single-query arithmetic, so every box is bitwise the one the
 // query gets alone.
-template <int KIND, int E>
+//
+// S = 1 runs only side `side` of a pack of a cooperative system: the longest
+// packs of a batch go to two waves, one per side, where a single wave would hold
+// up the end of the launch (see plan_batch); `pair` counts the pack's finished
+// sides, and the wave that finishes last checks the order.
+template <int KIND, int E, int S>
 __device__ __forceinline__ void run_seg(const QDesc* __restrict__ desc,
-                                     const uint32_t* __restrict__ mem_idx, int count,
-                                     unsigned int* qflags, unsigned int* status) {
+                                     const uint32_t* __restrict__ mem_idx, int count, int side,
+                                     unsigned int* pair, unsigned int* qflags,
+                                     unsigned int* status) {
     using T = double;
-    constexpr int S = 2;
     const int lane = threadIdx.x;
     const QDesc* d0 = desc + mem_idx[0];
     int mem = -1, off = 0, base = 0, len = 0;
@@ -307,10 +312,11 @@ __device__ __forceinline__ void run_seg(const QDesc* __restrict__ desc,
     Inputs<T, E, S, IN_SCALAR> U;
 #pragma unroll
     for (int s = 0; s < S; ++s) {
+        const int sd = S == 1 ? side : s;
 #pragma unroll
         for (int e = 0; e < E; ++e)
-            y[s][e] = (e < L.cnt) ? src[s][L.first + e] : ghost<KIND, T>();
-        U.u[s] = (valid && pin[s]) ? *pin[s] : T(0);
+            y[s][e] = (e < L.cnt) ? src[sd][L.first + e] : ghost<KIND, T>();
+        U.u[s] = (valid && pin[sd]) ? *pin[sd] : T(0);
     }
     SysPrm<T> P;
     P.a0 = d0->prm[0]; P.a1 = d0->prm[1]; P.a2 = d0->prm[2]; P.a3 = d0->prm[3]; P.a4 = d0->prm[4];
@@ -331,10 +337,31 @@ __device__ __forceinline__ void run_seg(const QDesc* __restrict__ desc,
     for (int e = 0; e < E; ++e) {
         if (e < L.cnt) {
             const int64_t j = L.first + e;
-            dst[0][j] = y[0][e];
-            dst[1][j] = y[1][e];
-            if (!finiteT(y[0][e]) || !finiteT(y[1][e])) bits |= ST_NONFINITE;
-            if (y[0][e] > y[1][e]) bits |= ST_ORDER;
+#pragma unroll
+            for (int s = 0; s < S; ++s) {
+                dst[S == 1 ? side : s][j] = y[s][e];
+                if (!finiteT(y[s][e])) bits |= ST_NONFINITE;
+            }
+            if constexpr (S == 2) {
+                if (y[0][e] > y[1][e]) bits |= ST_ORDER;
+            }
+        }
+    }
+    if constexpr (S == 1) {
+        // publish this side, then the second side to finish checks the order
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+        uint64_t old = 0;
+        if (lane == 0)
+            old = __hip_atomic_fetch_add(pair, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
+        if (wave_bcast(old) == 1) {
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+#pragma unroll
+            for (int e = 0; e < E; ++e) {
+                if (e < L.cnt) {
+                    const T o = dst[1 - side][L.first + e];
+                    if (side == 0 ? y[0][e] > o : o > y[0][e]) bits |= ST_ORDER;
+                }
+            }
         }
     }
     if (bits) {
@@ -430,42 +457,72 @@ __global__ __launch_bounds__(64) void batch_kernel(const QDesc* __restrict__ des
 // per SIMD (it runs fastest at two); the 16-cell bodies need ~240 registers,
 // so EMAX = 16 fits two waves per SIMD and runs fastest at one, whose 32
 // independent cell-sides per stage keep the SIMD issuing.
-template <int EMAX>
+// n_items: the item count in its low half; the first (its high half) of them
+// run one side per wave (SIDES; the kernel without those bodies is 2.5% faster
+// on a batch that has none).
+template <int EMAX, bool SIDES>
 __global__ __launch_bounds__(64, EMAX > 8 ? 2 : 3) void pack_kernel(
         const QDesc* __restrict__ desc, const BatchItem* __restrict__ items,
         const uint32_t* __restrict__ members, const uint64_t* n_items,
-        unsigned long long* counter, unsigned int* qflags, unsigned int* status) {
+        unsigned long long* counter, unsigned int* qflags, unsigned int* pair,
+        unsigned int* status) {
     const int lane = threadIdx.x;
-    const uint64_t ni = wave_bcast(*n_items);
+    const uint64_t nw = wave_bcast(*n_items);
+    const uint64_t ni = nw & 0xFFFFFFFFu, ns = SIDES ? nw >> 32 : 0;
     for (;;) {
         uint64_t u = 0;
         if (lane == 0) u = atomicAdd(counter, 1ULL);
         u = wave_bcast(u);
-        if (u >= ni) break;
-        const BatchItem it = items[u];
+        if (u >= ni + ns) break;
+        const bool one = SIDES && u < 2 * ns;        // one side of item u / 2
+        const uint64_t i = one ? u >> 1 : u - ns;
+        const int side = SIDES ? (int)(u & 1) : 0;
+        const BatchItem it = items[i];
         const int kind = desc[members[it.start]].kind;
         const uint32_t* mi = members + it.start;
         const int cnt = it.count;
         const int ki = kind == K_CTM ? 0 : kind == K_RD ? 1 : 2;
         const int ei = it.E == 2 ? 0 : it.E == 4 ? 1 : it.E == 8 ? 2 : 3;
+#define REACH_PACK(KIND, E, S) run_seg<KIND, E, S>(desc, mi, cnt, side, pair + i, qflags, status)
+        if constexpr (SIDES) {
+            if (one && ki < 2) {
+                switch (4 * ki + ei) {
+                    case 0: REACH_PACK(K_CTM, 2, 1); break;
+                    case 1: REACH_PACK(K_CTM, 4, 1); break;
+                    case 2: REACH_PACK(K_CTM, 8, 1); break;
+                    case 4: REACH_PACK(K_RD, 2, 1); break;
+                    case 5: REACH_PACK(K_RD, 4, 1); break;
+                    case 6: REACH_PACK(K_RD, 8, 1); break;
+                    default:
+                        if constexpr (EMAX > 8) {
+                            if (ki == 0) REACH_PACK(K_CTM, 16, 1);
+                            else REACH_PACK(K_RD, 16, 1);
+                        }
+                        break;
+                }
+                continue;
+            }
+            if (one && side == 1) continue;              // a coupled pack ran whole as side 0
+        }
         switch (4 * ki + ei) {
-            case 0: run_seg<K_CTM, 2>(desc, mi, cnt, qflags, status); break;
-            case 1: run_seg<K_CTM, 4>(desc, mi, cnt, qflags, status); break;
-            case 2: run_seg<K_CTM, 8>(desc, mi, cnt, qflags, status); break;
-            case 4: run_seg<K_RD, 2>(desc, mi, cnt, qflags, status); break;
-            case 5: run_seg<K_RD, 4>(desc, mi, cnt, qflags, status); break;
-            case 6: run_seg<K_RD, 8>(desc, mi, cnt, qflags, status); break;
-            case 8: run_seg<K_LIN3, 2>(desc, mi, cnt, qflags, status); break;
-            case 9: run_seg<K_LIN3, 4>(desc, mi, cnt, qflags, status); break;
-            case 10: run_seg<K_LIN3, 8>(desc, mi, cnt, qflags, status); break;
+            case 0: REACH_PACK(K_CTM, 2, 2); break;
+            case 1: REACH_PACK(K_CTM, 4, 2); break;
+            case 2: REACH_PACK(K_CTM, 8, 2); break;
+            case 4: REACH_PACK(K_RD, 2, 2); break;
+            case 5: REACH_PACK(K_RD, 4, 2); break;
+            case 6: REACH_PACK(K_RD, 8, 2); break;
+            case 8: REACH_PACK(K_LIN3, 2, 2); break;
+            case 9: REACH_PACK(K_LIN3, 4, 2); break;
+            case 10: REACH_PACK(K_LIN3, 8, 2); break;
             default:   // E = 16 (the host gives such packs to EMAX = 16 only)
                 if constexpr (EMAX > 8) {
-                    if (ki == 0) run_seg<K_CTM, 16>(desc, mi, cnt, qflags, status);
-                    else if (ki == 1) run_seg<K_RD, 16>(desc, mi, cnt, qflags, status);
-                    else run_seg<K_LIN3, 16>(desc, mi, cnt, qflags, status);
+                    if (ki == 0) REACH_PACK(K_CTM, 16, 2);
+                    else if (ki == 1) REACH_PACK(K_RD, 16, 2);
+                    else REACH_PACK(K_LIN3, 16, 2);
                 }
                 break;
         }
+#undef REACH_PACK
     }
 }
 
@@ -589,12 +646,18 @@ hipError_t launch_batch(const QDesc* d, const BatchItem* items, const uint32_t* 
                         const uint64_t* n_items, unsigned long long* counter,
                         unsigned int* qflags, unsigned int* pair, unsigned int* status,
                         int split, int packed, int64_t grid, hipStream_t s) {
-    if (packed == 2)
-        hipLaunchKernelGGL(pack_kernel<16>, dim3((unsigned)grid), dim3(WAVE), 0, s, d, items,
-                           members, n_items, counter, qflags, status);
+    if (packed == 2 && split)
+        hipLaunchKernelGGL((pack_kernel<16, true>), dim3((unsigned)grid), dim3(WAVE), 0, s, d, items,
+                           members, n_items, counter, qflags, pair, status);
+    else if (packed == 2)
+        hipLaunchKernelGGL((pack_kernel<16, false>), dim3((unsigned)grid), dim3(WAVE), 0, s, d, items,
+                           members, n_items, counter, qflags, pair, status);
+    else if (packed && split)
+        hipLaunchKernelGGL((pack_kernel<8, true>), dim3((unsigned)grid), dim3(WAVE), 0, s, d, items,
+                           members, n_items, counter, qflags, pair, status);
     else if (packed)
-        hipLaunchKernelGGL(pack_kernel<8>, dim3((unsigned)grid), dim3(WAVE), 0, s, d, items,
-                           members, n_items, counter, qflags, status);
+        hipLaunchKernelGGL((pack_kernel<8, false>), dim3((unsigned)grid), dim3(WAVE), 0, s, d, items,
+                           members, n_items, counter, qflags, pair, status);
     else
         hipLaunchKernelGGL(batch_kernel, dim3((unsigned)grid), dim3(WAVE), 0, s, d, items,
                            members, n_items, counter, qflags, pair, status, split);

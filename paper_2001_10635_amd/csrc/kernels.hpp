@@ -198,15 +198,18 @@ struct BatchItem {
 // run by the wide packing kernel (room for two); packed 0:
 // every item is one query (E = 0), or with `split` two per item (one per side
 // of a cooperative chain), pair[i] counting the finished sides of item i.
+// *n_items of a packed batch with `split` holds in its high half the number of
+// leading items that run one side per wave (pair[i] as above).
 hipError_t launch_batch(const QDesc* d, const BatchItem* items, const uint32_t* members,
                         const uint64_t* n_items, unsigned long long* counter,
                         unsigned int* qflags, unsigned int* pair, unsigned int* status,
                         int split, int packed, int64_t grid, hipStream_t stream);
-// Default waves per compute unit of the batch kernels: the one-query kernel
-// and the narrow packing kernel two per SIMD (the narrow one fits three, which
-// measures slower), the wide packing kernel one per SIMD (16 cells give one
+// Default waves per compute unit of the batch kernels: the one-query kernel one
+// per SIMD (its long queries then have a SIMD to themselves: 2000 mixed queries
+// 446 us, 627 at two per SIMD, 4000 572 and 636), the narrow packing kernel two
+// (it fits three, which measures slower), the wide packing kernel one per SIMD (16 cells give one
 // wave enough independent work to keep its SIMD issuing; two measure slower).
-constexpr int kBatchWavesPerCU = 8;
+constexpr int kBatchWavesPerCU = 4;
 constexpr int kPackWavesPerCU = 8;
 constexpr int kWideWavesPerCU = 4;
 // Zero `count` 32-bit words (a kernel, so it can sit in a captured graph).

@@ -1672,14 +1672,15 @@ int batch_ecap(const reach_ctx* c, int kind, int bucket) {
 // still open at the end are packed again per key, widest query first into
 // the first pack with room.  Items are then ordered longest first by the wave
 // time (E * steps of the longest member; ceil(n / 64) * steps alone) at 1/16
-// octave, ties in unit order.
+// octave, ties in unit order.  Packs of a batch too small for its longest query
+// are narrowed, and its longest items run one side per wave (see there).
 struct PlanTimes {
     double pass1_ms = 0, pass_ms = 0, order_ms = 0, members_ms = 0;
 };
 
 reach_status plan_batch(reach_ctx* c, HostPool* pool, const reach_query* q, int64_t nq,
                         int split, int nth, QDesc* descs, std::vector<uint32_t>* members_out,
-                        std::vector<BatchItem>* items_out, int* packed,
+                        std::vector<BatchItem>* items_out, int* packed, int64_t* sides_out,
                         PlanTimes* times = nullptr,
                         const std::function<void()>& descs_done = nullptr) {
     using clk = std::chrono::steady_clock;
@@ -1753,6 +1754,47 @@ reach_status plan_batch(reach_ctx* c, HostPool* pool, const reach_query* q, int6
     int8_t etab[4][513];
     for (int ci = 0; ci < 4; ++ci)
         for (int64_t n = 1; n <= 512; ++n) etab[ci][n] = (int8_t)seg_E(n, 2 << ci);
+    // The batch's load: the wave time E * steps of the packs, by the lanes their
+    // queries take, over the SIMDs.  A pack longer than that holds up the end
+    // of the launch, so queries whose packs would take more than 1.25 loads go
+    // to narrower packs (as far as their lanes fit a wave), and the items still
+    // longer than one load run one side per wave (*sides_out).  A 10^4-query mix
+    // (4-512 cells, 10-1000 steps) has a load of about 4200: 16 cells for 1000
+    // steps would take 16000, 8 cells and one side the time of 4000.
+    uint64_t load = 0;
+    if (packs) {
+        std::vector<uint64_t> part((size_t)nu, 0);
+        run_units(pool, nth, nu, [&](int t) {
+            int64_t lo, hi;
+            chunk(t, nq, &lo, &hi);
+            uint64_t sum = 0;   // E * lanes * steps
+            for (int64_t i = lo; i < hi; ++i) {
+                const reach_system& sy = q[i].sys;
+                if (sy.n < 1 || sy.n > kBatchMaxN || q[i].nsteps < 0) continue;   // refused below
+                const int cap = ecap[sy.kind & 3][std::min(n_bucket(sy.n), kNB - 1)];
+                const int E = etab[cap >= 16 ? 3 : cap >= 8 ? 2 : cap >= 4 ? 1 : 0][sy.n];
+                sum += (uint64_t)(E * ((sy.n + E - 1) / E)) *
+                       (uint64_t)std::min<int64_t>(q[i].nsteps, (int64_t)1 << 32);
+            }
+            part[(size_t)t] = sum;
+        });
+        for (const uint64_t v : part) load += v;
+        load /= (uint64_t)kLanes * 4 * (uint64_t)(c ? c->cus : 256);
+    }
+    // (a caller who asks for packs or for a width gets the widths as they are)
+    const bool narrow = packs && !(c && (opt_get(c, "batch.pack") || opt_get(c, "batch.E")));
+    const auto narrower = [&](int64_t n, int E, int64_t steps) {
+        int best = E;
+        if (!narrow) return best;
+        for (int k = kNE - 1; k >= 0; --k) {
+            const int e = kSegE[k];
+            const int64_t L = (n + e - 1) / e;
+            if (e >= best || L > kLanes || n < (int64_t)(e - 1) * L) continue;
+            if ((uint64_t)best * (uint64_t)steps <= load + load / 4) break;
+            best = e;
+        }
+        return best;
+    };
     // pass 1: descriptors, validation, pack keys (class ids local to the
     // chunk); a chunk's packed queries are listed by the partition owning
     // their (E, step bucket) pair, r mod nu
@@ -1786,7 +1828,8 @@ reach_status plan_batch(reach_ctx* c, HostPool* pool, const reach_query* q, int6
                 continue;
             }
             const int cap = ecap[d.kind & 3][std::min(n_bucket(d.n), kNB - 1)];
-            const int E = etab[cap >= 16 ? 3 : cap >= 8 ? 2 : cap >= 4 ? 1 : 0][d.n];
+            const int E = narrower(d.n, etab[cap >= 16 ? 3 : cap >= 8 ? 2 : cap >= 4 ? 1 : 0][d.n],
+                                   std::min<int64_t>(d.nsteps, (int64_t)1 << 32));
             int cls = -1;
             Consts cs;
             std::memset(&cs, 0, sizeof cs);
@@ -2009,6 +2052,14 @@ reach_status plan_batch(reach_ctx* c, HostPool* pool, const reach_query* q, int6
             ni += v;
             nm += mv;
         }
+    // items longer than the load come first: those of the buckets before its own
+    *sides_out = 0;
+    if (packs) {
+        const int lb = wave_time_bucket(load);
+        // (the counts are item indices now: that of unit 0 in the load's bucket is
+        // the number of items in the buckets before)
+        *sides_out = lb <= b0 ? 0 : lb > b1 ? ni : hist[lb];
+    }
     if (times) times->order_ms = since(t0);
     t0 = clk::now();
     std::vector<BatchItem>& io = *items_out;
@@ -2065,8 +2116,9 @@ reach_status reach_plan_batch(reach_ctx* c, const reach_query* q, int64_t nq,
     }
     const int nth = pool ? std::min(batch_host_threads(nq), pool->size()) : 1;
     int packed = 0;
+    int64_t sides = 0;
     const reach_status st = plan_batch(c, pool, q, nq, split, nth, descs.data(), &members, &items,
-                                       &packed);
+                                       &packed, &sides);
     if (st != REACH_OK) return st;
     for (size_t k = 0; k < items.size(); ++k) {
         item_start[k] = items[k].start;
@@ -2087,9 +2139,9 @@ reach_status reach_embed_rk4_batch(reach_ctx* c, const reach_query* q, int64_t n
     if (!ws || ws_bytes < need) return fail(c, REACH_E_NOMEM, "workspace of %zu bytes needed", need);
     HIPCHK(c, hipSetDevice(c->device));
     hipStream_t hs = (hipStream_t)stream;
-    // whole queries per wave by default (most work per wave, best throughput);
-    // batch.split = 1 gives each side of a cooperative query its own wave
-    const int split = opt_get(c, "batch.split") ? 1 : 0;
+    // batch.split = 1 gives each side of a cooperative query its own wave; so does
+    // a batch too small to pack, whose time is its longest query's
+    int split = opt_get(c, "batch.split") ? 1 : 0;
     HostPool* pool = batch_host_threads(nq) > 1 ? host_pool(c) : nullptr;
     const int nth = pool ? std::min(batch_host_threads(nq), pool->size()) : 1;
     // pinned staging (reused; wait for the previous upload from it, which
@@ -2131,12 +2183,13 @@ reach_status reach_embed_rk4_batch(reach_ctx* c, const reach_query* q, int64_t n
     std::vector<BatchItem> items;
     PlanTimes pt;
     int packed = 0;
+    int64_t sides = 0;   // leading items of a packed batch that run one side per wave
     // the descriptors go up as soon as they are written, while the host forms
     // the work items
     hipError_t desc_err = hipSuccess;
     const size_t desc_bytes = sizeof(QDesc) * (size_t)nq;
     reach_status pst = plan_batch(c, pool, q, nq, split, nth, hb.desc, &members, &items, &packed,
-                                  &pt, [&] {
+                                  &sides, &pt, [&] {
         desc_err = hipMemcpyAsync(db.desc, hb.desc, desc_bytes, hipMemcpyHostToDevice, cs);
     });
     if (pst != REACH_OK) return pst;
@@ -2144,7 +2197,8 @@ reach_status reach_embed_rk4_batch(reach_ctx* c, const reach_query* q, int64_t n
     const int64_t ni = (int64_t)items.size();
     std::memcpy(hb.items, items.data(), sizeof(BatchItem) * (size_t)ni);
     std::memcpy(hb.members, members.data(), sizeof(uint32_t) * (size_t)nq);
-    *hb.count = (uint64_t)ni;
+    *hb.count = (uint64_t)ni | ((uint64_t)sides << 32);
+    if (!packed || sides > 0) split = 1;
     const auto t_plan = std::chrono::steady_clock::now();
 
     int64_t grid = opt_get(c, "batch.waves");
@@ -2157,7 +2211,7 @@ reach_status reach_embed_rk4_batch(reach_ctx* c, const reach_query* q, int64_t n
         if (packed == 2) grid = std::min<int64_t>(grid, (int64_t)c->cus * 8);
     }
     c->last_packed = packed;
-    grid = std::min<int64_t>(grid, split ? 2 * ni : ni);
+    grid = std::min<int64_t>(grid, packed ? ni + sides : 2 * ni);
 
     if (c->log) {
         using ms = std::chrono::duration<double, std::milli>;
