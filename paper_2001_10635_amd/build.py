@@ -24,7 +24,7 @@ SOURCES = ["embed.hip", "embed_ctm_f64.hip", "embed_ctm_f32.hip", "embed_rd_f64.
            "embed_rd_f32.hip", "embed_lin3_f64.hip", "embed_lin3_f32.hip", "gb.hip",
            "heat3d.hip", "mc.hip", "mc_ctm_f64.hip", "mc_ctm_f32.hip", "mc_rd_f64.hip",
            "mc_rd_f32.hip", "mc_lin3_f64.hip", "mc_lin3_f32.hip", "mc_noalloc.hip", "batch.hip",
-           "runtime.cpp", "server.cpp", "user.cpp"]
+           "batch_sides.hip", "runtime.cpp", "server.cpp", "user.cpp"]
 COMMON = ["-O3", "-std=c++17", "-fPIC", "-ffp-contract=off", f"--offload-arch={ARCH}",
           "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
           "-Wno-unused-command-line-argument", "-Wno-unused-value", "-Wno-unused-result"]

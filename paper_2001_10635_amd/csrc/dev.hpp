@@ -195,8 +195,11 @@ template <class T, int S> struct Edges {
 
 // Whether a stage hands its edge cells on as soon as they are known: not in the
 // widest windows, where the values held meanwhile cost registers and the inner
-// cells cover the shifts anyway.
-template <class T, int E> constexpr bool early_edges() { return E * sizeof(T) <= 128; }
+// cells cover the shifts anyway, nor at two RD cells, which are both edges (5%
+// slower there; the CTM's fluxes between them leave work to overlap).
+template <int KIND, class T, int E> constexpr bool early_edges() {
+    return E * sizeof(T) <= 128 && !(KIND == K_RD && E == 2);
+}
 
 template <int KIND, class T, int E, int S, bool END>
 __device__ __forceinline__ void get_edges(Edges<T, S>& c, const T (&in)[E], int s,
@@ -242,7 +245,7 @@ __device__ __forceinline__ void rk_stage(T (&y)[S][E], T (&acc)[S][E], T (&t)[S]
     T (&in)[S][E] = (STAGE == 1) ? y : t;
     T (&out)[S][E] = (STAGE == 4) ? y : t;
     constexpr bool FIX = Mask<E, MASKED, END, ONE>::template indexed<T>();
-    constexpr bool EARLY = !FIX && early_edges<T, E>();
+    constexpr bool EARLY = !FIX && early_edges<KIND, T, E>();
     if constexpr (!EARLY) {
 #pragma unroll
         for (int s = 0; s < S; ++s) get_edges<KIND, T, E, S, END>(c, in[s], s, P);
@@ -298,6 +301,18 @@ __device__ __forceinline__ void rk_stage(T (&y)[S][E], T (&acc)[S][E], T (&t)[S]
         };
 #pragma unroll
         for (int s = 0; s < S; ++s) {
+            if constexpr (!EARLY) {
+                T left = c.l[s];
+#pragma unroll
+                for (int e = 0; e < E; ++e) {
+                    const T mid = in[s][e];
+                    const T k = f(s, e, left, mid, (e == E - 1) ? c.r[s] : in[s][e + 1]);
+                    left = mid;
+                    put(s, e, k);
+                }
+                finish(s);
+                continue;
+            }
             const T o0 = in[s][0], oE = in[s][E - 1];
             if constexpr (E == 1) {
                 put(s, 0, f(s, 0, c.l[s], o0, c.r[s]));
@@ -400,7 +415,7 @@ __device__ __forceinline__ void rk4_steps(T (&y)[S][E], int64_t nsteps, const Sy
     T acc[S][E], t[S][E];
     Edges<T, S> c;
     first_edges<KIND>(c, P);
-    if constexpr (early_edges<T, E>()) {
+    if constexpr (early_edges<KIND, T, E>()) {
 #pragma unroll
         for (int s = 0; s < S; ++s) get_edges<KIND, T, E, S, END>(c, y[s], s, P);
     }

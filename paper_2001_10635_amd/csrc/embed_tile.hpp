@@ -124,8 +124,9 @@ void embed_tile_kernel(EmbedPass a) {
                 rk4_steps<KIND, T, E, S, MODE>(y, a.ksteps, P, U, st, M);
             }
         } else if constexpr (S == 1) {
-            // a single window, longer than the chain
-            const auto M = chain_end_mask<E, true, true>(a.n - ts);
+            // a single window, longer than the chain: one indexed move a stage
+            // sets the ghost, cheaper than the selects from 12 cells a lane on
+            const auto M = chain_end_mask<E, true, (E >= 12)>(a.n - ts);
             rk4_steps<KIND, T, E, S, MODE>(y, a.ksteps, P, U, st, M);
         } else {
             Mask<E, true, true> M{nvalid};

@@ -71,7 +71,7 @@ void gb_tile_kernel(GbPass a) {
 
     const Mask<E, false, false> inner{E};
     const Mask<E, false, true> end{E};
-    const auto padded = chain_end_mask<E, true, true>(a.n - ts);
+    const auto padded = chain_end_mask<E, true, (E >= 12)>(a.n - ts);
     if (side == 0) {
         if (!fast) rk4_steps<KIND, T, E, 1, MODE>(y, a.ksteps, P, U, st, padded);
         else if (KIND == K_CTM && reaches_end) rk4_steps<KIND, T, E, 1, MODE>(y, a.ksteps, P, U, st, end);

@@ -59,6 +59,14 @@ struct GraphKey {
 
 struct TuneEntry { int E; int K; int S; };
 
+// The last shapes estimated (fastest_shape), by what they depend on: a call of a
+// few microseconds would otherwise spend one on the estimate each time.
+struct ShapeMemo {
+    struct Slot { int64_t n = 0, K = 0; int kind = 0, dtype = 0, flags = 0; TuneEntry t{0, 0, 0}; };
+    Slot slot[16];
+    int next = 0;
+};
+
 }  // namespace
 
 // Host worker threads kept for the life of a context (starting threads per
@@ -160,6 +168,7 @@ struct reach_ctx {
     std::map<std::string, int64_t> opt;
     // (kind, dtype, log2 n bucket, per-cell inputs)
     std::map<std::tuple<int, int, int, int>, TuneEntry> tune;
+    ShapeMemo shapes;
     std::map<std::pair<int, int>, int> batch_tune;        // (kind, log2 n bucket) -> pack E cap
     int64_t batch_waves[2] = {0, 0};                     // autotuned resident waves of the
                                                          // narrow / wide packing kernel (0 = none)
@@ -221,6 +230,7 @@ reach_status hip_fail(reach_ctx* c, hipError_t e, const char* what) {
 size_t dsize(reach_dtype d) { return d == REACH_F64 ? 8 : 4; }
 
 int64_t opt_get(const reach_ctx* c, const char* k) {
+    if (c->opt.empty()) return 0;   // no option was ever set: the small calls' path
     auto it = c->opt.find(k);
     return it == c->opt.end() ? 0 : it->second;
 }
@@ -370,7 +380,8 @@ double step_us(int kind, int dtype, bool cell_in, int S, int E, int64_t K, int64
     const int wide = S == 2 ? (f64 ? (cell_in ? 8 : 12) : 16)
                             : (f64 ? (cell_in ? 24 : 28) : 48);
     if (E > wide && r > 1) return 1e300;
-    const double c = kind == REACH_LIN3 ? 0.0765 : kind == REACH_RD ? 0.0438 : f64 ? 0.051 : 0.040;
+    double c = kind == REACH_LIN3 ? 0.0765 : kind == REACH_RD ? 0.0438 : f64 ? 0.051 : 0.040;
+    if (E > wide) c *= S == 2 ? 2.0 : 1.2;   // register moves
     const double bytes = (double)n * (f64 ? 8.0 : 4.0) * (cell_in ? 6.0 : 4.0);
     return (double)r * c * E + 0.06 + (2.5 + bytes / 7.0e6) / (double)K;
 }
@@ -378,8 +389,12 @@ double step_us(int kind, int dtype, bool cell_in, int S, int E, int64_t K, int64
 // The shape of the least estimated step time, at K steps per pass (K = 0: the
 // best K as well, up to 64), among the embedding's shapes or (gb) the growth
 // bound's.
-TuneEntry fastest_shape(int kind, int dtype, bool cell_in, int64_t n, int64_t simds, int64_t K,
+TuneEntry fastest_shape(reach_ctx* c, int kind, int dtype, bool cell_in, int64_t n, int64_t K,
                         bool gb = false) {
+    const int64_t simds = (int64_t)4 * c->cus;
+    const int flags = (cell_in ? 1 : 0) | (gb ? 2 : 0);
+    for (const ShapeMemo::Slot& m : c->shapes.slot)
+        if (m.n == n && m.K == K && m.kind == kind && m.dtype == dtype && m.flags == flags) return m.t;
     const int S = kind == REACH_LIN3 ? 2 : 1;
     TuneEntry best{0, 0, S};
     double t_best = 1e300;
@@ -391,6 +406,9 @@ TuneEntry fastest_shape(int kind, int dtype, bool cell_in, int64_t n, int64_t si
             if (t < t_best) { t_best = t; best.E = E; best.K = (int)k; }
         }
     }
+    ShapeMemo::Slot& m = c->shapes.slot[c->shapes.next];
+    c->shapes.next = (c->shapes.next + 1) % 16;
+    m.n = n; m.K = K; m.kind = kind; m.dtype = dtype; m.flags = flags; m.t = best;
     return best;
 }
 
@@ -405,14 +423,15 @@ bool estimated(int kind, int dtype, bool cell_in, int64_t n, int64_t simds) {
 
 // Runs of at most this many steps keep a chain that one window holds in one
 // window (no workspace, one launch): splitting it would save a few microseconds.
-// A tube of many short runs does split it.
+// A tube of many short runs does split it, and so does the LIN3 chain, whose wave
+// holds both sides (n = 1000, 8 steps: 23 us in one window, 16 in several).
 constexpr int64_t kSplitSteps = 8;
 
 // Default shape of a multi-window run of many steps.
-TuneEntry default_shape(const reach_ctx* c, int kind, int dtype, bool cell_in, int64_t n) {
+TuneEntry default_shape(reach_ctx* c, int kind, int dtype, bool cell_in, int64_t n) {
     const int64_t simds = (int64_t)4 * c->cus;
     if (kind != REACH_HEAT3D && estimated(kind, dtype, cell_in, n, simds)) {
-        const TuneEntry t = fastest_shape(kind, dtype, cell_in, n, simds, 0);
+        const TuneEntry t = fastest_shape(c, kind, dtype, cell_in, n, 0);
         if (t.E) return t;
     }
     return default_tune(kind, dtype, cell_in, n);
@@ -426,27 +445,33 @@ reach_status plan_embed(reach_ctx* c, const reach_system* s, reach_dtype dtype, 
     const int64_t n = s->n;
     const bool cell_in = s->n_in > 1;
     const int64_t oE = opt_get(c, "embed.E"), oK = opt_get(c, "embed.K"), oS = opt_get(c, "embed.S");
-    const bool tuned_here = c->tune.count({s->kind, dtype, n_bucket(n), cell_in ? 1 : 0}) != 0;
     const int64_t simds = (int64_t)4 * c->cus;
-    if (split && !oE && !oK && !oS && !tuned_here &&
+    // (up to two cells per lane one window is always the better one)
+    if (split && n > 128 && !oE && !oK && !oS &&
+        (c->tune.empty() || !c->tune.count({s->kind, dtype, n_bucket(n), cell_in ? 1 : 0})) &&
         estimated(s->kind, dtype, cell_in, n, simds)) {
         const int one = smallest_E(s->kind, dtype, s->kind == REACH_LIN3 ? 2 : 1, n);
-        if (!one || nsteps > one_steps) {
+        if (!one || nsteps > (s->kind == REACH_LIN3 ? 1 : one_steps)) {
             // the best K for many steps gives the pass count; the steps are
             // spread evenly over the passes, and the shape is the best for those
-            const TuneEntry t = fastest_shape(s->kind, dtype, cell_in, n, simds, 0);
+            const TuneEntry t = fastest_shape(c, s->kind, dtype, cell_in, n, 0);
             const int64_t steps = std::max<int64_t>(nsteps, 1);
             const int64_t passes = (steps + t.K - 1) / t.K;
             const int64_t K = (steps + passes - 1) / passes;
-            const TuneEntry u = fastest_shape(s->kind, dtype, cell_in, n, simds, K);
+            const TuneEntry u = fastest_shape(c, s->kind, dtype, cell_in, n, K);
             // one window: the launch once, padding selects (a third more
-            // instructions) unless the chain fills it
+            // instructions) unless the chain fills it.  Several windows pay a
+            // launch per pass, about 3 us on the host beside the call's own 9
+            // through the Python binding (a tube's slots are one call).
+            const double host_us = one_steps < kSplitSteps ? 0.0 : 9.0;
             const double c1 = step_us(s->kind, dtype, cell_in, t.S, one ? one : 1, 1, 1, simds);
             const double one_us =
-                one ? 2.5 + (double)steps * (c1 - 2.5) * (n == (int64_t)64 * one ? 1.0 : 1.33)
+                one ? std::max(host_us + 3.0, 2.5 + (double)steps * (c1 - 2.5) *
+                                                        (n == (int64_t)64 * one ? 1.0 : 1.33))
                     : 1e300;
             const double many_us =
-                (double)steps * step_us(s->kind, dtype, cell_in, t.S, u.E, K, n, simds);
+                std::max(host_us + 3.0 * (double)passes,
+                         (double)steps * step_us(s->kind, dtype, cell_in, t.S, u.E, K, n, simds));
             if (u.E && many_us < one_us) {
                 set_windows(p, u.E, u.S, K, n, nsteps);
                 if (p->W > 1) return REACH_OK;
@@ -1393,10 +1418,10 @@ reach_status reach_growth_bound(reach_ctx* c, const reach_system* s, reach_dtype
         const int64_t simds = (int64_t)4 * c->cus;
         TuneEntry t{0, 0, 1};
         if (!K && nsteps > 0 && estimated(like, dtype, cell_in, n, simds)) {
-            t = fastest_shape(like, dtype, cell_in, n, simds, 0, true);
+            t = fastest_shape(c, like, dtype, cell_in, n, 0, true);
             const int64_t passes = (nsteps + t.K - 1) / t.K;
             t.K = (int)((nsteps + passes - 1) / passes);
-            t = fastest_shape(like, dtype, cell_in, n, simds, t.K, true);
+            t = fastest_shape(c, like, dtype, cell_in, n, t.K, true);
             if ((int64_t)64 * t.E >= n) t.E = 0;   // one window: no passes at all
             else if (one && nsteps <= kSplitSteps) t.E = 0;
         }
