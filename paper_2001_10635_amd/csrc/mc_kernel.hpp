@@ -250,12 +250,22 @@ void mc_kernel(McArgs a) {
 
         if constexpr (SEG) {
             T acc[E], t[E];
-            for (int64_t k = 0; k < a.nsteps; ++k) {
+            const auto step = [&] {
                 seg_stage<KIND, 1>(y[0], acc, t, P, I, st, S);
                 seg_stage<KIND, 2>(y[0], acc, t, P, I, st, S);
                 seg_stage<KIND, 3>(y[0], acc, t, P, I, st, S);
                 seg_stage<KIND, 4>(y[0], acc, t, P, I, st, S);
+            };
+            int64_t k = 0;
+            if constexpr (E * sizeof(T) <= 16) {   // (see rk4_steps)
+                for (; k + 4 <= a.nsteps; k += 4) {
+                    step();
+                    step();
+                    step();
+                    step();
+                }
             }
+            for (; k < a.nsteps; ++k) step();
         } else if (E * sizeof(T) <= 128 || n == WAVE * E) {   // (see mc_plan)
             Mask<E, false, true> M{E};
             rk4_steps<KIND, T, E, 1, MODE>(y, a.nsteps, P, I, st, M);
