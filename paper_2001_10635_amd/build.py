@@ -20,18 +20,38 @@ PROBE_SO = os.path.join(HERE, "libreach_probe.so")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"
 
-SOURCES = ["embed.hip", "embed_ctm_f64.hip", "embed_ctm_f32.hip", "embed_rd_f64.hip",
-           "embed_rd_f32.hip", "embed_lin3_f64.hip", "embed_lin3_f32.hip", "gb.hip",
-           "heat3d.hip", "mc.hip", "mc_ctm_f64.hip", "mc_ctm_f32.hip", "mc_rd_f64.hip",
-           "mc_rd_f32.hip", "mc_lin3_f64.hip", "mc_lin3_f32.hip", "mc_noalloc.hip", "batch.hip",
-           "batch_sides.hip", "runtime.cpp", "server.cpp", "user.cpp"]
+# Sources that share one object file: the dispatch and the sources it dispatches
+# to, compiled apart (in parallel) and joined by a relocatable link.
+GROUPS = {"embed": ["embed.hip", "embed_ctm_f64.hip", "embed_ctm_f32.hip", "embed_rd_f64.hip",
+                    "embed_rd_f32.hip", "embed_lin3_f64.hip", "embed_lin3_f32.hip"],
+          "mc": ["mc.hip", "mc_ctm_f64.hip", "mc_ctm_f32.hip", "mc_rd_f64.hip", "mc_rd_f32.hip",
+                 "mc_lin3_f64.hip", "mc_lin3_f32.hip"],
+          "batch": ["batch.hip", "batch_sides.hip"]}
+SOURCES = [*GROUPS["embed"], "gb.hip", "heat3d.hip", *GROUPS["mc"], "mc_noalloc.hip",
+           *GROUPS["batch"], "runtime.cpp", "server.cpp", "user.cpp"]
 COMMON = ["-O3", "-std=c++17", "-fPIC", "-ffp-contract=off", f"--offload-arch={ARCH}",
           "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
           "-Wno-unused-command-line-argument", "-Wno-unused-value", "-Wno-unused-result"]
 
 
 def _obj(src: str) -> str:
-    return os.path.join(BUILD, os.path.splitext(src)[0] + ".o")
+    """Object of one source (a group's joined object takes its first source's name)."""
+    base = os.path.splitext(src)[0]
+    return os.path.join(BUILD, base + (".part.o" if base in GROUPS else ".o"))
+
+
+def _join() -> list[str]:
+    """The library's objects, each group's joined into one."""
+    parts = {src for group in GROUPS.values() for src in group}
+    objs = [_obj(src) for src in SOURCES if src not in parts]
+    for base, group in GROUPS.items():
+        out = os.path.join(BUILD, base + ".o")
+        r = subprocess.run(["ld", "-r", *[_obj(src) for src in group], "-o", out],
+                           capture_output=True, text=True)
+        if r.returncode != 0:
+            raise RuntimeError(f"joining {out} failed:\n{r.stderr}")
+        objs.append(out)
+    return objs
 
 
 def _compile(src: str) -> str:
@@ -48,12 +68,11 @@ def build(verbose: bool = False) -> str:
     os.makedirs(BUILD, exist_ok=True)
     jobs = min(len(SOURCES), max(1, (os.cpu_count() or 4)))
     with ThreadPoolExecutor(max_workers=jobs) as ex:
-        objs = list(ex.map(_compile, SOURCES + [PROBE_SRC]))
-    probe_obj = objs.pop()
+        probe_obj = list(ex.map(_compile, SOURCES + [PROBE_SRC]))[-1]
     from .isa_check import check_device_asm
     for src in SOURCES + [PROBE_SRC]:
         check_device_asm(BUILD, src, ARCH)
-    cmd = [HIPCC, f"--offload-arch={ARCH}", "-shared", "-fPIC", *objs, "-o", SO + ".tmp",
+    cmd = [HIPCC, f"--offload-arch={ARCH}", "-shared", "-fPIC", *_join(), "-o", SO + ".tmp",
            "-lpthread", "-lhiprtc"]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
