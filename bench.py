@@ -54,12 +54,12 @@ def log(msg):
 
 # the kernel sources a PMC summary is tied to (the pass structs in kernels.hpp
 # change with the kernels that read them)
-EMBED_SOURCES = ("dev.hpp", "embed.hip")
+EMBED_SOURCES = ("dev.hpp", "tile_io.hpp", "embed_tile.hpp")
 HEAT_SOURCES = ("dev.hpp", "heat3d.hip")
 # the packed batch's kernel sources (its instruction count also follows the
 # planner's packing, whose changes call for a new summary)
-BATCH_SOURCES = ("dev.hpp", "batch.hip")
-MC_SOURCES = ("dev.hpp", "mc.hip")
+BATCH_SOURCES = ("dev.hpp", "batch_pack.hpp", "batch.hip")
+MC_SOURCES = ("dev.hpp", "mc_kernel.hpp")
 # FP64 VALU instructions of one state-step's arithmetic in the batch kernels
 # (per cell and stage: RD 4, CTM 5 for the right-hand side; the RK4 updates
 # 1 + 2 + 2 + 2 over the four stages)
