@@ -164,17 +164,22 @@ const char* reach_last_error(const reach_ctx* ctx);
      "heat.P"     rows per wavefront of the 3-D heat kernel: 2, 3, 4, 5 or 8
                   (with 16, 12, 8, 8 or 4 wavefronts per block; FP64 builds 2, 3,
                   4 and 5, FP32 2, 3, 4 and 8; 0 = tuned default)
-     "mc.waves"   resident waves of the Monte Carlo kernel (0 = default, at most 4096)
-     "batch.split" 1: one wave per side of each cooperative query (shorter
-                  latency per query); 0 (default): one wave per query or pack
+     "mc.waves"   resident waves of the Monte Carlo kernel (0 = default: at most
+                  16 per compute unit; at most 4096)
+     "batch.split" 1: no packing, one wave per side of each cooperative query
+                  (shorter latency per query); 0 (default): a batch that does
+                  not pack runs so anyway; in a packed one the packs run whole,
+                  except the longest of a batch too small for them
      "batch.pack" 0 (default): segment packs when the batch has more queries
-                  than twice the resident waves; 1: always; 2: never
+                  than 16 per compute unit (than twice "batch.waves" when set);
+                  1: always; 2: never
      "batch.E"    largest cells per lane of a segment pack: 2, 4, 8 or 16 (0 =
                   the autotuned cap of the query's bucket, else that of the
                   whole batch, else 16)
      "batch.waves" resident waves of the batch kernels (0 = default: the
                   count the autotuner chose for that packing kernel, else 8
-                  per compute unit, 4 when a pack has 16 cells per lane)
+                  per compute unit, 4 when a pack has 16 cells per lane or
+                  the batch does not pack)
      "serve.mode" 0 (default): persistent serving kernel; 1: one launch per
                   served query (read by reach_server_start)
      "serve.waves" resident waves of the serving kernel (0 = default)
@@ -217,7 +222,10 @@ reach_status reach_autotune_embed(reach_ctx* ctx, const reach_system* sys, reach
 
 /* Bytes of device workspace reach_embed_rk4 (m = 0) or reach_montecarlo
    (m = sample count) needs for this system and dtype with the context's
-   current tuning; 0 if none is needed; (size_t)-1 on invalid arguments. */
+   current tuning; 0 if none is needed; (size_t)-1 on invalid arguments.
+   For an embedding that one window of the kernel holds, the bytes are those a
+   long run uses to cut the chain into several windows; without them it runs
+   in one window, with the same results. */
 size_t reach_workspace_bytes(reach_ctx* ctx, const reach_system* sys, reach_dtype dtype,
                              int64_t m);
 
@@ -234,8 +242,8 @@ reach_status reach_sync(reach_ctx* ctx, void* stream);
  *   p_lo, p_hi  n_in elements (NULL iff n_in == 0)
  *   r_lo, r_hi  n elements; may be the same arrays as x_lo, x_hi
  *   workspace   device memory of reach_workspace_bytes(ctx, sys, dtype, 0)
- *               bytes (may be NULL when that is 0); must not overlap the
- *               other arrays
+ *               bytes (may be NULL when that is 0, and for a chain that one
+ *               window of the kernel holds); must not overlap the other arrays
  * nsteps = 0 copies the box.  Errors: REACH_E_INVAL for n < 1, n_in not in
  * {0, 1, n}, dt not finite or <= 0, nsteps < 0, NULL required pointers,
  * unknown kind or nonzero reserved field, workspace too small;
@@ -368,13 +376,15 @@ size_t reach_batch_workspace_bytes(int64_t nq);
 
 /* The schedule reach_embed_rk4_batch launches for these queries, computed on
  * the host only (no device call; the query pointers are not dereferenced).
- * A batch with more queries than twice the resident waves of the unpacked
- * kernel (option "batch.pack": 0 = that rule, 1 = always, 2 = never) is
+ * A batch with more queries than 16 per compute unit, or than twice option
+ * "batch.waves" when that is set (option "batch.pack": 0 = that rule, 1 = always, 2 = never) is
  * packed: every work item is then a segment pack, queries of one kind with
  * bitwise equal parameters and dt, step counts in the same 1/16 octave and
  * the same cells per lane E (2, 4, 8 or 16, chosen per query by the least
  * estimated issue cost, at most option "batch.E" or else the (kind, size)
- * bucket's autotuned cap) sharing a wavefront, query m on ceil(n_m / E)
+ * bucket's autotuned cap; unless option "batch.pack" or "batch.E" is set, a
+ * query whose pack would outlast the batch's average load of a SIMD by a
+ * quarter takes a narrower one) sharing a wavefront, query m on ceil(n_m / E)
  * lanes, at most 64 lanes and 64 queries.  An unpacked batch runs every
  * query alone, spread over a whole wavefront (E = ceil(n / 64)).  Items come
  * longest first (wave time E * nsteps of the longest member).

@@ -8,11 +8,12 @@
 // large-n embedding kernel's, so a query gives the same box alone, in a batch,
 // or served.
 //
-//   batch_kernel   persistent grid; each wave pops the next work item (a whole
-//                  query, or with `split` one side of a cooperative query) from
-//                  a device counter until the batch is exhausted.
+//   batch_kernel   persistent grid; each wave pops the next work item (one side
+//                  of a cooperative query) from a device counter until the
+//                  batch is exhausted.
 //   pack_kernel    the same for a packed batch, whose items are segment packs:
-//                  queries sharing a wave at E cells per lane.
+//                  queries sharing a wave at E cells per lane
+//                  (pack_sides_kernel: the longest of them one side per wave).
 //   single_kernel  one query per launch (the baseline the batch is compared with).
 //   serve_kernel   persistent grid fed through a ring of descriptors in pinned
 //                  host memory; each wave claims the next work item (sequence
@@ -144,27 +145,16 @@ __global__ __launch_bounds__(64) void batch_kernel(const QDesc* __restrict__ des
                                                    const uint64_t* n_items,
                                                    unsigned long long* counter,
                                                    unsigned int* qflags, unsigned int* pair,
-                                                   unsigned int* status, int split) {
+                                                   unsigned int* status) {
     const int lane = threadIdx.x;
     const uint64_t ni = wave_bcast(*n_items);
-    const uint64_t total = split ? 2 * ni : ni;
+    const uint64_t total = 2 * ni;
     for (;;) {
         uint64_t u = 0;
         if (lane == 0) u = atomicAdd(counter, 1ULL);
         u = wave_bcast(u);
         if (u >= total) break;
-        if (!split) {
-            // a whole query over the wave (both sides, E = ceil(n / 64))
-            const BatchItem it = items[u];
-            const QDesc d = desc[members[it.start]];
-            const unsigned bits = run_query(d);
-            if (lane == 0 && bits) {
-                atomicOr(&qflags[d.tag], bits);
-                atomicOr(status, bits);
-            }
-            continue;
-        }
-        // one side of item i (items are single queries when split)
+        // one side of item i
         const uint64_t i = u >> 1;
         const int side = (int)(u & 1);
         const QDesc d = desc[members[items[i].start]];
@@ -318,8 +308,8 @@ hipError_t launch_pack_sides(const QDesc* d, const BatchItem* items, const uint3
 hipError_t launch_batch(const QDesc* d, const BatchItem* items, const uint32_t* members,
                         const uint64_t* n_items, unsigned long long* counter,
                         unsigned int* qflags, unsigned int* pair, unsigned int* status,
-                        int split, int packed, int64_t grid, hipStream_t s) {
-    if (packed && split)
+                        bool sides, int packed, int64_t grid, hipStream_t s) {
+    if (packed && sides)
         return launch_pack_sides(d, items, members, n_items, counter, qflags, pair, status,
                                  packed == 2, grid, s);
     if (packed == 2)
@@ -330,7 +320,7 @@ hipError_t launch_batch(const QDesc* d, const BatchItem* items, const uint32_t* 
                            members, n_items, counter, qflags, status);
     else
         hipLaunchKernelGGL(batch_kernel, dim3((unsigned)grid), dim3(WAVE), 0, s, d, items,
-                           members, n_items, counter, qflags, pair, status, split);
+                           members, n_items, counter, qflags, pair, status);
     return hipGetLastError();
 }
 

@@ -196,14 +196,14 @@ struct BatchItem {
 // pack of at most 8 cells per lane (E > 0), run by the packing kernel (room
 // for three waves per SIMD); packed 2: some pack has 16 cells per lane, all
 // run by the wide packing kernel (room for two); packed 0:
-// every item is one query (E = 0), or with `split` two per item (one per side
-// of a cooperative chain), pair[i] counting the finished sides of item i.
-// *n_items of a packed batch with `split` holds in its high half the number of
+// every item is one query (E = 0) and runs as two, one per side of a cooperative
+// chain, pair[i] counting the finished sides of item i.
+// *n_items of a packed batch with `sides` holds in its high half the number of
 // leading items that run one side per wave (pair[i] as above).
 hipError_t launch_batch(const QDesc* d, const BatchItem* items, const uint32_t* members,
                         const uint64_t* n_items, unsigned long long* counter,
                         unsigned int* qflags, unsigned int* pair, unsigned int* status,
-                        int split, int packed, int64_t grid, hipStream_t stream);
+                        bool sides, int packed, int64_t grid, hipStream_t stream);
 // Default waves per compute unit of the batch kernels: the one-query kernel one
 // per SIMD (its long queries then have a SIMD to themselves: 2000 mixed queries
 // 446 us, 627 at two per SIMD, 4000 572 and 636), the narrow packing kernel two

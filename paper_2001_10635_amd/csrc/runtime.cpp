@@ -2164,9 +2164,9 @@ reach_status reach_embed_rk4_batch(reach_ctx* c, const reach_query* q, int64_t n
     if (!ws || ws_bytes < need) return fail(c, REACH_E_NOMEM, "workspace of %zu bytes needed", need);
     HIPCHK(c, hipSetDevice(c->device));
     hipStream_t hs = (hipStream_t)stream;
-    // batch.split = 1 gives each side of a cooperative query its own wave; so does
-    // a batch too small to pack, whose time is its longest query's
-    int split = opt_get(c, "batch.split") ? 1 : 0;
+    // batch.split = 1 turns packing off.  An unpacked batch, whose time is its longest
+    // query's, runs each side of a cooperative query in a wave of its own
+    const int split = opt_get(c, "batch.split") ? 1 : 0;
     HostPool* pool = batch_host_threads(nq) > 1 ? host_pool(c) : nullptr;
     const int nth = pool ? std::min(batch_host_threads(nq), pool->size()) : 1;
     // pinned staging (reused; wait for the previous upload from it, which
@@ -2223,7 +2223,6 @@ reach_status reach_embed_rk4_batch(reach_ctx* c, const reach_query* q, int64_t n
     std::memcpy(hb.items, items.data(), sizeof(BatchItem) * (size_t)ni);
     std::memcpy(hb.members, members.data(), sizeof(uint32_t) * (size_t)nq);
     *hb.count = (uint64_t)ni | ((uint64_t)sides << 32);
-    if (!packed || sides > 0) split = 1;
     const auto t_plan = std::chrono::steady_clock::now();
 
     int64_t grid = opt_get(c, "batch.waves");
@@ -2246,7 +2245,7 @@ reach_status reach_embed_rk4_batch(reach_ctx* c, const reach_query* q, int64_t n
                     "\"plan_members_ms\": %.3f",
                  (long long)nq, (long long)ni, (long long)(nq - (int64_t)std::count_if(
                      items.begin(), items.end(), [](const BatchItem& x) { return x.count == 1; })),
-                 (long long)grid, split, nth, ms(t_plan - t_start).count(), pt.pass1_ms,
+                 (long long)grid, !packed || sides > 0 ? 1 : 0, nth, ms(t_plan - t_start).count(), pt.pass1_ms,
                  pt.pass_ms, pt.order_ms, pt.members_ms);
     }
     // the rest of the block (items, their count, the members) follows; the
@@ -2261,14 +2260,14 @@ reach_status reach_embed_rk4_batch(reach_ctx* c, const reach_query* q, int64_t n
         hipError_t e = launch_zero(base, (int64_t)(align256(8) + 2 * align256(4 * (size_t)nq)) / 4, s);
         if (e != hipSuccess) return e;
         return launch_batch(db.desc, db.items, db.members, db.count, counter, qflags, pair,
-                            c->status, split, packed, grid, s);
+                            c->status, sides > 0, packed, grid, s);
     };
 
     if (hs == nullptr) {
         hipError_t e = enqueue(hs);
         if (e != hipSuccess) return hip_fail(c, e, "batch launch");
     } else {
-        GraphKey key{nq, ws, c->staging, (((grid * 2 + split) * 3 + packed) * 2 + blk), hs};
+        GraphKey key{nq, ws, c->staging, (((grid * 2 + (sides > 0)) * 3 + packed) * 2 + blk), hs};
         auto it = c->graphs.find(key);
         if (it == c->graphs.end()) {
             hipGraph_t g = nullptr;
