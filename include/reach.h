@@ -162,8 +162,9 @@ const char* reach_last_error(const reach_ctx* ctx);
      "embed.S"    sides per wavefront, 1 or 2 (0 = tuned default)
      "gb.E", "gb.K"  cells per lane / steps per pass of the growth-bound kernel
      "heat.P"     rows per wavefront of the 3-D heat kernel: 2, 3, 4, 5 or 8
-                  (with 16, 12, 8, 8 or 4 wavefronts per block; FP64 builds 2, 3,
-                  4 and 5, FP32 2, 3, 4 and 8; 0 = tuned default)
+                  (with 16, 12, 8, 8 or 4 wavefronts per block, 2 rows on small
+                  grids with 12 or 8; FP64 builds 2, 3, 4 and 5, FP32 2, 3, 4
+                  and 8; 0 = tuned default)
      "mc.waves"   resident waves of the Monte Carlo kernel (0 = default: at most
                   16 per compute unit; at most 4096)
      "batch.split" 1: no packing, one wave per side of each cooperative query

@@ -34,7 +34,9 @@
 // level carries that error one plane inwards, so the 4 halo planes absorb it
 // and every stored plane has the bits of the uncut sweep.  The launcher takes
 // the cut only where it shortens the launch (heat_z_chunks): 200 x 180 x 150
-// FP32 has 64 tiles of both sides for 256 compute units.
+// FP32 has 64 tiles of both sides for 256 compute units.  Smaller grids also take
+// lower tiles, of 12 or 8 waves: an iteration's time is the rows its block holds
+// (100^3 FP64 27 us a step with 16 waves, 25 with 12; 40^3 18 and, with 8, 12).
 //
 // Boundaries without per-cell tests:
 //   - y faces: ghost rows load the mirror image of the grid (even
@@ -72,13 +74,13 @@ struct HeatLds {
     T e[4][2][WV][2][WAVE];   // [level input][plane parity][wave][first/last row][lane]
 };
 
-template <class T>
+template <class T, bool CUT>
 struct HeatCtx {
     const T* src;
     T* dst;
     int64_t plane;       // nx * ny
     int nz;              // planes of this block's sweep (a chunk with its halo planes)
-    int zo, ze;          // output planes [zo, ze) of the sweep
+    int zo, ze;          // output planes [zo, ze) of the sweep (CUT; else all)
     int lane, w, wm, wp; // wave index and the waves above / below (clamped)
     int xl;              // x index this lane loads (mirror-mapped), valid if xload
     bool xload;          // lane loads a grid cell (else it holds 0)
@@ -95,8 +97,8 @@ struct HeatRows {
     bool out[P];         // row is an output row of this tile
 };
 
-template <class T, int P, int WV>
-__device__ __forceinline__ void heat_load(T (&dst)[P], const HeatCtx<T>& c,
+template <class T, int P, int WV, bool CUT>
+__device__ __forceinline__ void heat_load(T (&dst)[P], const HeatCtx<T, CUT>& c,
                                           const HeatRows<T, P>& rows, int z) {
     const T* base = c.src + (int64_t)z * c.plane + c.xl;
 #pragma unroll
@@ -106,9 +108,9 @@ __device__ __forceinline__ void heat_load(T (&dst)[P], const HeatCtx<T>& c,
     }
 }
 
-template <class T, int P, int WV>
+template <class T, int P, int WV, bool CUT>
 __device__ __forceinline__ void heat_publish(HeatLds<T, WV>& L, int lvl, int par,
-                                             const T (&v)[P], const HeatCtx<T>& c) {
+                                             const T (&v)[P], const HeatCtx<T, CUT>& c) {
     L.e[lvl][par][c.w][0][c.lane] = v[0];
     L.e[lvl][par][c.w][1][c.lane] = v[P - 1];
 }
@@ -120,9 +122,9 @@ struct HeatEdges {
     T up[4], dn[4];   // last row of the wave above, first row of the wave below
 };
 
-template <int PH, class T, int WV>
+template <int PH, class T, int WV, bool CUT>
 __device__ __forceinline__ void heat_read_edges(HeatEdges<T>& E, const HeatLds<T, WV>& L,
-                                                const HeatCtx<T>& c) {
+                                                const HeatCtx<T, CUT>& c) {
 #pragma unroll
     for (int l = 0; l < 4; ++l) {
         const int par = pmod(PH - 1 - l, 2);
@@ -150,8 +152,8 @@ __device__ __forceinline__ void heat_apply(T (&out)[P], const T (&cur)[P], const
     }
 }
 
-template <class T, int P>
-__device__ __forceinline__ void heat_zero_ghost(T (&v)[P], const HeatCtx<T>& c) {
+template <class T, int P, bool CUT>
+__device__ __forceinline__ void heat_zero_ghost(T (&v)[P], const HeatCtx<T, CUT>& c) {
 #pragma unroll
     for (int p = 0; p < P; ++p) v[p] = c.zlane ? T(0) : v[p];
 }
@@ -169,9 +171,9 @@ __device__ __forceinline__ void copy_rows(T (&d)[P], const T (&s)[P]) {
 // ring slots, pipes and LDS rows that are rewritten before their next use)
 // and store nothing.  STEADY: the caller guarantees zo <= q < ze and no
 // mirror copy due, so the uniform tests drop out.
-template <int LV, int PH, bool STEADY, bool ZT, class T, int P, int WV>
+template <int LV, int PH, bool STEADY, bool ZT, class T, int P, int WV, bool CUT>
 __device__ __forceinline__ void heat_level(HeatRegs<T, P>& R, HeatLds<T, WV>& L,
-                                           const HeatEdges<T>& E, HeatCtx<T>& c,
+                                           const HeatEdges<T>& E, HeatCtx<T, CUT>& c,
                                            const HeatRows<T, P>& rows, int z) {
     const int q = z - 1 - LV;
     constexpr int par = pmod(PH - 1 - LV, 2);
@@ -203,7 +205,7 @@ __device__ __forceinline__ void heat_level(HeatRegs<T, P>& R, HeatLds<T, WV>& L,
         }
     } else {
         T* out = c.dst + (int64_t)q * c.plane;
-        const bool live = STEADY || (q >= c.zo && q < c.ze);
+        const bool live = STEADY || (CUT ? q >= c.zo && q < c.ze : q >= 0 && q < c.nz);
         T nv[P];
         heat_apply<T, P>(nv, cur, zm, zp, E.up[3], E.dn[3], y, c.cw[3], c.m6cw[3]);
 #pragma unroll
@@ -218,8 +220,8 @@ __device__ __forceinline__ void heat_level(HeatRegs<T, P>& R, HeatLds<T, WV>& L,
     }
 }
 
-template <int PH, bool STEADY, bool ZT, class T, int P, int WV>
-__device__ __forceinline__ void heat_iter(HeatRegs<T, P>& R, HeatLds<T, WV>& L, HeatCtx<T>& c,
+template <int PH, bool STEADY, bool ZT, class T, int P, int WV, bool CUT>
+__device__ __forceinline__ void heat_iter(HeatRegs<T, P>& R, HeatLds<T, WV>& L, HeatCtx<T, CUT>& c,
                                           const HeatRows<T, P>& rows, int z) {
     __syncthreads();
     // plane z + 3 into the slot of plane z - 3, which no level reads any more
@@ -237,8 +239,8 @@ __device__ __forceinline__ void heat_iter(HeatRegs<T, P>& R, HeatLds<T, WV>& L, 
 }
 
 // Six iterations, z0 % 6 == 0 (the ring slots repeat with period 6).
-template <bool STEADY, bool ZT, class T, int P, int WV>
-__device__ __forceinline__ void heat_group(HeatRegs<T, P>& R, HeatLds<T, WV>& L, HeatCtx<T>& c,
+template <bool STEADY, bool ZT, class T, int P, int WV, bool CUT>
+__device__ __forceinline__ void heat_group(HeatRegs<T, P>& R, HeatLds<T, WV>& L, HeatCtx<T, CUT>& c,
                                            const HeatRows<T, P>& rows, int z0) {
     heat_iter<0, STEADY, ZT>(R, L, c, rows, z0);
     heat_iter<1, STEADY, ZT>(R, L, c, rows, z0 + 1);
@@ -255,7 +257,7 @@ __device__ __forceinline__ void heat_group(HeatRegs<T, P>& R, HeatLds<T, WV>& L,
 // zo + 4 <= z, 5 <= z and z + 3 < nz (so z - 4 < ze), then the rest with the
 // tests again.
 template <bool CUT, bool ZT, class T, int P, int WV>
-__device__ __forceinline__ void heat_sweep(HeatRegs<T, P>& R, HeatLds<T, WV>& L, HeatCtx<T>& c,
+__device__ __forceinline__ void heat_sweep(HeatRegs<T, P>& R, HeatLds<T, WV>& L, HeatCtx<T, CUT>& c,
                                            const HeatRows<T, P>& rows) {
     int z = 0;
     if constexpr (CUT) {
@@ -266,7 +268,7 @@ __device__ __forceinline__ void heat_sweep(HeatRegs<T, P>& R, HeatLds<T, WV>& L,
         z = 6;
     }
     for (; z + 6 <= c.nz - 3; z += 6) heat_group<true, ZT>(R, L, c, rows, z);
-    for (; z < c.ze + 4; z += 6) heat_group<false, ZT>(R, L, c, rows, z);
+    for (; z < (CUT ? c.ze : c.nz) + 4; z += 6) heat_group<false, ZT>(R, L, c, rows, z);
 }
 
 // Even reflection of grid index g into [0, n) (period 2n).
@@ -295,13 +297,11 @@ __global__ __launch_bounds__(WAVE * WV) void heat3d_kernel(HeatPass a) {
     }
     const int64_t by = t / a.TX, bx = t - by * a.TX;
 
-    HeatCtx<T> c;
+    HeatCtx<T, CUT> c;
     c.src = (const T*)a.src[side];
     c.dst = (T*)a.dst[side];
     c.plane = a.nx * a.ny;
     c.nz = (int)a.nz;
-    c.zo = 0;
-    c.ze = c.nz;
     if constexpr (CUT) {
         // the chunk's output planes [zs, zt) of the grid; its sweep starts at
         // plane zb and ends before plane ze
@@ -402,19 +402,22 @@ hipError_t launch_center_radius(int dtype, const void* lo, const void* hi, int64
     return hipGetLastError();
 }
 
-template <class T, int P, int WV>
+template <class T, int P, int WV, bool CUT>
 static hipError_t go_heat(const HeatPass& a, int64_t grid, hipStream_t s) {
-    if (a.ZC > 1) {
-        if constexpr (P == HEAT_CUT_ROWS) {
-            hipLaunchKernelGGL((heat3d_kernel<T, P, WV, true>), dim3((unsigned)grid),
-                               dim3(WAVE * WV), 0, s, a);
-            return hipGetLastError();
-        }
-        return hipErrorInvalidValue;
-    }
-    hipLaunchKernelGGL((heat3d_kernel<T, P, WV, false>), dim3((unsigned)grid), dim3(WAVE * WV), 0,
-                       s, a);
+    hipLaunchKernelGGL((heat3d_kernel<T, P, WV, CUT>), dim3((unsigned)grid), dim3(WAVE * WV), 0, s,
+                       a);
     return hipGetLastError();
+}
+
+// The shapes with z chunks: HEAT_CUT_ROWS rows per wave, HEAT_CUT_WAVES waves.
+template <class T>
+static hipError_t go_heat_cut(int WV, const HeatPass& a, int64_t grid, hipStream_t s) {
+    switch (WV) {
+        case 8: return go_heat<T, HEAT_CUT_ROWS, 8, true>(a, grid, s);
+        case 12: return go_heat<T, HEAT_CUT_ROWS, 12, true>(a, grid, s);
+        case 16: return go_heat<T, HEAT_CUT_ROWS, 16, true>(a, grid, s);
+        default: return hipErrorInvalidValue;
+    }
 }
 
 // (P, WV) shapes: rows per wave, waves per block.  FP64 keeps the shapes
@@ -429,16 +432,20 @@ bool heat_has_shape(int dtype, int P, int WV) {
 
 hipError_t launch_heat3d(int dtype, int P, int WV, const HeatPass& a, int64_t grid,
                          hipStream_t s) {
+    if (a.ZC > 1 || (P == HEAT_CUT_ROWS && WV < 16)) {
+        if (P != HEAT_CUT_ROWS) return hipErrorInvalidValue;
+        return dtype == 0 ? go_heat_cut<double>(WV, a, grid, s) : go_heat_cut<float>(WV, a, grid, s);
+    }
     if (dtype == 0) {
-        if (P == 4 && WV == 8) return go_heat<double, 4, 8>(a, grid, s);
-        if (P == 2 && WV == 16) return go_heat<double, 2, 16>(a, grid, s);
-        if (P == 5 && WV == 8) return go_heat<double, 5, 8>(a, grid, s);
-        if (P == 3 && WV == 12) return go_heat<double, 3, 12>(a, grid, s);
+        if (P == 4 && WV == 8) return go_heat<double, 4, 8, false>(a, grid, s);
+        if (P == 2 && WV == 16) return go_heat<double, 2, 16, false>(a, grid, s);
+        if (P == 5 && WV == 8) return go_heat<double, 5, 8, false>(a, grid, s);
+        if (P == 3 && WV == 12) return go_heat<double, 3, 12, false>(a, grid, s);
     } else {
-        if (P == 4 && WV == 8) return go_heat<float, 4, 8>(a, grid, s);
-        if (P == 2 && WV == 16) return go_heat<float, 2, 16>(a, grid, s);
-        if (P == 8 && WV == 4) return go_heat<float, 8, 4>(a, grid, s);
-        if (P == 3 && WV == 12) return go_heat<float, 3, 12>(a, grid, s);
+        if (P == 4 && WV == 8) return go_heat<float, 4, 8, false>(a, grid, s);
+        if (P == 2 && WV == 16) return go_heat<float, 2, 16, false>(a, grid, s);
+        if (P == 8 && WV == 4) return go_heat<float, 8, 4, false>(a, grid, s);
+        if (P == 3 && WV == 12) return go_heat<float, 3, 12, false>(a, grid, s);
     }
     return hipErrorInvalidValue;
 }

@@ -103,7 +103,7 @@ struct HeatPass {
 hipError_t launch_heat3d(int dtype, int P, int WV, const HeatPass& a, int64_t grid,
                          hipStream_t stream);
 bool heat_has_shape(int dtype, int P, int WV);
-constexpr int HEAT_CUT_ROWS = 2;   // rows per wave of the shape built with z chunks
+constexpr int HEAT_CUT_ROWS = 2;   // rows per wave of the shapes built with z chunks (16, 12, 8 waves)
 // c = (lo + hi) / 2, r = (hi - lo) / 2 elementwise (growth-bound start).
 hipError_t launch_center_radius(int dtype, const void* lo, const void* hi, int64_t n, void* c,
                                 void* r, hipStream_t stream);

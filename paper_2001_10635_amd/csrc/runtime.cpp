@@ -518,32 +518,48 @@ struct HeatPlan {
     int P = 4, WV = 8;        // rows per wave, waves per block
     int OX = 0, OY = 0;       // output cells of a tile along x / y
     int64_t TX = 0, TY = 0;   // tiles per side along x / y
-    int64_t ZC = 1, LZ = 0;   // z chunks per tile, output planes of a chunk
+    int64_t ZC = 1, LZ = 0;   // z chunks per tile, output planes of a chunk (ZC = 1: all)
 };
 
-// Cuts the z sweep of `tiles` (both sides') x-y tiles into chunks when that
-// shortens the launch.  A block keeps a compute unit to itself, and its time
-// is its planes, so a launch takes about rounds * iterations: rounds of `cus`
-// blocks, LZ planes plus the pipeline's 4 and, when cut, the 8 halo planes,
-// in groups of 6, plus about 6 for the start.  The uncut sweep stays unless
-// the cut one is 10% shorter by that count: a launch of many rounds is bound
-// by memory, where the halo planes cost more than the last round's idle units
-// (1000^3: 5.9 rounds, uncut).  Measured per step, uncut / cut: 200 x 180 x 150
-// FP32 104 / 39 us.  Built for the default shape only, the fastest of the
-// built ones at every cut size tried (40^3 .. 500^3).
-void heat_z_chunks(int64_t tiles, int64_t nz, int64_t cus, HeatPlan* p) {
-    p->ZC = 1;
-    p->LZ = nz;
-    const auto cost = [&](int64_t LZ, int64_t ZC) {
-        const int64_t planes = LZ + 4 + (ZC > 1 ? 8 : 0);
-        return (double)((tiles * ZC + cus - 1) / cus) * (double)(6 * ((planes + 5) / 6) + 6);
-    };
-    double best = 0.9 * cost(nz, 1);
-    for (int64_t want = 2; want <= std::min<int64_t>(nz / 4, 256); ++want) {
-        const int64_t LZ = std::max<int64_t>(4, (nz + want - 1) / want);
-        const int64_t ZC = (nz + LZ - 1) / LZ;
-        const double t = cost(LZ, ZC);
-        if (t < best) { best = t; p->ZC = ZC; p->LZ = LZ; }
+// The waves per block and the z chunks of a grid at 2 rows per wave.  A launch takes
+// about rounds * iterations: rounds of `cus` blocks, and iterations in groups of 6, of
+// LZ planes plus 4 for the pipeline and, when cut, 4 halo planes before the chunk
+// (those behind it are read while the pipeline drains); the start costs about 9 more.
+// An iteration of 12 or 8 waves takes 0.82 or 0.64 of one of 16 (measured: 0.66,
+// 0.55 and 0.42 us FP32, 0.95, 0.77 and 0.60 FP64), for 16 or 8 output rows
+// instead of 24: the narrower blocks pay where the grid is too small to occupy the
+// chip with wide ones (at most 4 rounds: 600 x 600 x 25 FP32 takes 80 us with 8 waves in
+// 7 rounds, 75 with 16 in 3).  Two FP32 blocks of 8 waves share a compute unit and
+// then take 1.53 times one's time instead of twice.
+//
+// The uncut sweep of 16 waves stays unless the best is 10% shorter by that count: a
+// launch of many rounds is bound by memory, where the halo planes cost more than
+// the last round's idle units (1000^3: 5.9 rounds, uncut).  Measured per step, FP32 / FP64:
+//                      uncut        16 waves, cut   12 waves        8 waves
+//   40^3                              14 / 18       12 / 15          9.4 / 12
+//   100^3              79 / 115       19 / 27       19 / 25         20 / 27
+//   200 x 180 x 150   105 / 151       40 / 64       51 / 74         54 / 98
+void heat_z_chunks(int64_t nx, int64_t ny, int64_t nz, bool f64, int64_t cus, HeatPlan* p) {
+    double best = 0.0;
+    for (const int WV : {16, 12, 8}) {
+        const int64_t OX = 64 - 8, OY = HEAT_CUT_ROWS * WV - 8;
+        const int64_t TX = (nx + OX - 1) / OX, TY = (ny + OY - 1) / OY;
+        const double it = WV == 16 ? 1.0 : WV == 12 ? 0.82 : 0.64;
+        for (int64_t want = 1; want == 1 || want <= std::min<int64_t>(nz / 4, 256); ++want) {
+            const int64_t LZ = want == 1 ? nz : std::max<int64_t>(4, (nz + want - 1) / want);
+            const int64_t ZC = (nz + LZ - 1) / LZ;
+            const int64_t planes = LZ + 4 + (ZC > 1 ? 4 : 0);
+            const int64_t r = (2 * TX * TY * ZC + cus - 1) / cus;
+            if (WV < 16 && r > 4) break;   // (more chunks only add rounds)
+            const double rounds = !f64 && WV == 8 ? 1.0 + 0.53 * (double)(r - 1) : (double)r;
+            const double t = it * rounds * (double)(6 * ((planes + 5) / 6) + 9);
+            if (WV == 16 && want == 1) best = 0.9 * t;   // the plan as it stands
+            else if (t < best) {
+                best = t;
+                p->WV = WV; p->OY = (int)OY; p->TY = TY;
+                p->ZC = ZC; p->LZ = LZ;
+            }
+        }
     }
 }
 
@@ -577,7 +593,7 @@ reach_status plan_heat(reach_ctx* c, const reach_system* s, reach_dtype dtype, H
     p->TX = (nx + p->OX - 1) / p->OX;
     p->TY = (ny + p->OY - 1) / p->OY;
     p->LZ = (int64_t)s->prm[2];
-    if (P == HEAT_CUT_ROWS) heat_z_chunks(2 * p->TX * p->TY, p->LZ, c->cus, p);
+    if (P == HEAT_CUT_ROWS) heat_z_chunks(nx, ny, p->LZ, dtype == REACH_F64, c->cus, p);
     return REACH_OK;
 }
 

@@ -97,6 +97,33 @@ def test_heat3d_z_chunks_match_oracle(rc, grid, dtype):
             assert_rel(g_hi, o_hi, RTOL[np.dtype(dtype)], f"upper P={P}")
 
 
+@pytest.mark.parametrize("dtype", [np.float64, np.float32], ids=["f64", "f32"])
+@pytest.mark.parametrize("grid,tiles", [((57, 24, 10), 6), ((57, 25, 24), 8), ((57, 96, 24), 12),
+                                        ((113, 120, 24), 15)], ids=str)
+def test_heat3d_block_heights_match_oracle(rc, grid, tiles, dtype):
+    """Grids whose plan takes 8 waves uncut, and 8, 12 and 16 waves with z
+    chunks (tiles of 56 x 8, 16 and 24 outputs): the embedding, and the growth
+    bound by the same plan."""
+    prm, lo, hi, dt = heat_case(grid, dtype, seed=200 + sum(grid))
+    sysd = R.make_system(R.REACH_HEAT3D, lo.size, prm, 0)
+    dtc = R.REACH_F64 if dtype == np.float64 else R.REACH_F32
+    if torch.cuda.get_device_properties(0).multi_processor_count == 256:
+        assert R.reach_plan_embed(rc.ctx, sysd, dtc, 3)["tiles"] == tiles
+    rt = RTOL[np.dtype(dtype)]
+    wide = (lo.astype(np.float64), hi.astype(np.float64))
+    o_lo, o_hi = oracle.embed_rk4(oracle.HEAT3D, prm, *wide, dt=dt, nsteps=3)
+    say(f"heat3d block heights {grid} {np.dtype(dtype).name}")
+    g_lo, g_hi, st = run_embed(rc, prm, lo, hi, dt, 3)
+    assert st == R.REACH_OK
+    assert_rel(g_lo, o_lo, rt, "lower")
+    assert_rel(g_hi, o_hi, rt, "upper")
+    o_lo, o_hi = oracle.growth_bound(oracle.HEAT3D, prm, *wide, dt=dt, nsteps=3)
+    g_lo, g_hi = rc.growth_bound(R.REACH_HEAT3D, prm, to_dev(lo), to_dev(hi), dt, 3)
+    assert rc.sync() == R.REACH_OK
+    assert_rel(to_host(g_lo), o_lo, rt, "gb lower")
+    assert_rel(to_host(g_hi), o_hi, rt, "gb upper")
+
+
 def test_heat3d_resume_alias_and_zero_steps(rc):
     prm, lo, hi, dt = heat_case((90, 40, 11), np.float64, seed=42)
     say("heat3d resume")
