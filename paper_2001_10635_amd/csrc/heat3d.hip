@@ -409,7 +409,8 @@ static hipError_t go_heat(const HeatPass& a, int64_t grid, hipStream_t s) {
     return hipGetLastError();
 }
 
-// The shapes with z chunks: HEAT_CUT_ROWS rows per wave, HEAT_CUT_WAVES waves.
+// The shapes with z chunks: HEAT_CUT_ROWS rows per wave in 8, 12 or 16 waves (the
+// lower tiles of small grids also uncut).
 template <class T>
 static hipError_t go_heat_cut(int WV, const HeatPass& a, int64_t grid, hipStream_t s) {
     switch (WV) {

@@ -1667,8 +1667,9 @@ int seg_E(int64_t n, int cap) {
 }
 
 // Whether a batch packs: option batch.pack 1 always, 2 never, 0 (default)
-// when it has more queries than twice the resident waves (below that every
-// query gets a wave of its own and packing would only lengthen the longest).
+// when it has more queries than 16 per compute unit, or than twice option
+// batch.waves (below that every query side gets a wave of its own and packing
+// would only lengthen the longest).
 bool batch_packs(const reach_ctx* c, int64_t nq) {
     const int64_t mode = c ? opt_get(c, "batch.pack") : 0;
     if (mode == 1) return true;
