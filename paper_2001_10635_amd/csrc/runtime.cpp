@@ -60,8 +60,10 @@ struct GraphKey {
 struct TuneEntry { int E; int K; int S; };
 
 // The last shapes estimated (fastest_shape), by what they depend on: a call of a
-// few microseconds would otherwise spend one on the estimate each time.
+// few microseconds would otherwise spend one on the estimate each time.  Under a
+// lock of its own: planning otherwise only reads the context.
 struct ShapeMemo {
+    std::mutex m;
     struct Slot { int64_t n = 0, K = 0; int kind = 0, dtype = 0, flags = 0; TuneEntry t{0, 0, 0}; };
     Slot slot[16];
     int next = 0;
@@ -393,8 +395,12 @@ TuneEntry fastest_shape(reach_ctx* c, int kind, int dtype, bool cell_in, int64_t
                         bool gb = false) {
     const int64_t simds = (int64_t)4 * c->cus;
     const int flags = (cell_in ? 1 : 0) | (gb ? 2 : 0);
-    for (const ShapeMemo::Slot& m : c->shapes.slot)
-        if (m.n == n && m.K == K && m.kind == kind && m.dtype == dtype && m.flags == flags) return m.t;
+    {
+        std::lock_guard<std::mutex> lk(c->shapes.m);
+        for (const ShapeMemo::Slot& m : c->shapes.slot)
+            if (m.n == n && m.K == K && m.kind == kind && m.dtype == dtype && m.flags == flags)
+                return m.t;
+    }
     const int S = kind == REACH_LIN3 ? 2 : 1;
     TuneEntry best{0, 0, S};
     double t_best = 1e300;
@@ -406,6 +412,7 @@ TuneEntry fastest_shape(reach_ctx* c, int kind, int dtype, bool cell_in, int64_t
             if (t < t_best) { t_best = t; best.E = E; best.K = (int)k; }
         }
     }
+    std::lock_guard<std::mutex> lk(c->shapes.m);
     ShapeMemo::Slot& m = c->shapes.slot[c->shapes.next];
     c->shapes.next = (c->shapes.next + 1) % 16;
     m.n = n; m.K = K; m.kind = kind; m.dtype = dtype; m.flags = flags; m.t = best;
