@@ -224,9 +224,9 @@ reach_status reach_autotune_embed(reach_ctx* ctx, const reach_system* sys, reach
 /* Bytes of device workspace reach_embed_rk4 (m = 0) or reach_montecarlo
    (m = sample count) needs for this system and dtype with the context's
    current tuning; 0 if none is needed; (size_t)-1 on invalid arguments.
-   For an embedding that one window of the kernel holds, the bytes are those a
-   long run uses to cut the chain into several windows; without them it runs
-   in one window, with the same results. */
+   Calls that may run at the same time (on different streams) need a workspace
+   each, except embeddings that do not use theirs: chains that one window of the
+   kernel holds (0 bytes), and runs of one pass not in place. */
 size_t reach_workspace_bytes(reach_ctx* ctx, const reach_system* sys, reach_dtype dtype,
                              int64_t m);
 
@@ -243,8 +243,8 @@ reach_status reach_sync(reach_ctx* ctx, void* stream);
  *   p_lo, p_hi  n_in elements (NULL iff n_in == 0)
  *   r_lo, r_hi  n elements; may be the same arrays as x_lo, x_hi
  *   workspace   device memory of reach_workspace_bytes(ctx, sys, dtype, 0)
- *               bytes (may be NULL when that is 0, and for a chain that one
- *               window of the kernel holds); must not overlap the other arrays
+ *               bytes (may be NULL when that is 0); must not overlap the
+ *               other arrays; not shared with a call that may run meanwhile
  * nsteps = 0 copies the box.  Errors: REACH_E_INVAL for n < 1, n_in not in
  * {0, 1, n}, dt not finite or <= 0, nsteps < 0, NULL required pointers,
  * unknown kind or nonzero reserved field, workspace too small;

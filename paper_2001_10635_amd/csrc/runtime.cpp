@@ -69,6 +69,70 @@ struct ShapeMemo {
     int next = 0;
 };
 
+// Device memory of the passes of a chain that one window holds and that is cut
+// into several all the same (see plan_embed).  Such a call needs no workspace of
+// the caller's, and calls on different streams or threads do not wait for each
+// other's host side, so each stream gets a slot of its own as long as there are
+// any; after that the one used longest ago is taken over.  What keeps two runs in
+// one slot apart is the slot's lock (a run's passes are issued under it) and its
+// event (a run waits for the one before, on whichever stream that was); the
+// stream's handle only chooses the slot.
+struct CutScratch {
+    static constexpr int kSlots = 16;
+    static constexpr size_t kSlotBytes = 32768;   // 2n values: 2048 FP64 or 4096 FP32 cells
+    struct Slot {
+        std::mutex m;
+        hipEvent_t done = nullptr;   // the slot's last run
+        bool recorded = false;       // under m
+        bool taken = false;          // under CutScratch::m
+        hipStream_t stream = nullptr;
+        uint64_t last = 0;
+    };
+    std::mutex m;
+    uint64_t calls = 0;
+    Slot slot[kSlots];
+    char* mem = nullptr;
+
+    int pick(hipStream_t s) {
+        std::lock_guard<std::mutex> lk(m);
+        int k = -1;
+        for (int i = 0; i < kSlots && k < 0; ++i)
+            if (slot[i].taken && slot[i].stream == s) k = i;
+        for (int i = 0; i < kSlots && k < 0; ++i)
+            if (!slot[i].taken) k = i;
+        if (k < 0) {
+            k = 0;
+            for (int i = 1; i < kSlots; ++i)
+                if (slot[i].last < slot[k].last) k = i;
+        }
+        slot[k].taken = true;
+        slot[k].stream = s;
+        slot[k].last = ++calls;
+        return k;
+    }
+};
+
+// A run's hold on a slot: from the wait for the slot's previous run to the event
+// of its own last pass, which is recorded however the run's issue ends.
+struct CutRun {
+    CutScratch::Slot* slot = nullptr;
+    hipStream_t stream = nullptr;
+    char* mem = nullptr;
+    hipError_t begin(CutScratch& c, hipStream_t s) {
+        const int k = c.pick(s);
+        c.slot[k].m.lock();
+        slot = &c.slot[k];
+        stream = s;
+        mem = c.mem + (size_t)k * CutScratch::kSlotBytes;
+        return slot->recorded ? hipStreamWaitEvent(s, slot->done, 0) : hipSuccess;
+    }
+    ~CutRun() {
+        if (!slot) return;
+        slot->recorded |= hipEventRecord(slot->done, stream) == hipSuccess;
+        slot->m.unlock();
+    }
+};
+
 }  // namespace
 
 // Host worker threads kept for the life of a context (starting threads per
@@ -171,6 +235,7 @@ struct reach_ctx {
     // (kind, dtype, log2 n bucket, per-cell inputs)
     std::map<std::tuple<int, int, int, int>, TuneEntry> tune;
     ShapeMemo shapes;
+    CutScratch cut;                      // its memory follows the status word
     std::map<std::pair<int, int>, int> batch_tune;        // (kind, log2 n bucket) -> pack E cap
     int64_t batch_waves[2] = {0, 0};                     // autotuned resident waves of the
                                                          // narrow / wide packing kernel (0 = none)
@@ -304,6 +369,7 @@ struct EmbedPlan {
     int64_t OUT = 0;
     int H = 0;
     int64_t passes = 1;
+    bool cut_one = false;   // several windows although one holds the chain
 };
 
 // Defaults measured on MI355X for the 2^26-cell chains (overridden by the
@@ -388,9 +454,17 @@ double step_us(int kind, int dtype, bool cell_in, int S, int E, int64_t K, int64
     return (double)r * c * E + 0.06 + (2.5 + bytes / 7.0e6) / (double)K;
 }
 
+// Steps of a run that, not in place, never needs the workspace: one pass of the
+// default windows (and of those that per-cell LIN3 inputs took at 12 cells a lane).
+int64_t one_pass_steps(int kind, int dtype, bool cell_in, int64_t n) {
+    return std::max(12, default_tune(kind, dtype, cell_in, n).K);
+}
+
 // The shape of the least estimated step time, at K steps per pass (K = 0: the
 // best K as well, up to 64), among the embedding's shapes or (gb) the growth
-// bound's.
+// bound's.  A chain of several windows takes no smaller K than one_pass_steps, so
+// that what one pass of the default windows did stays one pass, which leaves the
+// workspace alone (200003 RD cells, FP64: 0.667 us a step at K = 47 for 0.638 at 15).
 TuneEntry fastest_shape(reach_ctx* c, int kind, int dtype, bool cell_in, int64_t n, int64_t K,
                         bool gb = false) {
     const int64_t simds = (int64_t)4 * c->cus;
@@ -402,12 +476,14 @@ TuneEntry fastest_shape(reach_ctx* c, int kind, int dtype, bool cell_in, int64_t
                 return m.t;
     }
     const int S = kind == REACH_LIN3 ? 2 : 1;
+    const int64_t least =
+        gb || smallest_E(kind, dtype, S, n) ? 4 : one_pass_steps(kind, dtype, cell_in, n);
     TuneEntry best{0, 0, S};
     double t_best = 1e300;
     for (int E : {1, 2, 4, 6, 8, 12, 16, 20, 24, 28, 32, 48, 64}) {
         if (gb ? !gb_has_E(E) : !embed_has_shape(kind, dtype, E, S)) continue;
         const int64_t top = std::min<int64_t>(64, 8 * E - 1);
-        for (int64_t k = K ? K : std::min<int64_t>(4, top); k <= (K ? K : top); ++k) {
+        for (int64_t k = K ? K : least; k <= (K ? K : top); ++k) {
             const double t = step_us(kind, dtype, cell_in, S, E, k, n, simds);
             if (t < t_best) { t_best = t; best.E = E; best.K = (int)k; }
         }
@@ -444,21 +520,23 @@ TuneEntry default_shape(reach_ctx* c, int kind, int dtype, bool cell_in, int64_t
     return default_tune(kind, dtype, cell_in, n);
 }
 
-// split: the caller has the workspace of a multi-pass run, so that a chain may
-// be cut into more windows and passes than the fewest; one_steps: the longest
-// run that keeps a chain one window holds in that window.
+// have_ws: the caller has the workspace of a multi-pass run, so that a chain of
+// several windows may be cut into more of them, and more passes, than the fewest;
+// cut_one: a chain that one window holds may be cut (its passes run in CutScratch);
+// one_steps: the longest run that keeps such a chain in that window.
 reach_status plan_embed(reach_ctx* c, const reach_system* s, reach_dtype dtype, int64_t nsteps,
-                        EmbedPlan* p, bool split = true, int64_t one_steps = kSplitSteps) {
+                        EmbedPlan* p, bool have_ws = true, bool cut_one = true,
+                        int64_t one_steps = kSplitSteps) {
     const int64_t n = s->n;
     const bool cell_in = s->n_in > 1;
     const int64_t oE = opt_get(c, "embed.E"), oK = opt_get(c, "embed.K"), oS = opt_get(c, "embed.S");
     const int64_t simds = (int64_t)4 * c->cus;
     // (up to two cells per lane one window is always the better one)
-    if (split && n > 128 && !oE && !oK && !oS &&
+    if ((have_ws || cut_one) && n > 128 && !oE && !oK && !oS &&
         (c->tune.empty() || !c->tune.count({s->kind, dtype, n_bucket(n), cell_in ? 1 : 0})) &&
         estimated(s->kind, dtype, cell_in, n, simds)) {
         const int one = smallest_E(s->kind, dtype, s->kind == REACH_LIN3 ? 2 : 1, n);
-        if (!one || nsteps > (s->kind == REACH_LIN3 ? 1 : one_steps)) {
+        if (one ? cut_one && nsteps > (s->kind == REACH_LIN3 ? 1 : one_steps) : have_ws) {
             // the best K for many steps gives the pass count; the steps are
             // spread evenly over the passes, and the shape is the best for those
             const TuneEntry t = fastest_shape(c, s->kind, dtype, cell_in, n, 0);
@@ -481,10 +559,12 @@ reach_status plan_embed(reach_ctx* c, const reach_system* s, reach_dtype dtype, 
                          (double)steps * step_us(s->kind, dtype, cell_in, t.S, u.E, K, n, simds));
             if (u.E && many_us < one_us) {
                 set_windows(p, u.E, u.S, K, n, nsteps);
+                p->cut_one = one != 0;
                 if (p->W > 1) return REACH_OK;
             }
         }
     }
+    p->cut_one = false;
     const TuneEntry te = tuned(c, s->kind, dtype, n, cell_in);
     int S = oS ? (int)oS : (oE ? (s->kind == REACH_LIN3 ? 2 : te.S) : te.S);
     if (s->kind == REACH_LIN3 && S == 1)
@@ -782,9 +862,7 @@ reach_status autotune_heat3d(reach_ctx* c, const reach_system* s, reach_dtype dt
 size_t embed_ws_bytes(reach_ctx* c, const reach_system* s, reach_dtype dtype) {
     if (s->kind == REACH_HEAT3D) return (size_t)2 * (size_t)s->n * dsize(dtype);
     EmbedPlan p;
-    // enough for a run of any length: a long one may cut a chain that a short
-    // one keeps in one window
-    if (plan_embed(c, s, dtype, (int64_t)1 << 20, &p) != REACH_OK) return (size_t)-1;
+    if (plan_embed(c, s, dtype, (int64_t)1 << 20, &p, true, false) != REACH_OK) return (size_t)-1;
     if (p.W == 1) return 0;
     return (size_t)2 * (size_t)s->n * dsize(dtype);
 }
@@ -956,7 +1034,11 @@ reach_status reach_ctx_create(int device, reach_ctx** out) {
     // failure is reported by that entry point, not here)
     (void)noalloc_setup(device);
     if (const char* e = std::getenv("REACH_LOG")) c->log = e[0] && std::strcmp(e, "0") != 0;
-    if (hipMalloc((void**)&c->status, 256) != hipSuccess) { delete c; return REACH_E_DEVICE; }
+    if (hipMalloc((void**)&c->status, 256 + CutScratch::kSlots * CutScratch::kSlotBytes) != hipSuccess) {
+        delete c;
+        return REACH_E_DEVICE;
+    }
+    c->cut.mem = (char*)c->status + 256;
     if (hipMemset(c->status, 0, 256) != hipSuccess) { hipFree(c->status); delete c; return REACH_E_DEVICE; }
     if (hipEventCreateWithFlags(&c->staging_ev, hipEventDisableTiming) != hipSuccess) {
         hipFree(c->status); delete c; return REACH_E_DEVICE;
@@ -964,10 +1046,14 @@ reach_status reach_ctx_create(int device, reach_ctx** out) {
     bool ok = hipEventCreateWithFlags(&c->batch_ev, hipEventDisableTiming) == hipSuccess;
     for (int k = 0; k < 2 && ok; ++k)
         ok = hipEventCreateWithFlags(&c->block_ev[k], hipEventDisableTiming) == hipSuccess;
+    for (int k = 0; k < CutScratch::kSlots && ok; ++k)
+        ok = hipEventCreateWithFlags(&c->cut.slot[k].done, hipEventDisableTiming) == hipSuccess;
     ok = ok && hipStreamCreateWithFlags(&c->copy_stream, hipStreamNonBlocking) == hipSuccess;
     if (!ok) {
         for (hipEvent_t e : {c->staging_ev, c->batch_ev, c->block_ev[0], c->block_ev[1]})
             if (e) hipEventDestroy(e);
+        for (CutScratch::Slot& k : c->cut.slot)
+            if (k.done) hipEventDestroy(k.done);
         hipFree(c->status);
         delete c;
         return REACH_E_DEVICE;
@@ -990,6 +1076,8 @@ void reach_ctx_destroy(reach_ctx* c) {
     if (c->batch_ev) hipEventDestroy(c->batch_ev);
     for (hipEvent_t e : c->block_ev)
         if (e) hipEventDestroy(e);
+    for (CutScratch::Slot& k : c->cut.slot)
+        if (k.done) hipEventDestroy(k.done);
     if (c->copy_stream) hipStreamDestroy(c->copy_stream);
     if (c->status) hipFree(c->status);
     c->pool.reset();
@@ -1068,6 +1156,15 @@ reach_status reach_sync(reach_ctx* c, void* stream) {
     return REACH_OK;
 }
 
+// Whether work issued to this stream now goes into a graph (as far as can be told).
+static bool capturing(hipStream_t s) {
+    if (!s) return false;   // the default stream cannot be captured
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &st) == hipSuccess) return st != hipStreamCaptureStatusNone;
+    (void)hipGetLastError();
+    return true;
+}
+
 static reach_status embed_run(reach_ctx* c, const reach_system* s, reach_dtype dtype,
                               const void* x_lo, const void* x_hi, const void* p_lo,
                               const void* p_hi, double t0, double dt, int64_t nsteps, void* r_lo,
@@ -1093,8 +1190,22 @@ static reach_status embed_run(reach_ctx* c, const reach_system* s, reach_dtype d
         return embed_heat3d(c, s, dtype, x_lo, x_hi, dt, nsteps, r_lo, r_hi, ws, ws_bytes, hs);
     EmbedPlan pl;
     const bool have_ws = ws && ws_bytes >= 2 * bytes;
-    st = plan_embed(c, s, dtype, nsteps, &pl, have_ws, one_steps);
+    const bool alias = (r_lo == x_lo) || (r_hi == x_hi) || (r_lo == x_hi) || (r_hi == x_lo);
+    st = plan_embed(c, s, dtype, nsteps, &pl, have_ws, true, one_steps);
     if (st != REACH_OK) return st;
+    // a cut chain that one window holds runs its passes in the context's scratch,
+    // which a captured call (replayed at any time, beside anything) does not use
+    CutRun cut;
+    if (pl.cut_one && (pl.passes >= 2 || alias)) {
+        if (2 * bytes > CutScratch::kSlotBytes || capturing(hs)) {
+            st = plan_embed(c, s, dtype, nsteps, &pl, have_ws, false, one_steps);
+            if (st != REACH_OK) return st;
+        } else {
+            HIPCHK(c, cut.begin(c->cut, hs));
+            ws = cut.mem;
+            ws_bytes = CutScratch::kSlotBytes;
+        }
+    }
     log_call(c, "\"call\": \"embed\", \"kind\": %d, \"dtype\": \"%s\", \"n\": %lld, "
                 "\"nsteps\": %lld, \"E\": %d, \"K\": %d, \"S\": %d, \"tiles\": %lld, "
                 "\"passes\": %lld",
@@ -1102,7 +1213,6 @@ static reach_status embed_run(reach_ctx* c, const reach_system* s, reach_dtype d
              (long long)(pl.S == 1 ? 2 * pl.W : pl.W), (long long)pl.passes);
 
     // buffers: the last pass writes r; multi-tile passes never run in place
-    const bool alias = (r_lo == x_lo) || (r_hi == x_hi) || (r_lo == x_hi) || (r_hi == x_lo);
     const bool inplace_ok = (pl.W == 1);
     const bool need_ws = !inplace_ok && (pl.passes >= 2 || alias);
     void *w_lo = nullptr, *w_hi = nullptr;

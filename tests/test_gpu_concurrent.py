@@ -1,0 +1,115 @@
+"""Embeddings in flight at the same time, captured, or with result arrays that
+overlap their inputs: the same bits as the call by itself."""
+import numpy as np
+import pytest
+
+from tests.gpu_util import say, to_dev
+from tests.test_gpu_embed import make_case
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+R = pytest.importorskip("paper_2001_10635_amd")
+
+NP = {R.REACH_F64: np.float64, R.REACH_F32: np.float32}
+
+
+@pytest.fixture(scope="module")
+def rc():
+    r = R.Reach(0)
+    yield r
+    r.close()
+
+
+def dev_case(variant, n, dtc, seed):
+    """(kind, prm, dt, device arrays x_lo, x_hi, p_lo, p_hi) of one chain."""
+    kind, prm, lo, hi, pl, ph, dt = make_case(variant, n, NP[dtc], seed=seed)
+    return (kind, prm, dt) + tuple(None if a is None else to_dev(a) for a in (lo, hi, pl, ph))
+
+
+def embed(rc, case, dtc, nsteps, r_lo, r_hi, ws=None, stream=None):
+    kind, prm, dt, x_lo, x_hi, p_lo, p_hi = case
+    sysd = R.make_system(kind, x_lo.numel(), prm, 0 if p_lo is None else p_lo.numel())
+    R.reach_embed_rk4(rc.ctx, sysd, dtc, x_lo, x_hi, p_lo, p_hi, 0.0, dt, nsteps, r_lo, r_hi, ws,
+                      0 if ws is None else ws.numel(), stream)
+
+
+@pytest.mark.parametrize("variant,n,dtc,nsteps", [
+    ("rd", 1000, R.REACH_F64, 100), ("ctm", 4000, R.REACH_F32, 90), ("lin3_cell", 900, R.REACH_F64, 40),
+    ("rd_cell", 2048, R.REACH_F64, 60), ("rd", 5000, R.REACH_F64, 20), ("ctm", 9000, R.REACH_F32, 12),
+    ("lin3_cell", 5000, R.REACH_F64, 12)])
+@pytest.mark.parametrize("streams", [2, 18])
+def test_streams_share_one_object(rc, variant, n, dtc, nsteps, streams):
+    """Chains that one window holds, and runs of one pass, on several streams of
+    one object (more streams than the context keeps scratch slots for), and with
+    one workspace given to all: they use none, so no call changes another's box."""
+    cases = [dev_case(variant, n, dtc, 40 + k) for k in range(streams)]
+    refs = []
+    for c in cases:
+        refs.append(rc.embed(c[0], c[1], c[3], c[4], c[2], nsteps, p_lo=c[5], p_hi=c[6]))
+        assert rc.sync() == R.REACH_OK
+    st = [torch.cuda.Stream() for _ in range(streams)]
+    ws = torch.empty(2 * n * cases[0][3].element_size(), dtype=torch.uint8, device="cuda")
+    outs = [(torch.empty_like(c[3]), torch.empty_like(c[4])) for c in cases]
+    torch.cuda.synchronize()
+    say(f"streams {variant} n={n} N={nsteps} streams={streams}")
+    for shared in (False, True):
+        for lo, hi in outs:
+            lo.zero_()
+            hi.zero_()
+        torch.cuda.synchronize()
+        for _ in range(3):
+            for c, s, (lo, hi) in zip(cases, st, outs):
+                if shared:
+                    embed(rc, c, dtc, nsteps, lo, hi, ws, s)
+                else:
+                    rc.embed(c[0], c[1], c[3], c[4], c[2], nsteps, p_lo=c[5], p_hi=c[6], r_lo=lo,
+                             r_hi=hi, stream=s)
+        torch.cuda.synchronize()
+        assert rc.sync() == R.REACH_OK
+        for (lo, hi), (a, b) in zip(outs, refs):
+            assert torch.equal(lo, a) and torch.equal(hi, b)
+
+
+def test_workspace_bytes_of_chains_one_window_holds(rc):
+    """No workspace: nothing of the caller's is written but the results."""
+    for n in (1, 64, 129, 1000, 2048):
+        assert R.reach_workspace_bytes(rc.ctx, R.make_system(R.REACH_RD, n, (1.0,), 0),
+                                       R.REACH_F64, 0) == 0
+    assert R.reach_workspace_bytes(rc.ctx, R.make_system(R.REACH_RD, 3000, (1.0,), 0),
+                                   R.REACH_F64, 0) == 2 * 3000 * 8
+
+
+@pytest.mark.parametrize("variant", ["ctm", "rd", "lin3"])
+@pytest.mark.parametrize("n", [200, 1000])
+def test_captured_call_keeps_to_its_own_arrays(rc, variant, n):
+    """A captured embedding replays beside eager ones of the same object and
+    stream, and after the object's workspace has grown."""
+    c = dev_case(variant, n, R.REACH_F64, 3)
+    other = dev_case(variant, n, R.REACH_F64, 4)
+    big = dev_case(variant, 70001, R.REACH_F64, 5)
+    ref = rc.embed(c[0], c[1], c[3], c[4], c[2], 70, p_lo=c[5], p_hi=c[6])
+    oref = rc.embed(other[0], other[1], other[3], other[4], other[2], 70, p_lo=other[5],
+                    p_hi=other[6])
+    assert rc.sync() == R.REACH_OK
+    lo, hi = torch.empty_like(c[3]), torch.empty_like(c[4])
+    o_lo, o_hi = torch.empty_like(c[3]), torch.empty_like(c[4])
+    s1, s2 = torch.cuda.Stream(), torch.cuda.Stream()
+    g = torch.cuda.CUDAGraph()
+    say(f"capture {variant} n={n}")
+    with torch.cuda.graph(g, stream=s1):
+        rc.embed(c[0], c[1], c[3], c[4], c[2], 70, p_lo=c[5], p_hi=c[6], r_lo=lo, r_hi=hi)
+    for k in range(4):
+        lo.zero_()
+        o_lo.zero_()
+        torch.cuda.synchronize()
+        with torch.cuda.stream(s2):
+            g.replay()
+        rc.embed(other[0], other[1], other[3], other[4], other[2], 70, p_lo=other[5],
+                 p_hi=other[6], r_lo=o_lo, r_hi=o_hi, stream=s1)
+        torch.cuda.synchronize()
+        assert rc.sync() == R.REACH_OK
+        assert torch.equal(lo, ref[0]) and torch.equal(hi, ref[1])
+        assert torch.equal(o_lo, oref[0]) and torch.equal(o_hi, oref[1])
+        if k == 1:
+            rc.embed(big[0], big[1], big[3], big[4], big[2], 70, p_lo=big[5], p_hi=big[6])
