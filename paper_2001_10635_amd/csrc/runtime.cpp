@@ -1165,6 +1165,11 @@ static bool capturing(hipStream_t s) {
     return true;
 }
 
+// Whether [p, p + np) and [q, q + nq) share a byte (p may be NULL).
+static bool overlaps(const void* p, size_t np, const void* q, size_t nq) {
+    return p && (const char*)p < (const char*)q + nq && (const char*)q < (const char*)p + np;
+}
+
 static reach_status embed_run(reach_ctx* c, const reach_system* s, reach_dtype dtype,
                               const void* x_lo, const void* x_hi, const void* p_lo,
                               const void* p_hi, double t0, double dt, int64_t nsteps, void* r_lo,
@@ -1191,7 +1196,16 @@ static reach_status embed_run(reach_ctx* c, const reach_system* s, reach_dtype d
     EmbedPlan pl;
     const bool have_ws = ws && ws_bytes >= 2 * bytes;
     const bool alias = (r_lo == x_lo) || (r_hi == x_hi) || (r_lo == x_hi) || (r_hi == x_lo);
-    st = plan_embed(c, s, dtype, nsteps, &pl, have_ws, true, one_steps);
+    // one window has read all its inputs before it writes a result; several read
+    // the per-cell inputs again in every pass and the box beside each other's
+    // results, so result arrays over either (the box's own aside) keep to the one
+    bool cut_one = true;
+    const size_t in_bytes = (size_t)s->n_in * dsize(dtype);
+    for (const void* r : {(const void*)r_lo, (const void*)r_hi}) {
+        cut_one &= !overlaps(p_lo, in_bytes, r, bytes) && !overlaps(p_hi, in_bytes, r, bytes);
+        for (const void* x : {x_lo, x_hi}) cut_one &= r == x || !overlaps(x, bytes, r, bytes);
+    }
+    st = plan_embed(c, s, dtype, nsteps, &pl, have_ws, cut_one, one_steps);
     if (st != REACH_OK) return st;
     // a cut chain that one window holds runs its passes in the context's scratch,
     // which a captured call (replayed at any time, beside anything) does not use
@@ -1603,16 +1617,13 @@ reach_status reach_growth_bound(reach_ctx* c, const reach_system* s, reach_dtype
     // The last pass writes the box itself unless the result arrays overlap what
     // other windows still read then (per-cell inputs; in a run of one pass the
     // box): such a call combines in a kernel of its own.
-    const auto overlap = [](const void* p, size_t np, const void* q, size_t nq) {
-        return p && (const char*)p < (const char*)q + nq && (const char*)q < (const char*)p + np;
-    };
     const size_t in_bytes = (size_t)s->n_in * dsize(dtype);
     bool fused = true;
     if (a.W > 1)
         for (const void* q : {(const void*)r_lo, (const void*)r_hi}) {
-            fused &= !overlap(a.p_lo, in_bytes, q, bytes) && !overlap(a.p_hi, in_bytes, q, bytes);
+            fused &= !overlaps(a.p_lo, in_bytes, q, bytes) && !overlaps(a.p_hi, in_bytes, q, bytes);
             if (passes == 1)
-                fused &= !overlap(x_lo, bytes, q, bytes) && !overlap(x_hi, bytes, q, bytes);
+                fused &= !overlaps(x_lo, bytes, q, bytes) && !overlaps(x_hi, bytes, q, bytes);
         }
     a.r_lo = r_lo; a.r_hi = r_hi;
     a.status = c->status;

@@ -113,3 +113,30 @@ def test_captured_call_keeps_to_its_own_arrays(rc, variant, n):
         assert torch.equal(o_lo, oref[0]) and torch.equal(o_hi, oref[1])
         if k == 1:
             rc.embed(big[0], big[1], big[3], big[4], big[2], 70, p_lo=big[5], p_hi=big[6])
+
+
+@pytest.mark.parametrize("variant", ["rd_cell", "lin3_cell", "rd"])
+@pytest.mark.parametrize("n", [60, 500, 1000])
+@pytest.mark.parametrize("nsteps", [1, 20, 100])
+def test_results_over_inputs(rc, variant, n, nsteps):
+    """A chain that one window holds, its box into the arrays of its inputs, and
+    into arrays a few cells past the box's own: the same bits as into others."""
+    c = dev_case(variant, n, R.REACH_F64, 70 + n)
+    ref = rc.embed(c[0], c[1], c[3], c[4], c[2], nsteps, p_lo=c[5], p_hi=c[6])
+    assert rc.sync() == R.REACH_OK
+    say(f"results over inputs {variant} n={n} N={nsteps}")
+    # (a scalar input: the first cell of the result)
+    q_lo, q_hi = torch.zeros_like(c[3]), torch.zeros_like(c[4])
+    k = c[5].numel()
+    q_lo[:k], q_hi[:k] = c[5], c[6]
+    d = c[:5] + (q_lo[:k], q_hi[:k])
+    embed(rc, d, R.REACH_F64, nsteps, q_lo, q_hi)
+    assert rc.sync() == R.REACH_OK
+    assert torch.equal(q_lo, ref[0]) and torch.equal(q_hi, ref[1])
+    # the lower box shifted by 3 cells (each side's wave reads before it writes)
+    y = torch.zeros(n + 3, dtype=torch.float64, device="cuda")
+    y[:n] = c[3]
+    hi = torch.empty_like(c[4])
+    embed(rc, c[:3] + (y[:n],) + c[4:], R.REACH_F64, nsteps, y[3:], hi)
+    assert rc.sync() == R.REACH_OK
+    assert torch.equal(y[3:], ref[0]) and torch.equal(hi, ref[1])
