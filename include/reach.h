@@ -241,7 +241,8 @@ reach_status reach_sync(reach_ctx* ctx, void* stream);
  * (x_lo, x_hi) with inputs (p_lo, p_hi), and write the box (r_lo, r_hi).
  *   x_lo, x_hi  n elements, x_lo <= x_hi expected (not checked)
  *   p_lo, p_hi  n_in elements (NULL iff n_in == 0)
- *   r_lo, r_hi  n elements; may be the same arrays as x_lo, x_hi
+ *   r_lo, r_hi  n elements; may be the same arrays as x_lo, x_hi, and with
+ *               nsteps > 0 as x_hi, x_lo (crossed)
  *   workspace   device memory of reach_workspace_bytes(ctx, sys, dtype, 0)
  *               bytes (may be NULL when that is 0); must not overlap the
  *               other arrays; not shared with a call that may run meanwhile

@@ -30,8 +30,8 @@ namespace reach {
 // [W, 2W) the upper side.  PAIR (S = 1): a block of two waves, the lower and the
 // upper side of one window.  The call's last pass runs so: the upper wave hands
 // its box to the lower one through LDS, which compares them, where a separate
-// kernel would read both results again (1 GiB at 2^26 cells); so does a chain
-// that one window holds.
+// kernel would read both results again (1 GiB at 2^26 cells); every pass of a
+// single window runs so too.
 //
 // LIN3 runs as K_LIN3C or K_LIN3M: with the sign of each coupling known its
 // decomposition function has 4 nonzero terms of 7.  Exchanging the two sides of
@@ -93,6 +93,12 @@ void embed_tile_kernel(EmbedPass a) {
         } else {
             IO::load(U.u[s], p, ts, a.n, T(0), fast, false, my_lds);
         }
+    }
+    // A single window may write its results over its inputs, also one side's over
+    // the other's: both waves have read before either writes.  (Several windows
+    // never write what a pass reads.)
+    if constexpr (PAIR) {
+        if (a.W == 1) __syncthreads();
     }
     const SysPrm<T> P = make_prm<T>(a.prm);
     const Steps<T> st = {(T)a.h2, (T)a.dt, (T)a.dt6};

@@ -1262,8 +1262,9 @@ static reach_status embed_run(reach_ctx* c, const reach_system* s, reach_dtype d
         // caches' retention (non-temporal), 1.8% faster at 2^26 cells
         a.nt = a.ksteps == 1 ? 1 : 0;
         // one side per wave: the last pass has both sides of a window in one
-        // block, which checks the order
-        const bool pair = pl.S == 1 && a.check;
+        // block, which checks the order, and so has every pass of a single
+        // window, whose sides may write over each other's inputs
+        const bool pair = pl.S == 1 && (a.check || pl.W == 1);
         const int64_t tiles = pl.S == 1 && !pair ? 2 * pl.W : pl.W;
         a.per_xcd = (int32_t)((tiles + 7) / 8);
         const int64_t grid = 8 * (int64_t)a.per_xcd;

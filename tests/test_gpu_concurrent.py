@@ -140,3 +140,33 @@ def test_results_over_inputs(rc, variant, n, nsteps):
     embed(rc, c[:3] + (y[:n],) + c[4:], R.REACH_F64, nsteps, y[3:], hi)
     assert rc.sync() == R.REACH_OK
     assert torch.equal(y[3:], ref[0]) and torch.equal(hi, ref[1])
+
+
+@pytest.mark.parametrize("variant", ["ctm", "rd", "rd_cell", "lin3"])
+@pytest.mark.parametrize("n", [1, 64, 100, 128, 700, 1536, 5000])
+@pytest.mark.parametrize("nsteps", [1, 7, 45])
+@pytest.mark.parametrize("K", [0, 3])
+def test_crossed_results(rc, variant, n, nsteps, K):
+    """r_lo over x_hi and r_hi over x_lo, one of the two, and both sides from one
+    array that a result replaces: each side's wave reads the box first."""
+    c = dev_case(variant, n, R.REACH_F64, 90 + n)
+    ref = rc.embed(c[0], c[1], c[3], c[4], c[2], nsteps, p_lo=c[5], p_hi=c[6])
+    one = rc.embed(c[0], c[1], c[3], c[3], c[2], nsteps, p_lo=c[5], p_hi=c[6])
+    assert rc.sync() == R.REACH_OK
+    rc.set_option("embed.K", K)
+    ws = torch.empty(2 * n * 8, dtype=torch.uint8, device="cuda")
+    say(f"crossed {variant} n={n} N={nsteps} K={K}")
+    try:
+        for cross in ("both", "lo", "hi", "same"):
+            lo, hi = c[3].clone(), c[4].clone()
+            if cross == "same":
+                r_lo, r_hi, want, hi = lo, torch.empty_like(lo), one, lo
+            else:
+                r_lo = torch.empty_like(lo) if cross == "hi" else hi
+                r_hi = torch.empty_like(hi) if cross == "lo" else lo
+                want = ref
+            embed(rc, c[:3] + (lo, hi) + c[5:], R.REACH_F64, nsteps, r_lo, r_hi, ws)
+            assert rc.sync() == R.REACH_OK
+            assert torch.equal(r_lo, want[0]) and torch.equal(r_hi, want[1]), cross
+    finally:
+        rc.set_option("embed.K", 0)
