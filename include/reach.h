@@ -359,7 +359,9 @@ int64_t reach_mc_samples(int64_t n, double eps, double delta);
  * `q` is a HOST array of nq queries whose pointers are device pointers; it is
  * read during the call only.  workspace: reach_batch_workspace_bytes(nq)
  * bytes of device memory.  Results are identical to nq separate
- * reach_embed_rk4 calls.  The workspace holds two blocks of descriptors
+ * reach_embed_rk4 calls.  A query's results may replace its own inputs, also
+ * crossed (r_lo over x_hi or p_hi, r_hi over x_lo or p_lo): a batch with a
+ * crossed CTM or RD query runs packed, both sides of every pack in one wavefront.  The workspace holds two blocks of descriptors
  * and work items, used by turns.  The query descriptors are copied into this
  * call's block on the context's own copy stream as soon as the host has
  * written them, while it forms the work items, which follow; the upload waits
@@ -377,7 +379,8 @@ int64_t reach_mc_samples(int64_t n, double eps, double delta);
 size_t reach_batch_workspace_bytes(int64_t nq);
 
 /* The schedule reach_embed_rk4_batch launches for these queries, computed on
- * the host only (no device call; the query pointers are not dereferenced).
+ * the host only (no device call; the query pointers are not dereferenced, nor
+ * looked at for crossed results).
  * A batch with more queries than 16 per compute unit, or than twice option
  * "batch.waves" when that is set (option "batch.pack": 0 = that rule, 1 = always, 2 = never) is
  * packed: every work item is then a segment pack, queries of one kind with

@@ -354,6 +354,11 @@ reach_status chains_only(reach_ctx* c, const reach_system* s, const char* what) 
 
 void kernel_prm(const reach_system* s, double out[5]) { kernel_params(s->kind, s->prm, out); }
 
+// Whether [p, p + np) and [q, q + nq) share a byte (p may be NULL).
+bool overlaps(const void* p, size_t np, const void* q, size_t nq) {
+    return p && (const char*)p < (const char*)q + nq && (const char*)q < (const char*)p + np;
+}
+
 int ceil_pow2_E(int64_t n) {
     int E = 1;
     while ((int64_t)64 * E < n) E *= 2;
@@ -1165,11 +1170,6 @@ static bool capturing(hipStream_t s) {
     return true;
 }
 
-// Whether [p, p + np) and [q, q + nq) share a byte (p may be NULL).
-static bool overlaps(const void* p, size_t np, const void* q, size_t nq) {
-    return p && (const char*)p < (const char*)q + nq && (const char*)q < (const char*)p + np;
-}
-
 static reach_status embed_run(reach_ctx* c, const reach_system* s, reach_dtype dtype,
                               const void* x_lo, const void* x_hi, const void* p_lo,
                               const void* p_hi, double t0, double dt, int64_t nsteps, void* r_lo,
@@ -1795,6 +1795,16 @@ int seg_E(int64_t n, int cap) {
     return bestE ? bestE : above;
 }
 
+// Whether one side's result lies over what the other side reads.  A wave that
+// holds both sides reads both before it writes; waves of one side each do not
+// wait for each other.  (A LIN3 query always runs whole.)
+bool crossed(const QDesc& d) {
+    if (d.kind == REACH_LIN3) return false;
+    const size_t box = sizeof(double) * (size_t)d.n;
+    return overlaps(d.x_hi, box, d.r_lo, box) || overlaps(d.p_hi, sizeof(double), d.r_lo, box) ||
+           overlaps(d.x_lo, box, d.r_hi, box) || overlaps(d.p_lo, sizeof(double), d.r_hi, box);
+}
+
 // Whether a batch packs: option batch.pack 1 always, 2 never, 0 (default)
 // when it has more queries than 16 per compute unit, or than twice option
 // batch.waves (below that every query side gets a wave of its own and packing
@@ -1845,6 +1855,10 @@ int batch_ecap(const reach_ctx* c, int kind, int bucket) {
 // time (E * steps of the longest member; ceil(n / 64) * steps alone) at 1/16
 // octave, ties in unit order.  Packs of a batch too small for its longest query
 // are narrowed, and its longest items run one side per wave (see there).
+//
+// cross (may be NULL): set when some query is `crossed`, the plan then unfinished;
+// whole: the plan for such a batch, packed whatever its size and the options,
+// every pack's sides in one wave.
 struct PlanTimes {
     double pass1_ms = 0, pass_ms = 0, order_ms = 0, members_ms = 0;
 };
@@ -1853,7 +1867,8 @@ reach_status plan_batch(reach_ctx* c, HostPool* pool, const reach_query* q, int6
                         int split, int nth, QDesc* descs, std::vector<uint32_t>* members_out,
                         std::vector<BatchItem>* items_out, int* packed, int64_t* sides_out,
                         PlanTimes* times = nullptr,
-                        const std::function<void()>& descs_done = nullptr) {
+                        const std::function<void()>& descs_done = nullptr, bool whole = false,
+                        bool* cross = nullptr) {
     using clk = std::chrono::steady_clock;
     auto since = [](clk::time_point t0) {
         return std::chrono::duration<double, std::milli>(clk::now() - t0).count();
@@ -1892,7 +1907,7 @@ reach_status plan_batch(reach_ctx* c, HostPool* pool, const reach_query* q, int6
         int64_t max_steps = 0;
         uint32_t mem[kPackMax];
     };
-    const bool packs = !split && batch_packs(c, nq);
+    const bool packs = whole || (!split && batch_packs(c, nq));
     *packed = packs ? 1 : 0;
     int ecap[4][kNB];
     for (int k = 0; k < 4; ++k)
@@ -1921,6 +1936,7 @@ reach_status plan_batch(reach_ctx* c, HostPool* pool, const reach_query* q, int6
     std::vector<std::vector<Item>> titems((size_t)nu);
     std::vector<std::vector<uint32_t>> tmembers((size_t)nu);
     std::vector<int64_t> bad((size_t)nu, nq);
+    std::vector<uint8_t> crosses((size_t)nu, 0);
     // cells per lane of a packed query by cap (2, 4, 8, 16) and size
     int8_t etab[4][513];
     for (int ci = 0; ci < 4; ++ci)
@@ -1986,6 +2002,7 @@ reach_status plan_batch(reach_ctx* c, HostPool* pool, const reach_query* q, int6
         std::vector<Item> items;
         std::vector<uint32_t> members;
         int64_t my_bad = nq;
+        bool my_cross = false;
         std::vector<Consts> classes;
         std::vector<QRef> mine;
         for (int64_t i = lo; i < hi; ++i) {
@@ -1994,6 +2011,7 @@ reach_status plan_batch(reach_ctx* c, HostPool* pool, const reach_query* q, int6
                 my_bad = std::min(my_bad, i);
                 continue;
             }
+            if (cross) my_cross |= crossed(d);
             if (!packs) {
                 push_alone(items, members, (uint32_t)i);
                 continue;
@@ -2044,11 +2062,16 @@ reach_status plan_batch(reach_ctx* c, HostPool* pool, const reach_query* q, int6
         tmembers[(size_t)t] = std::move(members);
         tclasses[(size_t)t] = std::move(classes);
         bad[(size_t)t] = my_bad;
+        crosses[(size_t)t] = my_cross ? 1 : 0;
     });
     const int64_t first_bad = *std::min_element(bad.begin(), bad.end());
     if (first_bad < nq) {
         QDesc tmp;
         return make_desc(c, q[first_bad], first_bad, &tmp);
+    }
+    if (cross) {
+        *cross = std::find(crosses.begin(), crosses.end(), 1) != crosses.end();
+        if (*cross) return REACH_OK;
     }
     // every descriptor is written: the caller may start moving them while
     // the items are formed
@@ -2225,7 +2248,7 @@ reach_status plan_batch(reach_ctx* c, HostPool* pool, const reach_query* q, int6
         }
     // items longer than the load come first: those of the buckets before its own
     *sides_out = 0;
-    if (packs) {
+    if (packs && !whole) {
         const int lb = wave_time_bucket(load);
         // (the counts are item indices now: that of unit 0 in the load's bucket is
         // the number of items in the buckets before)
@@ -2359,10 +2382,15 @@ reach_status reach_embed_rk4_batch(reach_ctx* c, const reach_query* q, int64_t n
     // the work items
     hipError_t desc_err = hipSuccess;
     const size_t desc_bytes = sizeof(QDesc) * (size_t)nq;
-    reach_status pst = plan_batch(c, pool, q, nq, split, nth, hb.desc, &members, &items, &packed,
-                                  &sides, &pt, [&] {
+    const auto upload = [&] {
         desc_err = hipMemcpyAsync(db.desc, hb.desc, desc_bytes, hipMemcpyHostToDevice, cs);
-    });
+    };
+    bool cross = false;
+    reach_status pst = plan_batch(c, pool, q, nq, split, nth, hb.desc, &members, &items, &packed,
+                                  &sides, &pt, upload, false, &cross);
+    if (pst == REACH_OK && cross)
+        pst = plan_batch(c, pool, q, nq, split, nth, hb.desc, &members, &items, &packed, &sides,
+                         &pt, upload, true);
     if (pst != REACH_OK) return pst;
     if (desc_err != hipSuccess) return hip_fail(c, desc_err, "descriptor upload");
     const int64_t ni = (int64_t)items.size();

@@ -170,3 +170,53 @@ def test_crossed_results(rc, variant, n, nsteps, K):
             assert torch.equal(r_lo, want[0]) and torch.equal(r_hi, want[1]), cross
     finally:
         rc.set_option("embed.K", 0)
+
+
+@pytest.mark.parametrize("pack", [0, 1, 2])
+@pytest.mark.parametrize("split", [0, 1])
+@pytest.mark.parametrize("nq", [3, 80, 4300])
+def test_batch_crossed_results(rc, pack, split, nq):
+    """Batches in which some queries' results replace the other side's box or
+    input, run packed or not: the boxes of the same queries with results of
+    their own.  4300 queries pack by default, the longest one side per wave."""
+    qs, refs, keep = [], [], []
+    for k in range(nq):
+        variant = ("ctm", "rd", "lin3")[k % 3]
+        n, nsteps = 5 + (37 * k) % 200, 1000 if k % 40 == 1 else 8 + k % 30
+        c = dev_case(variant, n, R.REACH_F64, 300 + k % 17)
+        kind, prm, dt, lo, hi, pl, ph = c
+        n_in = 0 if pl is None else 1
+        own = [torch.empty_like(lo), torch.empty_like(hi)]
+        refs.append((kind, n, prm, lo, hi, own, dt, nsteps, pl, ph, n_in))
+        x_lo, x_hi = lo.clone(), hi.clone()
+        r_lo, r_hi = torch.empty_like(lo), torch.empty_like(hi)
+        how = k % 5
+        if how == 0:
+            r_lo, r_hi = x_hi, x_lo
+        elif how == 1:
+            r_lo = x_hi
+        elif how == 2 and n_in:            # the results over the other side's input
+            r_lo[:1], r_hi[:1] = ph, pl
+            pl, ph = r_hi[:1], r_lo[:1]
+        elif how == 3:
+            r_lo, r_hi = x_lo, x_hi
+        qs.append((kind, n, prm, x_lo, x_hi, r_lo, r_hi, dt, nsteps, pl, ph, n_in))
+    make = lambda q, r_lo, r_hi: R.make_query(q[0], q[1], q[2], R.REACH_F64, q[3], q[4], r_lo, r_hi,
+                                              q[-5], q[-4], q[-3], q[-2], n_in=q[-1])
+    a = R.query_array([make(q, *q[5]) for q in refs])
+    b = R.query_array([make(q, q[5], q[6]) for q in qs])
+    nb = R.reach_batch_workspace_bytes(nq)
+    ws = torch.empty(nb, dtype=torch.uint8, device="cuda")
+    say(f"batch crossed nq={nq} pack={pack} split={split}")
+    R.reach_embed_rk4_each(rc.ctx, a)
+    assert rc.sync() == R.REACH_OK
+    try:
+        rc.set_option("batch.pack", pack)
+        rc.set_option("batch.split", split)
+        R.reach_embed_rk4_batch(rc.ctx, b, ws, nb)
+        assert rc.sync() == R.REACH_OK
+    finally:
+        rc.set_option("batch.pack", 0)
+        rc.set_option("batch.split", 0)
+    for k, (q, ref) in enumerate(zip(qs, refs)):
+        assert torch.equal(q[5], ref[5][0]) and torch.equal(q[6], ref[5][1]), k
