@@ -536,9 +536,10 @@ reach_status plan_embed(reach_ctx* c, const reach_system* s, reach_dtype dtype, 
     const bool cell_in = s->n_in > 1;
     const int64_t oE = opt_get(c, "embed.E"), oK = opt_get(c, "embed.K"), oS = opt_get(c, "embed.S");
     const int64_t simds = (int64_t)4 * c->cus;
+    const bool is_tuned =
+        !c->tune.empty() && c->tune.count({s->kind, dtype, n_bucket(n), cell_in ? 1 : 0}) != 0;
     // (up to two cells per lane one window is always the better one)
-    if ((have_ws || cut_one) && n > 128 && !oE && !oK && !oS &&
-        (c->tune.empty() || !c->tune.count({s->kind, dtype, n_bucket(n), cell_in ? 1 : 0})) &&
+    if ((have_ws || cut_one) && n > 128 && !oE && !oK && !oS && !is_tuned &&
         estimated(s->kind, dtype, cell_in, n, simds)) {
         const int one = smallest_E(s->kind, dtype, s->kind == REACH_LIN3 ? 2 : 1, n);
         if (one ? cut_one && nsteps > (s->kind == REACH_LIN3 ? 1 : one_steps) : have_ws) {
@@ -594,6 +595,11 @@ reach_status plan_embed(reach_ctx* c, const reach_system* s, reach_dtype dtype, 
     }
     int K = oK ? (int)oK : te.K;
     if (K < 1) K = 1;
+    // (per-cell LIN3 inputs: runs of more steps than the default pass that need
+    // no workspace)
+    if (!oK && !is_tuned && nsteps > K &&
+        nsteps <= one_pass_steps(s->kind, dtype, cell_in, n) && 8 * nsteps < span)
+        K = (int)nsteps;
     if ((int64_t)8 * K >= span) return fail(c, REACH_E_INVAL, "K = %d too large for E = %d", K, E);
     if (!oK && nsteps > 0) {
         // the same number of passes with the steps spread evenly: a smaller

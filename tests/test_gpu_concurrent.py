@@ -220,3 +220,16 @@ def test_batch_crossed_results(rc, pack, split, nq):
         rc.set_option("batch.split", 0)
     for k, (q, ref) in enumerate(zip(qs, refs)):
         assert torch.equal(q[5], ref[5][0]) and torch.equal(q[6], ref[5][1]), k
+
+
+@pytest.mark.parametrize("variant", ["lin3", "lin3_cell"])
+@pytest.mark.parametrize("n", [1025, 5000])
+@pytest.mark.parametrize("nsteps", [1, 10, 11, 12])
+def test_lin3_runs_of_one_pass_need_no_workspace(rc, variant, n, nsteps):
+    c = dev_case(variant, n, R.REACH_F64, 7)
+    ref = rc.embed(c[0], c[1], c[3], c[4], c[2], nsteps, p_lo=c[5], p_hi=c[6])
+    lo, hi = torch.empty_like(c[3]), torch.empty_like(c[4])
+    say(f"no workspace {variant} n={n} N={nsteps}")
+    embed(rc, c, R.REACH_F64, nsteps, lo, hi)
+    assert rc.sync() == R.REACH_OK
+    assert torch.equal(lo, ref[0]) and torch.equal(hi, ref[1])
