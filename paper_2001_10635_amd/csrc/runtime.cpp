@@ -431,6 +431,16 @@ void set_windows(EmbedPlan* p, int E, int S, int64_t K, int64_t n, int64_t nstep
     p->passes = (nsteps + K - 1) / K;
 }
 
+// Issue time of one cell and RK4 step (both sides for S = 2) of a lane of E cells.
+double cell_us(int kind, int dtype, bool cell_in, int S, int E, bool* over) {
+    const bool f64 = dtype == REACH_F64;
+    const int wide = S == 2 ? (f64 ? (cell_in ? 8 : 12) : 16)
+                            : (f64 ? (cell_in ? 24 : 28) : 48);
+    *over = E > wide;
+    const double c = kind == REACH_LIN3 ? 0.0765 : kind == REACH_RD ? 0.0438 : f64 ? 0.051 : 0.040;
+    return *over ? c * (S == 2 ? 2.0 : 1.2) : c;   // register moves
+}
+
 // Estimated time of one RK4 step (microseconds) of a chain whose windows do not
 // fill the chip several times over, at E cells per lane and K steps per pass
 // (measured on MI355X, chains of 12000 to 10^6 cells):
@@ -449,13 +459,10 @@ double step_us(int kind, int dtype, bool cell_in, int S, int E, int64_t K, int64
     const int64_t OUT = span - 8 * K;
     const int64_t W = n <= span ? 1 : 1 + (n - span + OUT - 1) / OUT;
     const int64_t r = ((S == 1 ? 2 : 1) * W + simds - 1) / simds;
-    const bool f64 = dtype == REACH_F64;
-    const int wide = S == 2 ? (f64 ? (cell_in ? 8 : 12) : 16)
-                            : (f64 ? (cell_in ? 24 : 28) : 48);
-    if (E > wide && r > 1) return 1e300;
-    double c = kind == REACH_LIN3 ? 0.0765 : kind == REACH_RD ? 0.0438 : f64 ? 0.051 : 0.040;
-    if (E > wide) c *= S == 2 ? 2.0 : 1.2;   // register moves
-    const double bytes = (double)n * (f64 ? 8.0 : 4.0) * (cell_in ? 6.0 : 4.0);
+    bool over = false;
+    const double c = cell_us(kind, dtype, cell_in, S, E, &over);
+    if (over && r > 1) return 1e300;
+    const double bytes = (double)n * (dtype == REACH_F64 ? 8.0 : 4.0) * (cell_in ? 6.0 : 4.0);
     return (double)r * c * E + 0.06 + (2.5 + bytes / 7.0e6) / (double)K;
 }
 
@@ -500,6 +507,32 @@ TuneEntry fastest_shape(reach_ctx* c, int kind, int dtype, bool cell_in, int64_t
     return best;
 }
 
+// Estimated time of a run in the one window of E cells a lane that holds the chain.
+// Padding costs the LIN3 chain's selects a third (at 16 cells a lane its moves are
+// fewer than cell_us says), the others a few percent (measured, us a step, FP64 RD:
+// 4 cells 0.254, 8 0.454, 12 0.581, 16 0.746, 32 1.80; FP64 CTM: 4 0.276, 8 0.515; FP32
+// CTM: 4 0.202, 16 0.693, 32 1.31, 64 3.62; FP64 LIN3: 4 0.500, 8 0.912, 12 1.33, 16 1.75).
+double one_window_us(int kind, int dtype, bool cell_in, int S, int E, int64_t n, int64_t nsteps) {
+    bool over = false;
+    const double step = cell_us(kind, dtype, cell_in, S, E, &over) * E + 0.06;
+    const double pad = n == (int64_t)64 * E ? 1.0 : S == 2 ? (over ? 0.7 : 1.36) : 1.05;
+    return 2.5 + (double)nsteps * step * pad;
+}
+
+// Whether a chain that one window holds is cut into several, whose run is estimated
+// to take many_us (hold: in CutScratch, whose event takes 3 us of a call).  A call
+// alone gains wherever that is less, but one window leaves the chip to other
+// streams' calls, of which four run at once, while a cut chain's passes are launches
+// of about 3 us for the host: with 8 streams a call of 100 steps takes, in one
+// window and cut, 30 and 18 us at 1000 RD cells (79 and 31 alone), 24 and 24 at 700
+// (62 and 28), and 11 and 19 at 130 (28 and 30).  So it has to gain more than half
+// as much again alone, and its passes have to keep up with four windows at a time.
+bool cut_pays(double one_us, double many_us, int64_t passes, bool hold) {
+    if (hold) many_us += 3.0;
+    return 1.6 * many_us <= one_us &&
+           (passes == 1 || one_us >= 7.0 * (double)passes + (hold ? 5.0 : 0.0));
+}
+
 // The estimate decides on chains whose default windows put at most 8 waves on a
 // SIMD; longer ones keep the shapes measured at 2^26 and 2^31 cells (there the
 // rounds run into each other and the last one weighs little).
@@ -510,7 +543,7 @@ bool estimated(int kind, int dtype, bool cell_in, int64_t n, int64_t simds) {
 }
 
 // Runs of at most this many steps keep a chain that one window holds in one
-// window (no workspace, one launch): splitting it would save a few microseconds.
+// window (one launch): splitting it would save a few microseconds.
 // A tube of many short runs does split it, and so does the LIN3 chain, whose wave
 // holds both sides (n = 1000, 8 steps: 23 us in one window, 16 in several).
 constexpr int64_t kSplitSteps = 8;
@@ -550,20 +583,11 @@ reach_status plan_embed(reach_ctx* c, const reach_system* s, reach_dtype dtype, 
             const int64_t passes = (steps + t.K - 1) / t.K;
             const int64_t K = (steps + passes - 1) / passes;
             const TuneEntry u = fastest_shape(c, s->kind, dtype, cell_in, n, K);
-            // one window: the launch once, padding selects (a third more
-            // instructions) unless the chain fills it.  Several windows pay a
-            // launch per pass, about 3 us on the host beside the call's own 9
-            // through the Python binding (a tube's slots are one call).
-            const double host_us = one_steps < kSplitSteps ? 0.0 : 9.0;
-            const double c1 = step_us(s->kind, dtype, cell_in, t.S, one ? one : 1, 1, 1, simds);
-            const double one_us =
-                one ? std::max(host_us + 3.0, 2.5 + (double)steps * (c1 - 2.5) *
-                                                        (n == (int64_t)64 * one ? 1.0 : 1.33))
-                    : 1e300;
             const double many_us =
-                std::max(host_us + 3.0 * (double)passes,
-                         (double)steps * step_us(s->kind, dtype, cell_in, t.S, u.E, K, n, simds));
-            if (u.E && many_us < one_us) {
+                (double)steps * step_us(s->kind, dtype, cell_in, t.S, u.E, K, n, simds);
+            // (a tube's slots share one hold on the scratch)
+            if (u.E && (!one || cut_pays(one_window_us(s->kind, dtype, cell_in, t.S, one, n, steps),
+                                         many_us, passes, passes > 1 && one_steps == kSplitSteps))) {
                 set_windows(p, u.E, u.S, K, n, nsteps);
                 p->cut_one = one != 0;
                 if (p->W > 1) return REACH_OK;
@@ -1180,7 +1204,7 @@ static reach_status embed_run(reach_ctx* c, const reach_system* s, reach_dtype d
                               const void* x_lo, const void* x_hi, const void* p_lo,
                               const void* p_hi, double t0, double dt, int64_t nsteps, void* r_lo,
                               void* r_hi, void* ws, size_t ws_bytes, void* stream,
-                              int64_t one_steps) {
+                              int64_t one_steps, CutRun* cut) {
     if (!c) return REACH_E_INVAL;
     reach_status st = check_system(c, s, dtype);
     if (st != REACH_OK) return st;
@@ -1215,14 +1239,13 @@ static reach_status embed_run(reach_ctx* c, const reach_system* s, reach_dtype d
     if (st != REACH_OK) return st;
     // a cut chain that one window holds runs its passes in the context's scratch,
     // which a captured call (replayed at any time, beside anything) does not use
-    CutRun cut;
     if (pl.cut_one && (pl.passes >= 2 || alias)) {
         if (2 * bytes > CutScratch::kSlotBytes || capturing(hs)) {
             st = plan_embed(c, s, dtype, nsteps, &pl, have_ws, false, one_steps);
             if (st != REACH_OK) return st;
         } else {
-            HIPCHK(c, cut.begin(c->cut, hs));
-            ws = cut.mem;
+            if (!cut->slot) HIPCHK(c, cut->begin(c->cut, hs));
+            ws = cut->mem;
             ws_bytes = CutScratch::kSlotBytes;
         }
     }
@@ -1290,8 +1313,9 @@ reach_status reach_embed_rk4(reach_ctx* c, const reach_system* s, reach_dtype dt
                              const void* x_lo, const void* x_hi, const void* p_lo,
                              const void* p_hi, double t0, double dt, int64_t nsteps, void* r_lo,
                              void* r_hi, void* ws, size_t ws_bytes, void* stream) {
+    CutRun cut;
     return embed_run(c, s, dtype, x_lo, x_hi, p_lo, p_hi, t0, dt, nsteps, r_lo, r_hi, ws, ws_bytes,
-                     stream, kSplitSteps);
+                     stream, kSplitSteps, &cut);
 }
 
 reach_status reach_embed_rk4_tube(reach_ctx* c, const reach_system* s, reach_dtype dtype,
@@ -1309,13 +1333,14 @@ reach_status reach_embed_rk4_tube(reach_ctx* c, const reach_system* s, reach_dty
     const int64_t slots = nsteps / every;
     const void* src_lo = x_lo;
     const void* src_hi = x_hi;
+    CutRun cut;
     for (int64_t k = 0; k < slots; ++k) {
         void* dlo = (char*)tube_lo + (size_t)k * bytes;
         void* dhi = (char*)tube_hi + (size_t)k * bytes;
         // each slot continues from the previous one: resumed runs are bitwise
         // the same as one run
         st = embed_run(c, s, dtype, src_lo, src_hi, p_lo, p_hi, t0 + (double)(k * every) * dt, dt,
-                       every, dlo, dhi, ws, ws_bytes, stream, slots > 1 ? 1 : kSplitSteps);
+                       every, dlo, dhi, ws, ws_bytes, stream, slots > 1 ? 1 : kSplitSteps, &cut);
         if (st != REACH_OK) return st;
         src_lo = dlo;
         src_hi = dhi;
@@ -1576,8 +1601,12 @@ reach_status reach_growth_bound(reach_ctx* c, const reach_system* s, reach_dtype
             const int64_t passes = (nsteps + t.K - 1) / t.K;
             t.K = (int)((nsteps + passes - 1) / passes);
             t = fastest_shape(c, like, dtype, cell_in, n, t.K, true);
-            if ((int64_t)64 * t.E >= n) t.E = 0;   // one window: no passes at all
-            else if (one && nsteps <= kSplitSteps) t.E = 0;
+            // one window: no passes at all
+            if (one && (nsteps <= kSplitSteps || (int64_t)64 * t.E >= n ||
+                        !cut_pays(one_window_us(like, dtype, cell_in, 1, one, n, nsteps),
+                                  (double)nsteps * step_us(like, dtype, cell_in, 1, t.E, t.K, n, simds),
+                                  passes, false)))
+                t.E = 0;
         }
         if (t.E) {
             E = t.E;

@@ -233,3 +233,14 @@ def test_lin3_runs_of_one_pass_need_no_workspace(rc, variant, n, nsteps):
     embed(rc, c, R.REACH_F64, nsteps, lo, hi)
     assert rc.sync() == R.REACH_OK
     assert torch.equal(lo, ref[0]) and torch.equal(hi, ref[1])
+
+
+@pytest.mark.parametrize("kind,prm,n,dtc,cut", [
+    (R.REACH_RD, (1.0,), 130, R.REACH_F64, False), (R.REACH_RD, (1.0,), 384, R.REACH_F64, False),
+    (R.REACH_RD, (1.0,), 1000, R.REACH_F64, True), (R.REACH_LIN3, (-0.5, -1.0, 0.75, -1.5), 130,
+                                                    R.REACH_F64, False),
+    (R.REACH_CTM, (0.5, 1 / 6, 40.0, 20.0), 4096, R.REACH_F32, True)])
+def test_short_chains_stay_in_one_window_unless_it_pays(rc, kind, prm, n, dtc, cut):
+    """100 steps: cut only where eight streams at once do not lose by it."""
+    plan = R.reach_plan_embed(rc.ctx, R.make_system(kind, n, prm, 0), dtc, 100)
+    assert (plan["tiles"] > 1) == cut and (plan["passes"] > 1) == cut
