@@ -721,27 +721,21 @@ reach_status plan_heat(reach_ctx* c, const reach_system* s, reach_dtype dtype, H
 
 // Which buffer each of `passes` passes reads and writes: 0 = x, 1 = r,
 // 2 = workspace.  The last pass writes r unless r aliases x and the pass
-// count makes the ping-pong end in the workspace (then final_copy).
-void plan_io(int64_t passes, bool inplace_ok, bool alias, std::vector<std::pair<int, int>>* io,
-             bool* final_copy) {
-    std::vector<int> dst(passes);
-    *final_copy = false;
-    if (inplace_ok) {
-        for (auto& d : dst) d = 1;
-    } else {
-        for (int64_t p = passes - 1, k = 0; p >= 0; --p, ++k) dst[p] = (k % 2 == 0) ? 1 : 2;
-        if (alias && dst[0] == 1) {
-            for (int64_t p = 0; p < passes; ++p) dst[p] = (p % 2 == 0) ? 2 : 1;
-            *final_copy = (dst[passes - 1] == 2);
-        }
+// count makes the ping-pong end in the workspace (then final_copy).  Computed per
+// pass: a long run of a short chain has millions of them.
+struct PassIo {
+    int64_t passes;
+    bool inplace;      // every pass reads and writes r (the first reads x)
+    bool ws_first;     // the ping-pong starts in the workspace
+    PassIo(int64_t n, bool inplace_ok, bool alias)
+        : passes(n), inplace(inplace_ok), ws_first(!inplace_ok && alias && n % 2 == 1) {}
+    int dst(int64_t p) const {
+        if (inplace) return 1;
+        return (ws_first ? p % 2 == 1 : (passes - 1 - p) % 2 == 0) ? 1 : 2;
     }
-    int src = 0;
-    io->clear();
-    for (int64_t p = 0; p < passes; ++p) {
-        io->push_back({src, dst[p]});
-        src = dst[p];
-    }
-}
+    int src(int64_t p) const { return p ? dst(p - 1) : 0; }
+    bool final_copy() const { return passes > 0 && dst(passes - 1) == 2; }
+};
 
 reach_status embed_heat3d(reach_ctx* c, const reach_system* s, reach_dtype dtype,
                           const void* x_lo, const void* x_hi, double dt, int64_t nsteps,
@@ -764,9 +758,7 @@ reach_status embed_heat3d(reach_ctx* c, const reach_system* s, reach_dtype dtype
         w_lo = ws;
         w_hi = (char*)ws + bytes;
     }
-    std::vector<std::pair<int, int>> io;
-    bool final_copy = false;
-    plan_io(passes, false, alias, &io, &final_copy);
+    const PassIo io(passes, false, alias);
     const void* lo_of[3] = {x_lo, r_lo, w_lo};
     const void* hi_of[3] = {x_hi, r_hi, w_hi};
     HeatPass a{};
@@ -783,17 +775,17 @@ reach_status embed_heat3d(reach_ctx* c, const reach_system* s, reach_dtype dtype
     const int64_t grid = 8 * (int64_t)a.per_xcd;
     const int dt_id = dtype == REACH_F64 ? 0 : 1;
     for (int64_t p = 0; p < passes; ++p) {
-        a.src[0] = lo_of[io[p].first];
-        a.src[1] = hi_of[io[p].first];
-        a.dst[0] = (void*)lo_of[io[p].second];
-        a.dst[1] = (void*)hi_of[io[p].second];
+        a.src[0] = lo_of[io.src(p)];
+        a.src[1] = hi_of[io.src(p)];
+        a.dst[0] = (void*)lo_of[io.dst(p)];
+        a.dst[1] = (void*)hi_of[io.dst(p)];
         hipError_t e = launch_heat3d(dt_id, hp.P, hp.WV, a, grid, hs);
         if (e != hipSuccess) return hip_fail(c, e, "3-D heat kernel launch");
     }
-    hipError_t e = launch_order_check(dt_id, lo_of[io.back().second], hi_of[io.back().second],
+    hipError_t e = launch_order_check(dt_id, lo_of[io.dst(passes - 1)], hi_of[io.dst(passes - 1)],
                                       s->n, c->status, hs);
     if (e != hipSuccess) return hip_fail(c, e, "order check launch");
-    if (final_copy) {
+    if (io.final_copy()) {
         HIPCHK(c, hipMemcpyAsync(r_lo, w_lo, bytes, hipMemcpyDeviceToDevice, hs));
         HIPCHK(c, hipMemcpyAsync(r_hi, w_hi, bytes, hipMemcpyDeviceToDevice, hs));
     }
@@ -1265,9 +1257,7 @@ static reach_status embed_run(reach_ctx* c, const reach_system* s, reach_dtype d
         w_lo = ws;
         w_hi = (char*)ws + bytes;
     }
-    bool final_copy = false;
-    std::vector<std::pair<int, int>> io;  // per pass: (src id, dst id); 0 = x, 1 = r, 2 = ws
-    plan_io(pl.passes, inplace_ok, alias, &io, &final_copy);
+    const PassIo io(pl.passes, inplace_ok, alias);
     const void* lo_of[3] = {x_lo, r_lo, w_lo};
     const void* hi_of[3] = {x_hi, r_hi, w_hi};
 
@@ -1281,10 +1271,10 @@ static reach_status embed_run(reach_ctx* c, const reach_system* s, reach_dtype d
     if (s->n_in == 0) { a.p_lo = nullptr; a.p_hi = nullptr; }
     int64_t done = 0;
     for (int64_t p = 0; p < pl.passes; ++p) {
-        a.src_lo = lo_of[io[p].first];
-        a.src_hi = hi_of[io[p].first];
-        a.dst_lo = (void*)lo_of[io[p].second];
-        a.dst_hi = (void*)hi_of[io[p].second];
+        a.src_lo = lo_of[io.src(p)];
+        a.src_hi = hi_of[io.src(p)];
+        a.dst_lo = (void*)lo_of[io.dst(p)];
+        a.dst_hi = (void*)hi_of[io.dst(p)];
         a.ksteps = std::min<int64_t>(pl.K, nsteps - done);
         a.check = (p == pl.passes - 1) ? 1 : 0;
         // a one-step pass is a pure stream: its reads and writes bypass the
@@ -1302,7 +1292,7 @@ static reach_status embed_run(reach_ctx* c, const reach_system* s, reach_dtype d
         if (e != hipSuccess) return hip_fail(c, e, "embedding kernel launch");
         done += a.ksteps;
     }
-    if (final_copy) {
+    if (io.final_copy()) {
         HIPCHK(c, hipMemcpyAsync(r_lo, w_lo, bytes, hipMemcpyDeviceToDevice, hs));
         HIPCHK(c, hipMemcpyAsync(r_hi, w_hi, bytes, hipMemcpyDeviceToDevice, hs));
     }
@@ -2687,7 +2677,10 @@ reach_status validate_user(reach_ctx* c, const reach_system* s, reach_dtype dtyp
 }
 void pass_buffers(int64_t passes, bool inplace_ok, bool alias,
                   std::vector<std::pair<int, int>>* io, bool* final_copy) {
-    plan_io(passes, inplace_ok, alias, io, final_copy);
+    const PassIo b(passes, inplace_ok, alias);
+    io->clear();
+    for (int64_t p = 0; p < passes; ++p) io->push_back({b.src(p), b.dst(p)});
+    *final_copy = b.final_copy();
 }
 
 }  // namespace rt
