@@ -207,7 +207,9 @@ reach_status reach_plan_embed(reach_ctx* ctx, const reach_system* sys, reach_dty
    re-times the four fastest and the built-in default over ten times the
    steps (three rounds, each shape once per round), and records the fastest
    (the default unless a shape beats it by more than 2%) for this system kind, dtype and power-of-two size bucket of
-   n in the context; later calls of that bucket use it.  Arguments
+   n in the context; later calls of that bucket use it, except of chains that one
+   window of the kernel holds.  Where the default wins, later calls go on choosing
+   theirs by n.  Arguments
    are those of reach_embed_rk4 (r_lo / r_hi receive scratch results).
    best[0] = E, best[1] = K, best[2] = femtoseconds per state-step (2n per
    step), best[3] = S (sides per wavefront).  `best` is a host array of 4.

@@ -569,13 +569,15 @@ reach_status plan_embed(reach_ctx* c, const reach_system* s, reach_dtype dtype, 
     const bool cell_in = s->n_in > 1;
     const int64_t oE = opt_get(c, "embed.E"), oK = opt_get(c, "embed.K"), oS = opt_get(c, "embed.S");
     const int64_t simds = (int64_t)4 * c->cus;
+    // (a tuned shape is for the chains of its bucket that no single window holds)
     const bool is_tuned =
         !c->tune.empty() && c->tune.count({s->kind, dtype, n_bucket(n), cell_in ? 1 : 0}) != 0;
     // (up to two cells per lane one window is always the better one)
-    if ((have_ws || cut_one) && n > 128 && !oE && !oK && !oS && !is_tuned &&
+    if ((have_ws || cut_one) && n > 128 && !oE && !oK && !oS &&
         estimated(s->kind, dtype, cell_in, n, simds)) {
         const int one = smallest_E(s->kind, dtype, s->kind == REACH_LIN3 ? 2 : 1, n);
-        if (one ? cut_one && nsteps > (s->kind == REACH_LIN3 ? 1 : one_steps) : have_ws) {
+        if (one ? cut_one && nsteps > (s->kind == REACH_LIN3 ? 1 : one_steps)
+                : have_ws && !is_tuned) {
             // the best K for many steps gives the pass count; the steps are
             // spread evenly over the passes, and the shape is the best for those
             const TuneEntry t = fastest_shape(c, s->kind, dtype, cell_in, n, 0);
@@ -980,6 +982,7 @@ McPlan mc_plan(const reach_ctx* c, int kind, int dtype, bool cell_in, int64_t n,
 
 // Autotune cache: one line per entry, each tagged with the format "reach2":
 //   reach2 embed <arch> <kind> <dtype> <log2 n bucket> <per-cell inputs 0/1> <E> <K> <S> <ps per state-step>
+//     (E = 0: the default shape, which takes back an earlier line of the bucket)
 //   reach2 batch <arch> <kind> <log2 n bucket> <pack E cap> <ns per batch>
 // Lines of any other form (an older format without the input mode among
 // them) are ignored.
@@ -997,7 +1000,9 @@ void load_tune_cache(reach_ctx* c) {
                         &bucket, &cell, &E, &K, &S, &ps) == 9) {
             const bool heat_ok = kind == REACH_HEAT3D && heat_waves(E) &&
                                  heat_has_shape(dtype == REACH_F64 ? 0 : 1, E, heat_waves(E));
-            if (c->arch == arch && (cell == 0 || cell == 1) &&
+            if (c->arch == arch && E == 0)
+                c->tune.erase({kind, dtype, bucket, cell});
+            else if (c->arch == arch && (cell == 0 || cell == 1) &&
                 (heat_ok || (embed_has_shape(kind, dtype, E, S) && K >= 1 && 8 * K < 64 * E)))
                 c->tune[{kind, dtype, bucket, cell}] = TuneEntry{E, K, S};
         } else if (std::sscanf(line, "reach2 batch %63s %d %d %d %lf", arch, &kind, &bucket, &cap,
@@ -1400,6 +1405,7 @@ reach_status reach_autotune_embed(reach_ctx* c, const reach_system* s, reach_dty
     }
     double best_ps = 1e300;
     TuneEntry bt{0, 0, 0};
+    bool default_won = false;
     if (st == REACH_OK && !scan.empty()) {
         std::stable_sort(scan.begin(), scan.end(),
                          [](const auto& a, const auto& b) { return a.first < b.first; });
@@ -1408,12 +1414,9 @@ reach_status reach_autotune_embed(reach_ctx* c, const reach_system* s, reach_dty
         const TuneEntry d = default_shape(c, s->kind, dtype, s->n_in > 1, s->n);
         bool have_d = false;
         for (const auto& f : finals) have_d |= (f.E == d.E && f.K == d.K && f.S == d.S);
-        // (a default of a K between the scanned ones is timed with the finals)
-        for (const auto& q : scan)
-            if (!have_d && q.second.E == d.E && q.second.S == d.S && 8 * d.K < 64 * d.E) {
-                finals.push_back(d);
-                have_d = true;
-            }
+        // (a default of a width or a K that the scan leaves out is timed with the finals)
+        if (!have_d && embed_has_shape(s->kind, dtype, d.E, d.S) && 8 * d.K < 64 * d.E)
+            finals.push_back(d);
         // the finals in three rounds, each shape once per round (a warm-up and
         // two timed calls), so that a drift of the clock over the trials
         // favours none of them; the measured default stays unless a shape
@@ -1436,6 +1439,7 @@ reach_status reach_autotune_embed(reach_ctx* c, const reach_system* s, reach_dty
         if (st == REACH_OK && d_ps <= best_ps * (1.0 + kKeepDefault)) {
             best_ps = d_ps;
             bt = d;
+            default_won = true;
         }
     }
     hipEventDestroy(e0);
@@ -1447,8 +1451,12 @@ reach_status reach_autotune_embed(reach_ctx* c, const reach_system* s, reach_dty
     if (bt.E == 0) return fail(c, REACH_E_UNSUPPORTED, "n too small to tile: nothing to tune");
     const int bucket = n_bucket(s->n);
     const int cell_in = s->n_in > 1 ? 1 : 0;
-    c->tune[{s->kind, dtype, bucket, cell_in}] = bt;
-    save_tune_entry(c, s->kind, dtype, bucket, cell_in, bt, best_ps);
+    // (where the default wins nothing is recorded for the rest of the bucket, whose
+    // default may be another; the line written takes back an earlier one)
+    if (default_won) c->tune.erase({s->kind, dtype, bucket, cell_in});
+    else c->tune[{s->kind, dtype, bucket, cell_in}] = bt;
+    save_tune_entry(c, s->kind, dtype, bucket, cell_in, default_won ? TuneEntry{0, 0, 0} : bt,
+                    best_ps);
     best[0] = bt.E;
     best[1] = bt.K;
     best[2] = (int64_t)std::llround(best_ps * 1000.0);

@@ -244,3 +244,47 @@ def test_short_chains_stay_in_one_window_unless_it_pays(rc, kind, prm, n, dtc, c
     """100 steps: cut only where eight streams at once do not lose by it."""
     plan = R.reach_plan_embed(rc.ctx, R.make_system(kind, n, prm, 0), dtc, 100)
     assert (plan["tiles"] > 1) == cut and (plan["passes"] > 1) == cut
+
+
+@pytest.mark.parametrize("n", [100003, 500001])
+def test_autotuner_keeps_a_default_it_has_not_beaten(tmp_path, monkeypatch, n):
+    """The default shape of these sizes is 6 or 20 cells a lane, widths the scan
+    leaves out: it is timed all the same, and where it wins nothing is recorded
+    for the bucket's other sizes."""
+    monkeypatch.setenv("REACH_AUTOTUNE_CACHE", str(tmp_path / "tune.txt"))
+    r = R.Reach(0)
+    try:
+        c = dev_case("rd", n, R.REACH_F64, 5)
+        sysd = R.make_system(c[0], n, c[1], 1)
+        other = R.make_system(c[0], n * 5 // 4, c[1], 1)
+        before = [R.reach_plan_embed(r.ctx, x, R.REACH_F64, 1000) for x in (sysd, other)]
+        ws = torch.empty(2 * n * 8, dtype=torch.uint8, device="cuda")
+        lo, hi = torch.empty_like(c[3]), torch.empty_like(c[4])
+        say(f"autotune n={n}")
+        best = R.reach_autotune_embed(r.ctx, sysd, R.REACH_F64, c[3], c[4], c[5], c[6], c[2], 8,
+                                      lo, hi, ws, ws.numel())
+        after = [R.reach_plan_embed(r.ctx, x, R.REACH_F64, 1000) for x in (sysd, other)]
+        line = (tmp_path / "tune.txt").read_text().split()
+        if best["E"] == before[0]["E"]:
+            assert after == before and line[7] == "0"
+        else:
+            assert line[7] == str(best["E"]) == str(after[1]["E"])
+    finally:
+        r.close()
+
+
+def test_tuned_shape_leaves_chains_of_one_window_alone(tmp_path, monkeypatch):
+    arch = torch.cuda.get_device_properties(0).gcnArchName.split(":")[0]
+    cache = tmp_path / "tune.txt"
+    sysd = [R.make_system(R.REACH_RD, n, (1.0,), 0) for n in (1500, 5000)]
+    plans = []
+    for text in ("", f"reach2 embed {arch} 2 0 10 0 16 6 1 1.0\nreach2 embed {arch} 2 0 12 0 16 6 1 1.0\n",
+                 f"reach2 embed {arch} 2 0 12 0 16 6 1 1.0\nreach2 embed {arch} 2 0 12 0 0 0 0 1.0\n"):
+        cache.write_text(text)
+        monkeypatch.setenv("REACH_AUTOTUNE_CACHE", str(cache))
+        r = R.Reach(0)
+        plans.append([R.reach_plan_embed(r.ctx, s, R.REACH_F64, 100) for s in sysd])
+        r.close()
+    assert plans[1][0] == plans[0][0] and plans[1][0]["tiles"] > 1
+    assert (plans[1][1]["E"], plans[1][1]["K"]) == (16, 6)
+    assert plans[2] == plans[0]
