@@ -1589,9 +1589,11 @@ reach_status reach_growth_bound(reach_ctx* c, const reach_system* s, reach_dtype
     const int like = s->kind == REACH_CTM ? REACH_CTM : REACH_RD;
     bool single = false;
     if (!E) {
+        // (a K of the caller's has to fit the window's halo, which the narrower of
+        // the widths, 2, 12 and 20 cells, would refuse at sizes that 4, 16 and 24 take)
         int one = 0;
         for (int e : {1, 2, 4, 8, 12, 16, 20, 24, 28, 32})
-            if ((int64_t)64 * e >= n) { one = e; break; }
+            if ((int64_t)64 * e >= n && !(K && (e == 2 || e == 12 || e == 20))) { one = e; break; }
         const int64_t simds = (int64_t)4 * c->cus;
         TuneEntry t{0, 0, 1};
         if (!K && nsteps > 0 && estimated(like, dtype, cell_in, n, simds)) {

@@ -256,7 +256,7 @@ def test_autotuner_keeps_a_default_it_has_not_beaten(tmp_path, monkeypatch, n):
     try:
         c = dev_case("rd", n, R.REACH_F64, 5)
         sysd = R.make_system(c[0], n, c[1], 1)
-        other = R.make_system(c[0], n * 5 // 4, c[1], 1)
+        other = R.make_system(c[0], n * 15 // 16, c[1], 1)   # of the same bucket
         before = [R.reach_plan_embed(r.ctx, x, R.REACH_F64, 1000) for x in (sysd, other)]
         ws = torch.empty(2 * n * 8, dtype=torch.uint8, device="cuda")
         lo, hi = torch.empty_like(c[3]), torch.empty_like(c[4])
@@ -288,3 +288,23 @@ def test_tuned_shape_leaves_chains_of_one_window_alone(tmp_path, monkeypatch):
     assert plans[1][0] == plans[0][0] and plans[1][0]["tiles"] > 1
     assert (plans[1][1]["E"], plans[1][1]["K"]) == (16, 6)
     assert plans[2] == plans[0]
+
+
+@pytest.mark.parametrize("n,K", [(100, 16), (100, 31), (128, 20), (600, 127), (768, 96), (1200, 160)])
+def test_growth_bound_takes_every_K_its_window_holds(rc, n, K):
+    """Option gb.K without gb.E, steps per pass that 4, 16 and 24 cells a lane
+    hold: the bits of the default plan; the first one past them is refused."""
+    c = dev_case("rd", n, R.REACH_F64, 11)
+    ref = rc.growth_bound(c[0], c[1], c[3], c[4], c[2], 200, p_lo=c[5], p_hi=c[6])
+    assert rc.sync() == R.REACH_OK
+    rc.set_option("gb.K", K)
+    try:
+        say(f"gb.K={K} n={n}")
+        got = rc.growth_bound(c[0], c[1], c[3], c[4], c[2], 200, p_lo=c[5], p_hi=c[6])
+        assert rc.sync() == R.REACH_OK
+        assert torch.equal(got[0], ref[0]) and torch.equal(got[1], ref[1])
+        rc.set_option("gb.K", 8 * {100: 4, 128: 4, 600: 16, 768: 16, 1200: 24}[n])
+        with pytest.raises(R.ReachError):
+            rc.growth_bound(c[0], c[1], c[3], c[4], c[2], 200, p_lo=c[5], p_hi=c[6])
+    finally:
+        rc.set_option("gb.K", 0)
