@@ -46,12 +46,12 @@ void gb_tile_kernel(GbPass a) {
     T y[1][E];
     if (a.first) {
         T hi[E];
-        IO::load(y[0], (const T*)a.x_lo, ts, a.n, T(0), fast, a.nt, my_lds);
-        IO::load(hi, (const T*)a.x_hi, ts, a.n, T(0), fast, a.nt, my_lds);
+        IO::load(y[0], (const T*)a.x_lo, ts, a.n, T(0), fast, false, my_lds);
+        IO::load(hi, (const T*)a.x_hi, ts, a.n, T(0), fast, false, my_lds);
 #pragma unroll
         for (int e = 0; e < E; ++e) y[0][e] = e < nvalid ? part(y[0][e], hi[e]) : out;
     } else {
-        IO::load(y[0], (const T*)(side == 0 ? a.src_c : a.src_r), ts, a.n, out, fast, a.nt, my_lds);
+        IO::load(y[0], (const T*)(side == 0 ? a.src_c : a.src_r), ts, a.n, out, fast, false, my_lds);
     }
 
     Inputs<T, E, 1, MODE> U;
@@ -84,7 +84,7 @@ void gb_tile_kernel(GbPass a) {
     const int olo = (w == 0) ? 0 : a.H + (int)(w * a.OUT - ts);
     const int ohi = reaches_end ? (int)(a.n - ts) : (int)(span - a.H);
     if (!a.last) {
-        IO::store(y[0], (T*)(side == 0 ? a.dst_c : a.dst_r), ts, olo, ohi, fast, a.nt, my_lds);
+        IO::store(y[0], (T*)(side == 0 ? a.dst_c : a.dst_r), ts, olo, ohi, fast, false, my_lds);
         return;
     }
     // [c - r, c + r]: the center wave writes the lower vector, the other the upper
@@ -106,7 +106,7 @@ void gb_tile_kernel(GbPass a) {
         y[0][e] = side == 0 ? lo : hi;
     }
     __syncthreads();   // both have read before the rows stage the stores
-    IO::store(y[0], (T*)(side == 0 ? a.r_lo : a.r_hi), ts, olo, ohi, fast, a.nt, my_lds);
+    IO::store(y[0], (T*)(side == 0 ? a.r_lo : a.r_hi), ts, olo, ohi, fast, false, my_lds);
     report_status(a.status, bits);
 }
 

@@ -66,7 +66,7 @@ struct GbPass {
     const void* p_lo;
     const void* p_hi;
     int64_t n, W, OUT, ksteps;
-    int32_t H, first, last, per_xcd, nt;
+    int32_t H, first, last, per_xcd;
     void* r_lo;
     void* r_hi;
     unsigned int* status;
