@@ -168,9 +168,9 @@ const char* reach_last_error(const reach_ctx* ctx);
      "mc.waves"   resident waves of the Monte Carlo kernel (0 = default: at most
                   16 per compute unit; at most 4096)
      "batch.split" 1: no packing, one wave per side of each cooperative query
-                  (shorter latency per query); 0 (default): a batch that does
-                  not pack runs so anyway; in a packed one the packs run whole,
-                  except the longest of a batch too small for them
+                  (shorter latency per query); 0 (default): one wave per query
+                  or pack, except the longest, which would outlast the batch's
+                  average load of a SIMD and run one side per wave
      "batch.pack" 0 (default): segment packs when the batch has more queries
                   than 16 per compute unit (than twice "batch.waves" when set);
                   1: always; 2: never
@@ -389,9 +389,10 @@ size_t reach_batch_workspace_bytes(int64_t nq);
  * bitwise equal parameters and dt, step counts in the same 1/16 octave and
  * the same cells per lane E (2, 4, 8 or 16, chosen per query by the least
  * estimated issue cost, at most option "batch.E" or else the (kind, size)
- * bucket's autotuned cap; unless option "batch.pack" or "batch.E" is set, a
- * query whose pack would outlast the batch's average load of a SIMD by a
- * quarter takes a narrower one) sharing a wavefront, query m on ceil(n_m / E)
+ * bucket's autotuned cap; unless option "batch.pack" or "batch.E" is set, and
+ * where the longest pack would take 1.45 times the batch's average load of a
+ * SIMD, a query whose pack would outlast that load by a quarter takes a
+ * narrower one) sharing a wavefront, query m on ceil(n_m / E)
  * lanes, at most 64 lanes and 64 queries.  An unpacked batch runs every
  * query alone, spread over a whole wavefront (E = ceil(n / 64)).  Items come
  * longest first (wave time E * nsteps of the longest member).

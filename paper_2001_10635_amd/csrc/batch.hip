@@ -3,14 +3,15 @@
 // Every query (FP64, n <= 512 cells, scalar input) is run by one wavefront
 // with its whole lower/upper state in registers (E = ceil(n / 64) cells per
 // lane, 1..8, spread so that every lane is busy), all N RK4 steps in one go:
-// no halo, no HBM traffic inside the step loop; short cooperative queries
-// share a wavefront, one cell per lane.  The arithmetic per cell is the
+// no halo, no HBM traffic inside the step loop.  Long cooperative queries, and
+// served ones, take a wavefront per side; the queries of a large batch share
+// wavefronts at 2 to 16 cells per lane.  The arithmetic per cell is the
 // large-n embedding kernel's, so a query gives the same box alone, in a batch,
 // or served.
 //
-//   batch_kernel   persistent grid; each wave pops the next work item (one side
-//                  of a cooperative query) from a device counter until the
-//                  batch is exhausted.
+//   batch_kernel   persistent grid; each wave pops the next work item (a query, or
+//                  one side of the longest cooperative ones) from a device
+//                  counter until the batch is exhausted.
 //   pack_kernel    the same for a packed batch, whose items are segment packs:
 //                  queries sharing a wave at E cells per lane
 //                  (pack_sides_kernel: the longest of them one side per wave).
@@ -147,20 +148,23 @@ __global__ __launch_bounds__(64) void batch_kernel(const QDesc* __restrict__ des
                                                    unsigned int* qflags, unsigned int* pair,
                                                    unsigned int* status) {
     const int lane = threadIdx.x;
-    const uint64_t ni = wave_bcast(*n_items);
-    const uint64_t total = 2 * ni;
+    const uint64_t nw = wave_bcast(*n_items);
+    const uint64_t ni = nw & 0xFFFFFFFFu, ns = nw >> 32;
     for (;;) {
         uint64_t u = 0;
         if (lane == 0) u = atomicAdd(counter, 1ULL);
         u = wave_bcast(u);
-        if (u >= total) break;
-        // one side of item i
-        const uint64_t i = u >> 1;
-        const int side = (int)(u & 1);
+        if (u >= ni + ns) break;
+        // one side of item u / 2, or the whole of a shorter query (4000 CTM and RD queries of
+        // 100 steps: 200 us whole, 490 by sides, which wait for each other's results
+        // through memory; 2000 of 10 to 1000 steps, the longest by sides: 470 for 950)
+        const bool one = u < 2 * ns;
+        const uint64_t i = one ? u >> 1 : u - ns;
+        const int side = one ? (int)(u & 1) : 0;
         const QDesc d = desc[members[items[i].start]];
         if (item_is_empty(d, side)) continue;
-        unsigned bits = run_item(d, side);
-        if (!item_is_whole(d)) {
+        unsigned bits = one ? run_item(d, side) : run_query(d);
+        if (one && !item_is_whole(d)) {
             // publish this side, then the second side to finish checks the order
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
             uint64_t old = 0;

@@ -195,18 +195,19 @@ struct BatchItem {
 // indices of the items in launch order).  packed 1: every item is a segment
 // pack of at most 8 cells per lane (E > 0), run by the packing kernel (room
 // for three waves per SIMD); packed 2: some pack has 16 cells per lane, all
-// run by the wide packing kernel (room for two); packed 0:
-// every item is one query (E = 0) and runs as two, one per side of a cooperative
-// chain, pair[i] counting the finished sides of item i.
-// *n_items of a packed batch with `sides` holds in its high half the number of
-// leading items that run one side per wave (pair[i] as above).
+// run by the wide packing kernel (room for two); // packed 0:
+// every item is one query (E = 0).
+// *n_items holds in its high half the number of leading items that run one side
+// per wave (a coupled one whole as its first side), pair[i] counting the
+// finished sides of item i; of a packed batch only with `sides`.
 hipError_t launch_batch(const QDesc* d, const BatchItem* items, const uint32_t* members,
                         const uint64_t* n_items, unsigned long long* counter,
                         unsigned int* qflags, unsigned int* pair, unsigned int* status,
                         bool sides, int packed, int64_t grid, hipStream_t stream);
 // Default waves per compute unit of the batch kernels: the one-query kernel one
-// per SIMD (its long queries then have a SIMD to themselves: 2000 mixed queries
-// 446 us, 627 at two per SIMD, 4000 572 and 636), the narrow packing kernel two
+// per SIMD (CTM and RD queries of 10 to 1000 steps, 1500 of them 449 us, 526 at two
+// per SIMD, 4096 488 and 643; of 100 steps 4096 203 and 234; LIN3 alone, 2500, 1100 and
+// 1234, 164 and 250), the narrow packing kernel two
 // (it fits three, which measures slower), the wide packing kernel one per SIMD (16 cells give one
 // wave enough independent work to keep its SIMD issuing; two measure slower).
 constexpr int kBatchWavesPerCU = 4;

@@ -1830,15 +1830,42 @@ int seg_E(int64_t n, int cap) {
     return bestE ? bestE : above;
 }
 
+// Cells per lane of a packed query by size: cap[c], the cheapest up to 2 << c cells,
+// and down[k], the widest narrower than kSegE[k] that its lanes still fit (0: none).
+struct PackWidths {
+    int8_t cap[4][513], down[4][513];
+};
+const PackWidths& pack_widths() {
+    static const PackWidths t = [] {
+        PackWidths w{};
+        for (int64_t n = 1; n <= 512; ++n)
+            for (int k = 0; k < 4; ++k) {
+                w.cap[k][n] = (int8_t)seg_E(n, 2 << k);
+                for (int j = 0; j < k; ++j) {
+                    const int e = kSegE[j];
+                    const int64_t L = (n + e - 1) / e;
+                    if (L <= 64 && n >= (int64_t)(e - 1) * L) w.down[k][n] = (int8_t)e;
+                }
+            }
+        return w;
+    }();
+    return t;
+}
+
 // Whether one side's result lies over what the other side reads.  A wave that
 // holds both sides reads both before it writes; waves of one side each do not
 // wait for each other.  (A LIN3 query always runs whole.)
-bool crossed(const QDesc& d) {
-    if (d.kind == REACH_LIN3) return false;
-    const size_t box = sizeof(double) * (size_t)d.n;
-    return overlaps(d.x_hi, box, d.r_lo, box) || overlaps(d.p_hi, sizeof(double), d.r_lo, box) ||
-           overlaps(d.x_lo, box, d.r_hi, box) || overlaps(d.p_lo, sizeof(double), d.r_hi, box);
+bool crossed(const reach_query& q) {
+    if (q.sys.kind == REACH_LIN3) return false;
+    const size_t box = sizeof(double) * (size_t)q.sys.n, in = sizeof(double) * (size_t)q.sys.n_in;
+    return overlaps(q.x_hi, box, q.r_lo, box) || overlaps(q.p_hi, in, q.r_lo, box) ||
+           overlaps(q.x_lo, box, q.r_hi, box) || overlaps(q.p_lo, in, q.r_hi, box);
 }
+
+// Least E * steps of a pack or query that may run one side per wave: the two waves
+// exchange the end of their item through memory, which writes back caches (700
+// queries of 20 steps: 88 us by sides, 52 whole; 4500 of 20 steps in packs: 428 and 294).
+constexpr uint64_t kMinSidePack = 1600, kMinSideQuery = 200;
 
 // Whether a batch packs: option batch.pack 1 always, 2 never, 0 (default)
 // when it has more queries than 16 per compute unit, or than twice option
@@ -1878,8 +1905,8 @@ int batch_ecap(const reach_ctx* c, int kind, int bucket) {
 // context; the first bad query, lowest index, is re-checked with the context
 // afterwards to set the error message).  When the batch does not pack
 // (batch_packs), every query is an item of its own, run alone over a whole
-// wave.  When it packs, every item is a segment pack, and each query gets a
-// pack key: its constants class (bitwise equal kind, dt and parameters),
+// wave.  When it packs, every item is a segment pack, and each query gets,
+// once the batch's load is known, a pack key: its constants class (bitwise equal kind, dt and parameters),
 // cells per lane E (seg_E under the bucket's cap) and 1/16-octave step
 // bucket.  Then unit u owns the keys of the (E, bucket) pairs r with r mod
 // nu = u and scans the queries of its keys in caller order, placing each in
@@ -1889,7 +1916,7 @@ int batch_ecap(const reach_ctx* c, int kind, int bucket) {
 // the first pack with room.  Items are then ordered longest first by the wave
 // time (E * steps of the longest member; ceil(n / 64) * steps alone) at 1/16
 // octave, ties in unit order.  Packs of a batch too small for its longest query
-// are narrowed, and its longest items run one side per wave (see there).
+// are narrowed, and the longest items run one side per wave (see there).
 //
 // cross (may be NULL): set when some query is `crossed`, the plan then unfinished;
 // whole: the plan for such a batch, packed whatever its size and the options,
@@ -1952,6 +1979,7 @@ reach_status plan_batch(reach_ctx* c, HostPool* pool, const reach_query* q, int6
         const uint64_t cost = (uint64_t)d.E * (uint64_t)std::min<int64_t>(d.nsteps, (int64_t)1 << 40);
         items.push_back(Item{(uint32_t)members.size(), 1, 0, (int16_t)wave_time_bucket(cost)});
         members.push_back(i);
+        return cost;
     };
     auto push_pack = [&](std::vector<Item>& items, std::vector<uint32_t>& members, Open& o) {
         if (o.count >= 1) {
@@ -1972,51 +2000,7 @@ reach_status plan_batch(reach_ctx* c, HostPool* pool, const reach_query* q, int6
     std::vector<std::vector<uint32_t>> tmembers((size_t)nu);
     std::vector<int64_t> bad((size_t)nu, nq);
     std::vector<uint8_t> crosses((size_t)nu, 0);
-    // cells per lane of a packed query by cap (2, 4, 8, 16) and size
-    int8_t etab[4][513];
-    for (int ci = 0; ci < 4; ++ci)
-        for (int64_t n = 1; n <= 512; ++n) etab[ci][n] = (int8_t)seg_E(n, 2 << ci);
-    // The batch's load: the wave time E * steps of the packs, by the lanes their
-    // queries take, over the SIMDs.  A pack longer than that holds up the end
-    // of the launch, so queries whose packs would take more than 1.25 loads go
-    // to narrower packs (as far as their lanes fit a wave), and the items still
-    // longer than one load run one side per wave (*sides_out).  A 10^4-query mix
-    // (4-512 cells, 10-1000 steps) has a load of about 4200: 16 cells for 1000
-    // steps would take 16000, 8 cells and one side the time of 4000.
-    uint64_t load = 0;
-    if (packs) {
-        std::vector<uint64_t> part((size_t)nu, 0);
-        run_units(pool, nth, nu, [&](int t) {
-            int64_t lo, hi;
-            chunk(t, nq, &lo, &hi);
-            uint64_t sum = 0;   // E * lanes * steps
-            for (int64_t i = lo; i < hi; ++i) {
-                const reach_system& sy = q[i].sys;
-                if (sy.n < 1 || sy.n > kBatchMaxN || q[i].nsteps < 0) continue;   // refused below
-                const int cap = ecap[sy.kind & 3][std::min(n_bucket(sy.n), kNB - 1)];
-                const int E = etab[cap >= 16 ? 3 : cap >= 8 ? 2 : cap >= 4 ? 1 : 0][sy.n];
-                sum += (uint64_t)(E * ((sy.n + E - 1) / E)) *
-                       (uint64_t)std::min<int64_t>(q[i].nsteps, (int64_t)1 << 32);
-            }
-            part[(size_t)t] = sum;
-        });
-        for (const uint64_t v : part) load += v;
-        load /= (uint64_t)kLanes * 4 * (uint64_t)(c ? c->cus : 256);
-    }
-    // (a caller who asks for packs or for a width gets the widths as they are)
-    const bool narrow = packs && !(c && (opt_get(c, "batch.pack") || opt_get(c, "batch.E")));
-    const auto narrower = [&](int64_t n, int E, int64_t steps) {
-        int best = E;
-        if (!narrow) return best;
-        for (int k = kNE - 1; k >= 0; --k) {
-            const int e = kSegE[k];
-            const int64_t L = (n + e - 1) / e;
-            if (e >= best || L > kLanes || n < (int64_t)(e - 1) * L) continue;
-            if ((uint64_t)best * (uint64_t)steps <= load + load / 4) break;
-            best = e;
-        }
-        return best;
-    };
+    const auto& etab = pack_widths().cap;
     // pass 1: descriptors, validation, pack keys (class ids local to the
     // chunk); a chunk's packed queries are listed by the partition owning
     // their (E, step bucket) pair, r mod nu
@@ -2027,10 +2011,57 @@ reach_status plan_batch(reach_ctx* c, HostPool* pool, const reach_query* q, int6
         int32_t key;       // (E index, step bucket) << 4 | chunk-local class
         int64_t nsteps;
         int32_t L;         // lanes at the key's E
+        uint16_t n;
+        uint8_t E;
+        int8_t cls;        // -1: a class beyond the unit's table
     };
     std::vector<std::vector<Consts>> tclasses((size_t)nu);
     std::vector<std::vector<QRef>> lists((size_t)nu);          // by partition, caller order within
     std::vector<std::vector<uint32_t>> list_at((size_t)nu);    // partition p: [at[p], at[p + 1])
+    std::vector<std::vector<QRef>> refs((size_t)nu);           // a chunk's packed queries
+    std::vector<std::pair<uint64_t, uint64_t>> loads((size_t)nu);   // sum and longest
+    // the keys of a chunk's queries, and the lists by partition
+    const auto key_refs = [&](int t, bool narrow, uint64_t load) {
+        std::vector<QRef>& mine = refs[(size_t)t];
+        titems[(size_t)t].clear();
+        tmembers[(size_t)t].clear();
+        std::vector<uint32_t>& at = list_at[(size_t)t];
+        at.assign((size_t)nu + 1, 0);
+        for (QRef& r : mine) {
+            const uint64_t steps = (uint64_t)std::min<int64_t>(r.nsteps, (int64_t)1 << 32);
+            while (narrow && r.E * steps > load + load / 4) {
+                const int e = pack_widths().down[r.E == 16 ? 3 : r.E == 8 ? 2 : r.E == 4 ? 1 : 0][r.n];
+                if (!e) break;
+                r.E = (uint8_t)e;
+            }
+            r.L = (int32_t)(((unsigned)r.n + r.E - 1) / r.E);
+            if (r.cls < 0) {
+                // a class beyond the unit's table: a pack of its own
+                Open o;
+                o.E = r.E;
+                o.mem[o.count++] = r.i;
+                o.lanes = r.L;
+                o.max_steps = r.nsteps;
+                push_pack(titems[(size_t)t], tmembers[(size_t)t], o);
+                continue;
+            }
+            int ei = 0;
+            while (kSegE[ei] != r.E) ++ei;
+            const int b = wave_time_bucket((uint64_t)std::min<int64_t>(r.nsteps, (int64_t)1 << 40));
+            r.key = ((ei * kBuckets + b) << 4) | r.cls;
+            ++at[(size_t)((r.key >> 4) % nu) + 1];
+        }
+        // by partition (counting sort, caller order kept within a partition)
+        for (int u = 0; u < nu; ++u) at[(size_t)u + 1] += at[(size_t)u];
+        std::vector<QRef>& out = lists[(size_t)t];
+        out.resize(at[(size_t)nu]);
+        std::vector<uint32_t> put(at.begin(), at.end() - 1);
+        for (const QRef& r : mine)
+            if (r.cls >= 0) out[put[(size_t)((r.key >> 4) % nu)]++] = r;
+    };
+    // (on several threads the keys at the first width are formed at once, which
+    // saves a batch without a tail a hand-over between them)
+    const bool keyed = nth > 1;
     run_units(pool, nth, nu, [&](int t) {
         int64_t lo, hi;
         chunk(t, nq, &lo, &hi);
@@ -2038,22 +2069,26 @@ reach_status plan_batch(reach_ctx* c, HostPool* pool, const reach_query* q, int6
         std::vector<uint32_t> members;
         int64_t my_bad = nq;
         bool my_cross = false;
+        uint64_t my_cost = 0, longest = 0;
         std::vector<Consts> classes;
         std::vector<QRef> mine;
+        if (packs) mine.reserve((size_t)(hi - lo));
         for (int64_t i = lo; i < hi; ++i) {
             QDesc& d = descs[i];
             if (make_desc(nullptr, q[i], i, &d) != REACH_OK) {
                 my_bad = std::min(my_bad, i);
                 continue;
             }
-            if (cross) my_cross |= crossed(d);
+            if (cross) my_cross |= crossed(q[i]);
             if (!packs) {
-                push_alone(items, members, (uint32_t)i);
+                my_cost += push_alone(items, members, (uint32_t)i);
                 continue;
             }
             const int cap = ecap[d.kind & 3][std::min(n_bucket(d.n), kNB - 1)];
-            const int E = narrower(d.n, etab[cap >= 16 ? 3 : cap >= 8 ? 2 : cap >= 4 ? 1 : 0][d.n],
-                                   std::min<int64_t>(d.nsteps, (int64_t)1 << 32));
+            const int E = etab[cap >= 16 ? 3 : cap >= 8 ? 2 : cap >= 4 ? 1 : 0][d.n];
+            const uint64_t steps = (uint64_t)std::min<int64_t>(d.nsteps, (int64_t)1 << 32);
+            my_cost += ((unsigned)d.n + (unsigned)E - 1) / (unsigned)E * (unsigned)E * steps;
+            longest = std::max(longest, (uint64_t)E * steps);
             int cls = -1;
             Consts cs;
             std::memset(&cs, 0, sizeof cs);
@@ -2066,38 +2101,16 @@ reach_status plan_batch(reach_ctx* c, HostPool* pool, const reach_query* q, int6
                 classes.push_back(cs);
                 cls = (int)classes.size() - 1;
             }
-            if (cls < 0) {
-                // a class beyond the thread's table: a pack of its own
-                Open o;
-                o.E = E;
-                o.mem[o.count++] = (uint32_t)i;
-                o.lanes = (int)((d.n + E - 1) / E);
-                o.max_steps = d.nsteps;
-                push_pack(items, members, o);
-                continue;
-            }
-            int ei = 0;
-            while (kSegE[ei] != E) ++ei;
-            const int b = wave_time_bucket((uint64_t)std::min<int64_t>(d.nsteps, (int64_t)1 << 40));
-            const int r = ei * kBuckets + b;
-            mine.push_back(QRef{(uint32_t)i, (r << 4) | cls, d.nsteps, (int32_t)((d.n + E - 1) / E)});
-        }
-        // by partition (counting sort, caller order kept within a partition)
-        std::vector<uint32_t>& at = list_at[(size_t)t];
-        at.assign((size_t)nu + 1, 0);
-        for (const QRef& qr : mine) ++at[(size_t)((qr.key >> 4) % nu) + 1];
-        for (int u = 0; u < nu; ++u) at[(size_t)u + 1] += at[(size_t)u];
-        std::vector<QRef>& sorted_refs = lists[(size_t)t];
-        sorted_refs.resize(mine.size());
-        {
-            std::vector<uint32_t> put(at.begin(), at.end() - 1);
-            for (const QRef& qr : mine) sorted_refs[put[(size_t)((qr.key >> 4) % nu)]++] = qr;
+            mine.push_back(QRef{(uint32_t)i, 0, d.nsteps, 0, (uint16_t)d.n, (uint8_t)E, (int8_t)cls});
         }
         titems[(size_t)t] = std::move(items);
         tmembers[(size_t)t] = std::move(members);
         tclasses[(size_t)t] = std::move(classes);
         bad[(size_t)t] = my_bad;
+        refs[(size_t)t] = std::move(mine);
+        if (packs && keyed) key_refs(t, false, 0);
         crosses[(size_t)t] = my_cross ? 1 : 0;
+        loads[(size_t)t] = {my_cost, longest};
     });
     const int64_t first_bad = *std::min_element(bad.begin(), bad.end());
     if (first_bad < nq) {
@@ -2111,6 +2124,26 @@ reach_status plan_batch(reach_ctx* c, HostPool* pool, const reach_query* q, int6
     // every descriptor is written: the caller may start moving them while
     // the items are formed
     if (descs_done) descs_done();
+    // The batch's load: the wave time E * steps of its items over the SIMDs (of packs,
+    // by the lanes their queries take).  An item longer than that holds up the end of
+    // the launch: it runs one side per wave (*sides_out).  Packs fill about four fifths
+    // of their lanes and narrower ones spend a ninth more on shifts and selects, so
+    // the packs of a batch are left as they are unless the longest takes 1.45 loads
+    // (7000 queries of 100 steps: 966 packs of 16 cells 204 us, 1574 of 8 cells 215);
+    // else queries whose packs would take more than 1.25 loads go to narrower ones (as
+    // far as their lanes fit a wave), and the items still longer than one load to two
+    // waves.  A 10^4-query mix (4-512 cells, 10-1000 steps) has a load of about 4200: 16
+    // cells for 1000 steps would take 16000, 8 cells and one side the time of 4000.
+    uint64_t load = 0, longest = 0;
+    for (const auto& v : loads) {
+        load += v.first;
+        longest = std::max(longest, v.second);
+    }
+    load /= (uint64_t)(packs ? kLanes : 1) * 4 * (uint64_t)(c ? c->cus : 256);
+    const bool tail = (double)longest > 1.45 * (double)load;
+    // (a caller who asks for packs or for a width gets the widths as they are)
+    const bool narrow = tail && !(c && (opt_get(c, "batch.pack") || opt_get(c, "batch.E")));
+    if (packs && (narrow || !keyed)) run_units(pool, nth, nu, [&](int t) { key_refs(t, narrow, load); });
     if (times) times->pass1_ms = since(t0);
     if (packs) {
         // global class ids (the chunks' tables merged in chunk order)
@@ -2283,8 +2316,9 @@ reach_status plan_batch(reach_ctx* c, HostPool* pool, const reach_query* q, int6
         }
     // items longer than the load come first: those of the buckets before its own
     *sides_out = 0;
-    if (packs && !whole) {
-        const int lb = wave_time_bucket(load);
+    if (split && !whole) *sides_out = ni;
+    else if (packs ? tail && !whole : true) {
+        const int lb = wave_time_bucket(std::max(load, packs ? kMinSidePack : kMinSideQuery));
         // (the counts are item indices now: that of unit 0 in the load's bucket is
         // the number of items in the buckets before)
         *sides_out = lb <= b0 ? 0 : lb > b1 ? ni : hist[lb];
@@ -2368,8 +2402,8 @@ reach_status reach_embed_rk4_batch(reach_ctx* c, const reach_query* q, int64_t n
     if (!ws || ws_bytes < need) return fail(c, REACH_E_NOMEM, "workspace of %zu bytes needed", need);
     HIPCHK(c, hipSetDevice(c->device));
     hipStream_t hs = (hipStream_t)stream;
-    // batch.split = 1 turns packing off.  An unpacked batch, whose time is its longest
-    // query's, runs each side of a cooperative query in a wave of its own
+    // batch.split = 1 turns packing off and runs each side of a cooperative query in a
+    // wave of its own
     const int split = opt_get(c, "batch.split") ? 1 : 0;
     HostPool* pool = batch_host_threads(nq) > 1 ? host_pool(c) : nullptr;
     const int nth = pool ? std::min(batch_host_threads(nq), pool->size()) : 1;
@@ -2444,7 +2478,13 @@ reach_status reach_embed_rk4_batch(reach_ctx* c, const reach_query* q, int64_t n
         if (packed == 2) grid = std::min<int64_t>(grid, (int64_t)c->cus * 8);
     }
     c->last_packed = packed;
-    grid = std::min<int64_t>(grid, packed ? ni + sides : 2 * ni);
+    // (a coupled item of the leading ones runs whole, its second half is empty: waves
+    // for those would leave SIMDs with two items beside SIMDs with none)
+    int64_t units = ni + sides;
+    if (ni < grid)
+        for (int64_t k = 0; k < sides; ++k)
+            units -= hb.desc[hb.members[hb.items[k].start]].kind == REACH_LIN3 ? 1 : 0;
+    grid = std::min<int64_t>(grid, units);
 
     if (c->log) {
         using ms = std::chrono::duration<double, std::milli>;
@@ -2454,7 +2494,7 @@ reach_status reach_embed_rk4_batch(reach_ctx* c, const reach_query* q, int64_t n
                     "\"plan_members_ms\": %.3f",
                  (long long)nq, (long long)ni, (long long)(nq - (int64_t)std::count_if(
                      items.begin(), items.end(), [](const BatchItem& x) { return x.count == 1; })),
-                 (long long)grid, !packed || sides > 0 ? 1 : 0, nth, ms(t_plan - t_start).count(), pt.pass1_ms,
+                 (long long)grid, sides > 0 ? 1 : 0, nth, ms(t_plan - t_start).count(), pt.pass1_ms,
                  pt.pass_ms, pt.order_ms, pt.members_ms);
     }
     // the rest of the block (items, their count, the members) follows; the

@@ -308,3 +308,51 @@ def test_growth_bound_takes_every_K_its_window_holds(rc, n, K):
             rc.growth_bound(c[0], c[1], c[3], c[4], c[2], 200, p_lo=c[5], p_hi=c[6])
     finally:
         rc.set_option("gb.K", 0)
+
+
+@pytest.mark.parametrize("kinds", [("ctm", "rd"), ("lin3",), ("ctm", "lin3", "rd")])
+@pytest.mark.parametrize("nq", [90, 1100, 4300, 6500])
+@pytest.mark.parametrize("long", [20, 1000])
+def test_batch_layouts_equal_single_runs(rc, kinds, nq, long):
+    """Default batches, unpacked and packed, of equally short queries (every item
+    whole) and of some much longer ones (narrowed packs, the longest items one
+    side per wave): every box is the one the query gets by itself, and flags
+    of whole items, sides and packs reach the status."""
+    base = {k: [dev_case(k, n, R.REACH_F64, 500 + n) for n in (4, 33, 64, 65, 200, 257, 512)]
+            for k in kinds}
+    a, b, outs = [], [], []
+    for k in range(nq):
+        cs = base[kinds[k % len(kinds)]]
+        kind, prm, dt, lo, hi, pl, ph = cs[(k // 3) % len(cs)]
+        nsteps = long if k % 50 == 7 else 12 + k % 9
+        o = [torch.empty_like(lo) for _ in range(4)]
+        outs.append(o)
+        for dst, r in ((a, o[:2]), (b, o[2:])):
+            dst.append(R.make_query(kind, lo.numel(), prm, R.REACH_F64, lo, hi, r[0], r[1], dt, nsteps,
+                                    pl, ph, n_in=0 if pl is None else 1))
+    nb = R.reach_batch_workspace_bytes(nq)
+    ws = torch.empty(nb, dtype=torch.uint8, device="cuda")
+    say(f"batch layouts {kinds} nq={nq} long={long}")
+    R.reach_embed_rk4_each(rc.ctx, R.query_array(a))
+    assert rc.sync() == R.REACH_OK
+    arr = R.query_array(b)
+    for _ in range(2):
+        R.reach_embed_rk4_batch(rc.ctx, arr, ws, nb)
+    assert rc.sync() == R.REACH_OK
+    for k, o in enumerate(outs):
+        assert torch.equal(o[0], o[2]) and torch.equal(o[1], o[3]), k
+    for k in (0, 7, nq - 1):
+        for bad, want in ((float("inf"), R.REACH_E_NONFINITE), (None, R.REACH_E_ORDER)):
+            q = b[k]
+            n = q.sys.n
+            lo = torch.ones(n, dtype=torch.float64, device="cuda")
+            hi = lo + 0.1
+            if bad is None:
+                lo[n // 2] = 9.0
+            else:
+                hi[n // 2] = bad
+            x = R.query_array(b)
+            x[k].x_lo, x[k].x_hi = lo.data_ptr(), hi.data_ptr()
+            x[k].nsteps = 1 if bad is None else q.nsteps
+            R.reach_embed_rk4_batch(rc.ctx, x, ws, nb)
+            assert rc.sync() == want, (k, bad)
