@@ -195,7 +195,7 @@ struct BatchItem {
 // indices of the items in launch order).  packed 1: every item is a segment
 // pack of at most 8 cells per lane (E > 0), run by the packing kernel (room
 // for three waves per SIMD); packed 2: some pack has 16 cells per lane, all
-// run by the wide packing kernel (room for two); // packed 0:
+// run by the wide packing kernel (room for two); packed 0:
 // every item is one query (E = 0).
 // *n_items holds in its high half the number of leading items that run one side
 // per wave (a coupled one whole as its first side), pair[i] counting the

@@ -124,10 +124,15 @@ struct CutRun {
         slot = &c.slot[k];
         stream = s;
         mem = c.mem + (size_t)k * CutScratch::kSlotBytes;
+        if (!slot->done) return hipEventCreateWithFlags(&slot->done, hipEventDisableTiming);
         return slot->recorded ? hipStreamWaitEvent(s, slot->done, 0) : hipSuccess;
     }
     ~CutRun() {
         if (!slot) return;
+        if (!slot->done) {
+            slot->m.unlock();
+            return;
+        }
         slot->recorded |= hipEventRecord(slot->done, stream) == hipSuccess;
         slot->m.unlock();
     }
@@ -1078,14 +1083,10 @@ reach_status reach_ctx_create(int device, reach_ctx** out) {
     bool ok = hipEventCreateWithFlags(&c->batch_ev, hipEventDisableTiming) == hipSuccess;
     for (int k = 0; k < 2 && ok; ++k)
         ok = hipEventCreateWithFlags(&c->block_ev[k], hipEventDisableTiming) == hipSuccess;
-    for (int k = 0; k < CutScratch::kSlots && ok; ++k)
-        ok = hipEventCreateWithFlags(&c->cut.slot[k].done, hipEventDisableTiming) == hipSuccess;
     ok = ok && hipStreamCreateWithFlags(&c->copy_stream, hipStreamNonBlocking) == hipSuccess;
     if (!ok) {
         for (hipEvent_t e : {c->staging_ev, c->batch_ev, c->block_ev[0], c->block_ev[1]})
             if (e) hipEventDestroy(e);
-        for (CutScratch::Slot& k : c->cut.slot)
-            if (k.done) hipEventDestroy(k.done);
         hipFree(c->status);
         delete c;
         return REACH_E_DEVICE;
