@@ -86,3 +86,29 @@ def test_mc_nonfinite_samples_reach_min_and_max(rc, n, m, bad, dtype):
         f = np.isfinite(o)
         assert np.array_equal(f, np.isfinite(g)) and not f.all()
         assert_rel(g[f], o[f], RTOL[np.dtype(dtype)], "finite dimensions")
+
+
+@pytest.mark.parametrize("variant", ["ctm", "rd", "lin3"])
+@pytest.mark.parametrize("n", [40, 64, 100])
+def test_mc_samples_sharing_a_wave_give_the_bits_of_samples_alone(variant, n, capfd, monkeypatch):
+    """Many samples share waves, a few take one each (the calls' log says so): the
+    min / max of a large range is bit for bit that of the small ones it holds."""
+    import re
+    monkeypatch.setenv("REACH_LOG", "1")
+    r = R.Reach(0)
+    try:
+        kind, prm, lo, hi, pl, ph, dt = make_case(variant, n, np.float64, seed=n)
+        dev = lambda a: None if a is None else torch.from_numpy(np.ascontiguousarray(a)).cuda()
+        args = (kind, prm, dev(lo), dev(hi), dt, 6)
+        kw = dict(p_lo=dev(pl), p_hi=dev(ph))
+        say(f"mc shared waves {variant} n={n}")
+        capfd.readouterr()
+        mn, mx = r.montecarlo(*args, 20000, 3, **kw)
+        parts = [r.montecarlo(*args, 250, 3, s0=s, **kw) for s in range(0, 20000, 250)]
+        assert r.sync() == R.REACH_OK
+        spw = [int(x) for x in re.findall(r'"samples_per_wave": (\d+)', capfd.readouterr().err)]
+        assert spw[0] > 1 and set(spw[1:]) == {1}
+        assert torch.equal(mn, torch.stack([p[0] for p in parts]).min(0).values)
+        assert torch.equal(mx, torch.stack([p[1] for p in parts]).max(0).values)
+    finally:
+        r.close()
