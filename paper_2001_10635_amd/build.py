@@ -21,7 +21,9 @@ HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"
 
 # Sources that share one object file: the dispatch and the sources it dispatches
-# to, compiled apart (in parallel) and joined by a relocatable link.
+# to, compiled apart (in parallel: one source of a kernel family takes minutes) and
+# joined by a relocatable link, so that a family stays the one object under the name
+# by which host programs of the tests link it.
 GROUPS = {"embed": ["embed.hip", "embed_ctm_f64.hip", "embed_ctm_f32.hip", "embed_rd_f64.hip",
                     "embed_rd_f32.hip", "embed_lin3_f64.hip", "embed_lin3_f32.hip"],
           "mc": ["mc.hip", "mc_ctm_f64.hip", "mc_ctm_f32.hip", "mc_rd_f64.hip", "mc_rd_f32.hip",

@@ -134,8 +134,8 @@ __device__ __forceinline__ void rk_update(T k, T& y, T& acc, T& t, const Steps<T
 //   PAD : the window runs past cell n-1; cells at or beyond n hold the
 //         boundary's ghost value at every stage (nvalid cells of this lane are
 //         inside the chain): a select per cell.
-//   ONE : (with PAD; waves that hold one side or sample) only cell n, the right neighbour of cell n-1, is set to the ghost after
-//         each stage: slot `en` of the lane holding it, en the same in every
+//   ONE : (with PAD; waves that hold one side) only cell n, the right
+//         neighbour of cell n-1, is set to the ghost after each stage: slot `en` of the lane holding it, en the same in every
 //         lane, so one indexed register move per stage replaces the per-cell
 //         selects.  Cells beyond n then hold values that reach no cell of the
 //         chain and that no caller reads or checks.  Only for lane arrays of
@@ -254,7 +254,7 @@ __device__ __forceinline__ void rk_stage(T (&y)[S][E], T (&acc)[S][E], T (&t)[S]
         rk_update<STAGE>(k, y[s][e], acc[s][e], t[s][e], st);
         if (M.template per_cell<T>() && !M.ok(e)) out[s][e] = ghost<KIND, T>();
     };
-    // the masked slot (Monte Carlo)
+    // the ghost's slot (a padded window)
     const auto finish = [&](int s) {
         if constexpr (FIX) M.fix(out[s], ghost<KIND, T>());
     };

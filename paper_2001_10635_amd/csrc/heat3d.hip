@@ -421,8 +421,9 @@ static hipError_t go_heat_cut(int WV, const HeatPass& a, int64_t grid, hipStream
     }
 }
 
-// (P, WV) shapes: rows per wave, waves per block.  FP64 keeps the shapes
-// whose registers fit in the steady loop (4 x 8, 5 x 8, 3 x 12, 2 x 16).
+// (P, WV) shapes: rows per wave, waves per block.  In FP64 the steady loops of
+// 4 x 8, 3 x 12 and 2 x 16 stay in registers; 5 x 8 spills there (36 to 42 scratch
+// accesses per six planes) and is never the default.
 bool heat_has_shape(int dtype, int P, int WV) {
     if (dtype == 0)
         return (P == 4 && WV == 8) || (P == 2 && WV == 16) || (P == 5 && WV == 8) ||

@@ -172,8 +172,10 @@ __device__ __forceinline__ void seg_stage(T (&y)[E], T (&acc)[E], T (&t)[E], con
 // Waves per SIMD the registers have to leave room for: y, acc and t are 3 E
 // values a lane, per-cell inputs E more.  FP32 instructions of different waves
 // overlap, so FP32 gains from a third and fourth wave; FP64 has no use for more
-// than two.  (What the limit pushes to scratch memory lies in the draws and the
-// fold, not in the step loop.)
+// than two.  What the limit pushes to scratch memory lies in the draws and the
+// fold, but for two accesses a step in the FP32 kernels of 48 cells a lane and more
+// (480 to 1152 FMAs) and 9 to 32 in the plain FP64 ones of 32 cells with per-cell
+// inputs, whose state alone takes 256 registers.
 constexpr int mc_min_waves(int size, int E, bool cell_in) {
     const int regs = (cell_in ? 4 : 3) * E * size / 4;
     return regs > 208 ? 1 : size == 8 || regs > 112 ? 2 : regs > 64 ? 3 : 4;

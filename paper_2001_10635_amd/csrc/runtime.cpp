@@ -668,6 +668,8 @@ struct HeatPlan {
 //   40^3                              14 / 18       12 / 15          9.4 / 12
 //   100^3              79 / 115       19 / 27       19 / 25         20 / 27
 //   200 x 180 x 150   105 / 151       40 / 64       51 / 74         54 / 98
+// (the FP64 kernel of 16 waves spills in its cut instance, 4 to 11 scratch accesses
+// per six planes, which these figures hold)
 void heat_z_chunks(int64_t nx, int64_t ny, int64_t nz, bool f64, int64_t cus, HeatPlan* p) {
     double best = 0.0;
     for (const int WV : {16, 12, 8}) {
