@@ -201,8 +201,8 @@ int64_t reach_get_option(const reach_ctx* ctx, const char* key);
 reach_status reach_plan_embed(reach_ctx* ctx, const reach_system* sys, reach_dtype dtype,
                               int64_t nsteps, int64_t* out);
 
-/* Autotuner for reach_embed_rk4: times every built tile shape (E cells per
-   lane) and steps-per-pass K on the caller's own buffers (trial_steps RK4
+/* Autotuner for reach_embed_rk4: times the built tile shapes (E = 4, 8, 12, 16,
+   24, 28, 32, 48 and 64 cells per lane) and steps-per-pass K on the caller's own buffers (trial_steps RK4
    steps per trial, one warm-up and two timed calls, HIP events on `stream`),
    re-times the four fastest and the built-in default over ten times the
    steps (three rounds, each shape once per round), and records the fastest
