@@ -518,7 +518,12 @@ def make_query(kind, n, prm, dtype_code_, x_lo, x_hi, r_lo, r_hi, dt, nsteps, p_
 
 
 class Reach:
-    """A context plus workspace management around the C entry points."""
+    """A context plus workspace management around the C entry points.
+
+    The object's calls share one workspace, so calls that may run at the same
+    time need a stream in common or an object each; embeddings that use none
+    (chains that one window of the kernel holds, and runs of one pass not in
+    place) may run on any streams."""
 
     def __init__(self, device: int = 0):
         self.device = torch.device("cuda", device)
