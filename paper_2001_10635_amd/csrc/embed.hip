@@ -20,8 +20,8 @@ hipError_t launch_embed_lin3_f64(int mode, int E, int S, bool pair, const EmbedP
 hipError_t launch_embed_lin3_f32(int mode, int E, int S, bool pair, const EmbedPass& a,
                           int64_t grid, hipStream_t s);
 
-// Lower > upper check of a finished box (the heat grid, where no wave sees both
-// sides of a cell).
+// Lower > upper check of a finished box where no block sees both sides of a cell (the
+// heat grid, and a last pass in blocks of one wave).
 template <class T>
 __global__ __launch_bounds__(256) void order_check_kernel(const T* __restrict__ lo,
                                                           const T* __restrict__ hi, int64_t n,
@@ -60,8 +60,8 @@ hipError_t launch_embed(int kind, int mode, int dtype, int E, int S, bool pair, 
 }
 
 hipError_t launch_order_check(int dtype, const void* lo, const void* hi, int64_t n,
-                              unsigned int* status, hipStream_t s) {
-    const int64_t blocks = std::min<int64_t>((n + 255) / 256, 8192);
+                              unsigned int* status, int64_t max_blocks, hipStream_t s) {
+    const int64_t blocks = std::min<int64_t>((n + 255) / 256, max_blocks);
     if (dtype == 0)
         hipLaunchKernelGGL(order_check_kernel<double>, dim3((unsigned)blocks), dim3(256), 0, s,
                            (const double*)lo, (const double*)hi, n, status);

@@ -1,17 +1,18 @@
 // Contraction / growth-bound reachable box on gfx950 (PIRK Sec. 2.1,
 // Algorithm 2).
 //
-// Two RK4 runs share every launch: a block's first wave integrates the center
-// of the box with the system's own f at the center input, its second wave the
+// Two RK4 runs share every launch: one wave integrates the center
+// of the box with the system's own f at the center input, another the
 // half-width of the same window with the linear growth dynamics
 // r' = C r + |b| [p], C the tridiagonal contraction matrix.  Each wave holds one
 // run's window in registers, exactly like the one-side embedding tiles (same
 // per-cell code, transfers, temporal blocking and halos).  The first pass forms
-// c = (lo + hi) / 2 or r = (hi - lo) / 2 as it loads the box.  In the last pass
-// the two waves exchange their windows through LDS and write [c - r, c + r]
-// themselves: a separate combining kernel reads c and r and writes the box
+// c = (lo + hi) / 2 or r = (hi - lo) / 2 as it loads the box.  The two waves of a
+// window are one block (PAIR); in the last pass they exchange their windows
+// through LDS and write [c - r, c + r] themselves: a separate combining kernel reads c and r and writes the box
 // again, 64 bytes per FP64 cell (it remains for calls whose result arrays
-// overlap what the last pass still reads).
+// overlap what the last pass still reads, and where blocks of two waves would share
+// SIMDs, see pairs_share in the runtime).
 #include <algorithm>
 
 #include "kernels.hpp"
@@ -19,24 +20,26 @@
 
 namespace reach {
 
-template <int KIND, class T, int E, int MODE>
-__global__ __launch_bounds__(2 * WAVE, E * sizeof(T) <= 192 ? 2 : 1)
+template <int KIND, class T, int E, int MODE, bool PAIR>
+__global__ __launch_bounds__(PAIR ? 2 * WAVE : WAVE, E * sizeof(T) <= 192 ? 2 : 1)
 void gb_tile_kernel(GbPass a) {
     using IO = TileIO<T, E>;
     constexpr int ROW = IO::STAGED ? IO::ROW : E;
-    constexpr int LDS = IO::STAGED ? IO::LDS_ELEMS : WAVE * E;
-    __shared__ __attribute__((aligned(16))) T lds[2 * LDS];
+    constexpr int LDS = IO::STAGED || !PAIR ? IO::LDS_ELEMS : WAVE * E;
+    __shared__ __attribute__((aligned(16))) T lds[LDS * (PAIR ? 2 : 1)];
     const int lane = threadIdx.x & (WAVE - 1);
-    const int side = (int)(threadIdx.x / WAVE);      // 0: center run, 1: half-width run
     const int64_t b = blockIdx.x;
-    const int64_t w = (b & 7) * (int64_t)a.per_xcd + (b >> 3);
-    if (w >= a.W) return;
-    T* const my_lds = lds + side * LDS;
+    const int64_t g = (b & 7) * (int64_t)a.per_xcd + (b >> 3);
+    if (g >= (PAIR ? a.W : 2 * a.W)) return;
+    // 0: center run, 1: half-width run
+    const int side = PAIR ? (int)(threadIdx.x / WAVE) : g >= a.W ? 1 : 0;
+    const int64_t w = PAIR ? g : g - side * a.W;
+    T* const my_lds = lds + (PAIR ? side * LDS : 0);
     // the last of several windows ends with the chain (see embed_tile_kernel)
     const int64_t span = (int64_t)WAVE * E;
     const int64_t ts = w == a.W - 1 && w > 0 ? a.n - span : w * a.OUT;
     const bool reaches_end = ts + span >= a.n;
-    const bool fast = ts + span <= a.n;
+    const bool fast = !PAIR || ts + span <= a.n;   // (only a single window holds padding)
     const int64_t left = a.n - (ts + (int64_t)lane * E);
     const int nvalid = (int)(left < 0 ? 0 : (left > E ? E : left));
 
@@ -71,7 +74,7 @@ void gb_tile_kernel(GbPass a) {
 
     const Mask<E, false, false> inner{E};
     const Mask<E, false, true> end{E};
-    const auto padded = chain_end_mask<E, true, (E >= 12)>(a.n - ts);
+    const auto padded = chain_end_mask<E, true, (E * sizeof(T) >= 48)>(a.n - ts);
     if (side == 0) {
         if (!fast) rk4_steps<KIND, T, E, 1, MODE>(y, a.ksteps, P, U, st, padded);
         else if (KIND == K_CTM && reaches_end) rk4_steps<KIND, T, E, 1, MODE>(y, a.ksteps, P, U, st, end);
@@ -83,31 +86,33 @@ void gb_tile_kernel(GbPass a) {
 
     const int olo = (w == 0) ? 0 : a.H + (int)(w * a.OUT - ts);
     const int ohi = reaches_end ? (int)(a.n - ts) : (int)(span - a.H);
-    if (!a.last) {
+    if (!PAIR || !a.last) {
         IO::store(y[0], (T*)(side == 0 ? a.dst_c : a.dst_r), ts, olo, ohi, fast, false, my_lds);
         return;
     }
-    // [c - r, c + r]: the center wave writes the lower vector, the other the upper
+    if constexpr (PAIR) {
+        // [c - r, c + r]: the center wave writes the lower vector, the other the upper
 #pragma unroll
-    for (int e = 0; e < E; ++e) my_lds[lane * ROW + e] = y[0][e];
-    __syncthreads();
-    const T* const other = lds + (1 - side) * LDS;
-    unsigned bits = 0;
+        for (int e = 0; e < E; ++e) my_lds[lane * ROW + e] = y[0][e];
+        __syncthreads();
+        const T* const other = lds + (1 - side) * LDS;
+        unsigned bits = 0;
 #pragma unroll
-    for (int e = 0; e < E; ++e) {
-        const T o = other[lane * ROW + e];
-        const T c = side == 0 ? y[0][e] : o, r = side == 0 ? o : y[0][e];
-        const T lo = c - r, hi = c + r;
-        const int el = lane * E + e;
-        if (el >= olo && el < ohi) {
-            if (!finiteT(lo) || !finiteT(hi)) bits |= ST_NONFINITE;
-            if (lo > hi) bits |= ST_ORDER;
+        for (int e = 0; e < E; ++e) {
+            const T o = other[lane * ROW + e];
+            const T c = side == 0 ? y[0][e] : o, r = side == 0 ? o : y[0][e];
+            const T lo = c - r, hi = c + r;
+            const int el = lane * E + e;
+            if (el >= olo && el < ohi) {
+                if (!finiteT(lo) || !finiteT(hi)) bits |= ST_NONFINITE;
+                if (lo > hi) bits |= ST_ORDER;
+            }
+            y[0][e] = side == 0 ? lo : hi;
         }
-        y[0][e] = side == 0 ? lo : hi;
+        __syncthreads();   // both have read before the rows stage the stores
+        IO::store(y[0], (T*)(side == 0 ? a.r_lo : a.r_hi), ts, olo, ohi, fast, false, my_lds);
+        report_status(a.status, bits);
     }
-    __syncthreads();   // both have read before the rows stage the stores
-    IO::store(y[0], (T*)(side == 0 ? a.r_lo : a.r_hi), ts, olo, ohi, fast, false, my_lds);
-    report_status(a.status, bits);
 }
 
 template <class T>
@@ -129,8 +134,12 @@ __global__ __launch_bounds__(256) void gb_combine_kernel(const T* __restrict__ c
 
 template <int KIND, class T, int E, int MODE>
 static hipError_t go_gb(const GbPass& a, int64_t grid, hipStream_t s) {
-    hipLaunchKernelGGL((gb_tile_kernel<KIND, T, E, MODE>), dim3((unsigned)grid), dim3(2 * WAVE), 0,
-                       s, a);
+    if (a.pair)
+        hipLaunchKernelGGL((gb_tile_kernel<KIND, T, E, MODE, true>), dim3((unsigned)grid),
+                           dim3(2 * WAVE), 0, s, a);
+    else
+        hipLaunchKernelGGL((gb_tile_kernel<KIND, T, E, MODE, false>), dim3((unsigned)grid),
+                           dim3(WAVE), 0, s, a);
     return hipGetLastError();
 }
 
@@ -156,8 +165,10 @@ bool gb_has_E(int E) {
            E == 28 || E == 32;
 }
 
-hipError_t launch_gb(int kind, int mode, int dtype, int E, const GbPass& a, int64_t grid,
-                     hipStream_t s) {
+hipError_t launch_gb(int kind, int mode, int dtype, int E, GbPass a, hipStream_t s) {
+    const int64_t blocks = a.pair ? a.W : 2 * a.W;
+    a.per_xcd = (int32_t)((blocks + 7) / 8);
+    const int64_t grid = 8 * (int64_t)a.per_xcd;
     if (dtype == 0) {
         if (kind == K_CTM) return gb_by_E<K_CTM, double, IN_SCALAR>(E, a, grid, s);
         if (kind == K_RD) return mode ? gb_by_E<K_RD, double, IN_CELL>(E, a, grid, s)
@@ -175,8 +186,8 @@ hipError_t launch_gb(int kind, int mode, int dtype, int E, const GbPass& a, int6
 }
 
 hipError_t launch_gb_combine(int dtype, const void* c, const void* r, int64_t n, void* lo,
-                             void* hi, unsigned int* status, hipStream_t s) {
-    const int64_t blocks = std::min<int64_t>((n + 255) / 256, 8192);
+                             void* hi, unsigned int* status, int64_t max_blocks, hipStream_t s) {
+    const int64_t blocks = std::min<int64_t>((n + 255) / 256, max_blocks);
     if (dtype == 0)
         hipLaunchKernelGGL(gb_combine_kernel<double>, dim3((unsigned)blocks), dim3(256), 0, s,
                            (const double*)c, (const double*)r, n, (double*)lo, (double*)hi, status);

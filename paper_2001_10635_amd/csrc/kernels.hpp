@@ -51,11 +51,12 @@ bool embed_has_shape(int kind, int dtype, int E, int S);
 int embed_max_E(int dtype, int S);
 // Flags lower > upper anywhere in a finished box.
 hipError_t launch_order_check(int dtype, const void* lo, const void* hi, int64_t n,
-                              unsigned int* status, hipStream_t stream);
+                              unsigned int* status, int64_t max_blocks, hipStream_t stream);
 
-// One pass of the growth-bound method: W blocks of two waves, which advance the
-// center and the half-width of a window; `first` forms them from the box
-// (x_lo, x_hi), `last` writes the box (r_lo, r_hi) instead of (dst_c, dst_r).
+// One pass of the growth-bound method: two waves per window advance its center and
+// its half-width (one block of both if `pair`, as W == 1 and `last` need, else a block each);
+// `first` forms them from the box (x_lo, x_hi), `last` writes the box (r_lo, r_hi)
+// instead of (dst_c, dst_r).
 struct GbPass {
     const void* x_lo;
     const void* x_hi;
@@ -66,7 +67,8 @@ struct GbPass {
     const void* p_lo;
     const void* p_hi;
     int64_t n, W, OUT, ksteps;
-    int32_t H, first, last, per_xcd;
+    int32_t H, first, last, pair;
+    int32_t per_xcd;   // blocks per XCD (set by launch_gb)
     void* r_lo;
     void* r_hi;
     unsigned int* status;
@@ -74,10 +76,10 @@ struct GbPass {
     double prm_r[5];   // the growth dynamics: {C_sub, C_diag, C_sup, |b|}
     double h2, dt, dt6;
 };
-hipError_t launch_gb(int kind, int mode, int dtype, int E, const GbPass& a, int64_t grid,
-                     hipStream_t stream);
+hipError_t launch_gb(int kind, int mode, int dtype, int E, GbPass a, hipStream_t stream);
 hipError_t launch_gb_combine(int dtype, const void* c, const void* r, int64_t n, void* lo,
-                             void* hi, unsigned int* status, hipStream_t stream);
+                             void* hi, unsigned int* status, int64_t max_blocks,
+                             hipStream_t stream);
 bool gb_has_E(int E);
 
 // One RK4 step of the 3-D heat grid for `sides` independent states

@@ -538,6 +538,36 @@ bool cut_pays(double one_us, double many_us, int64_t passes, bool hold) {
            (passes == 1 || one_us >= 7.0 * (double)passes + (hold ? 5.0 : 0.0));
 }
 
+// A second block of two waves on a compute unit lands on the SIMDs of the first
+// while the other two stay idle: W such blocks, one window each, take up to 1.65
+// times as long as blocks of one wave where they are more than the compute units
+// and at most twice as many (growth bound, 8 FP64 RD cells a lane, 200 steps: 256
+// windows 100 us, 284 166 in blocks of two and 102 of one, 512 167 and 122, 520 168 and
+// 168; with more windows than that blocks of two are up to 15% faster).
+bool pairs_share(const reach_ctx* c, int64_t W) { return W > c->cus && W <= 2 * (int64_t)c->cus; }
+
+// Whether a last pass of W FP64 windows of E cells a lane and `steps` steps does better
+// in blocks of one wave, its two sides brought together by a kernel of its own that
+// moves `bytes` (FP32 instructions of two waves on a SIMD overlap: no gain there).  At two
+// waves per SIMD a second round of windows ends alike (`rounds`; RD, 20 steps: 500000
+// cells, 446 windows, 39 us in blocks of two and 27 with the check apart; 2 * 10^6 cells,
+// 1454 windows, 92 and 78).
+bool part_last_pass(const reach_ctx* c, int kind, int dtype, bool cell_in, int64_t W, int E,
+                    int64_t steps, double bytes, bool rounds) {
+    const int64_t round = (int64_t)4 * c->cus;
+    const int64_t rest = rounds && W < 2 * round ? W % round : W;
+    bool over = false;
+    const double step = 0.8 * cell_us(kind, dtype, cell_in, 1, E, &over) * E;
+    return dtype == REACH_F64 && !over && pairs_share(c, rest) &&
+           step * (double)steps > 2.5 + bytes / 5.0e6;
+}
+
+// Blocks of the kernel that brings two sides together: as many as keep a large sweep
+// busy, but behind waves that had a SIMD each no more than find a place at once.  After
+// 2048 blocks or more the next kernel's waves share SIMDs again (20 steps, 24 FP64 RD cells
+// a lane, one call behind another: 400 windows 50 us, 31 behind 1024 blocks).
+constexpr int64_t kSweepBlocks = 8192, kPartBlocks = 1024;
+
 // The estimate decides on chains whose default windows put at most 8 waves on a
 // SIMD; longer ones keep the shapes measured at 2^26 and 2^31 cells (there the
 // rounds run into each other and the last one weighs little).
@@ -792,7 +822,7 @@ reach_status embed_heat3d(reach_ctx* c, const reach_system* s, reach_dtype dtype
         if (e != hipSuccess) return hip_fail(c, e, "3-D heat kernel launch");
     }
     hipError_t e = launch_order_check(dt_id, lo_of[io.dst(passes - 1)], hi_of[io.dst(passes - 1)],
-                                      s->n, c->status, hs);
+                                      s->n, c->status, kSweepBlocks, hs);
     if (e != hipSuccess) return hip_fail(c, e, "order check launch");
     if (io.final_copy()) {
         HIPCHK(c, hipMemcpyAsync(r_lo, w_lo, bytes, hipMemcpyDeviceToDevice, hs));
@@ -841,7 +871,7 @@ reach_status gb_heat3d(reach_ctx* c, const reach_system* s, reach_dtype dtype, c
         if (e != hipSuccess) return hip_fail(c, e, "3-D heat kernel launch");
         cur = dst;
     }
-    e = launch_gb_combine(dt_id, cur, cur + bytes, s->n, r_lo, r_hi, c->status, hs);
+    e = launch_gb_combine(dt_id, cur, cur + bytes, s->n, r_lo, r_hi, c->status, kSweepBlocks, hs);
     if (e != hipSuccess) return hip_fail(c, e, "growth-bound combine launch");
     return REACH_OK;
 }
@@ -1277,6 +1307,7 @@ static reach_status embed_run(reach_ctx* c, const reach_system* s, reach_dtype d
     a.status = c->status;
     const int mode = s->n_in > 1 ? 1 : 0;   // per-cell inputs
     if (s->n_in == 0) { a.p_lo = nullptr; a.p_hi = nullptr; }
+    bool part = false;
     int64_t done = 0;
     for (int64_t p = 0; p < pl.passes; ++p) {
         a.src_lo = lo_of[io.src(p)];
@@ -1289,9 +1320,13 @@ static reach_status embed_run(reach_ctx* c, const reach_system* s, reach_dtype d
         // caches' retention (non-temporal), 1.8% faster at 2^26 cells
         a.nt = a.ksteps == 1 ? 1 : 0;
         // one side per wave: the last pass has both sides of a window in one
-        // block, which checks the order, and so has every pass of a single
-        // window, whose sides may write over each other's inputs
-        const bool pair = pl.S == 1 && (a.check || pl.W == 1);
+        // block, which checks the order (unless such blocks would share SIMDs), and
+        // so has every pass of a single window, whose sides may write over each
+        // other's inputs
+        part = pl.S == 1 && a.check &&
+               part_last_pass(c, s->kind, dtype, mode == 1, pl.W, pl.E, a.ksteps,
+                              2.0 * (double)bytes, true);
+        const bool pair = pl.S == 1 && (a.check || pl.W == 1) && !part;
         const int64_t tiles = pl.S == 1 && !pair ? 2 * pl.W : pl.W;
         a.per_xcd = (int32_t)((tiles + 7) / 8);
         const int64_t grid = 8 * (int64_t)a.per_xcd;
@@ -1299,6 +1334,11 @@ static reach_status embed_run(reach_ctx* c, const reach_system* s, reach_dtype d
                                     a, grid, hs);
         if (e != hipSuccess) return hip_fail(c, e, "embedding kernel launch");
         done += a.ksteps;
+    }
+    if (part) {
+        hipError_t e = launch_order_check(dtype == REACH_F64 ? 0 : 1, a.dst_lo, a.dst_hi, s->n,
+                                          c->status, kPartBlocks, hs);
+        if (e != hipSuccess) return hip_fail(c, e, "order check launch");
     }
     if (io.final_copy()) {
         HIPCHK(c, hipMemcpyAsync(r_lo, w_lo, bytes, hipMemcpyDeviceToDevice, hs));
@@ -1651,8 +1691,6 @@ reach_status reach_growth_bound(reach_ctx* c, const reach_system* s, reach_dtype
         a.W = (n <= span) ? 1 : 1 + (n - span + a.OUT - 1) / a.OUT;
         passes = std::max<int64_t>(1, (nsteps + K - 1) / K);
     }
-    a.per_xcd = (int32_t)((a.W + 7) / 8);
-    const int64_t grid = 8 * (int64_t)a.per_xcd;
     // The last pass writes the box itself unless the result arrays overlap what
     // other windows still read then (per-cell inputs; in a run of one pass the
     // box): such a call combines in a kernel of its own.
@@ -1664,6 +1702,9 @@ reach_status reach_growth_bound(reach_ctx* c, const reach_system* s, reach_dtype
             if (passes == 1)
                 fused &= !overlaps(x_lo, bytes, q, bytes) && !overlaps(x_hi, bytes, q, bytes);
         }
+    const bool part = part_last_pass(c, like, dtype, cell_in, a.W, E, nsteps - (passes - 1) * K,
+                                     4.0 * (double)bytes, false);
+    fused &= !part;
     a.r_lo = r_lo; a.r_hi = r_hi;
     a.status = c->status;
     log_call(c, "\"call\": \"growth_bound\", \"kind\": %d, \"dtype\": \"%s\", \"n\": %lld, "
@@ -1681,15 +1722,17 @@ reach_status reach_growth_bound(reach_ctx* c, const reach_system* s, reach_dtype
         char* src = ((passes - 1 - p) % 2 == 0) ? B : A;
         a.first = (p == 0) ? 1 : 0;
         a.last = fused && p == passes - 1 ? 1 : 0;
+        a.pair = a.last || !pairs_share(c, a.W) ? 1 : 0;
         a.src_c = src; a.src_r = src + bytes;
         a.dst_c = dst; a.dst_r = dst + bytes;
         a.ksteps = std::min<int64_t>(K, nsteps - done);
-        hipError_t e = launch_gb(s->kind, mode, dt_id, E, a, grid, hs);
+        hipError_t e = launch_gb(s->kind, mode, dt_id, E, a, hs);
         if (e != hipSuccess) return hip_fail(c, e, "growth-bound kernel launch");
         done += a.ksteps;
     }
     if (fused) return REACH_OK;
-    hipError_t e = launch_gb_combine(dt_id, A, A + bytes, n, r_lo, r_hi, c->status, hs);
+    hipError_t e = launch_gb_combine(dt_id, A, A + bytes, n, r_lo, r_hi, c->status,
+                                     part ? kPartBlocks : kSweepBlocks, hs);
     if (e != hipSuccess) return hip_fail(c, e, "growth-bound combine launch");
     return REACH_OK;
 }

@@ -356,3 +356,53 @@ def test_batch_layouts_equal_single_runs(rc, kinds, nq, long):
             x[k].nsteps = 1 if bad is None else q.nsteps
             R.reach_embed_rk4_batch(rc.ctx, x, ws, nb)
             assert rc.sync() == want, (k, bad)
+
+
+def shaped(rc, call, c, nsteps, E, K, over=False):
+    """One call at E cells a lane and K steps a pass, with its results over the box if
+    `over`: (status, lower, upper)."""
+    kind, prm, dt, x_lo, x_hi, p_lo, p_hi = c
+    if over:
+        x_lo, x_hi = x_lo.clone(), x_hi.clone()
+    r = (x_lo, x_hi) if over else (torch.empty_like(x_lo), torch.empty_like(x_hi))
+    names = ("gb.E", "gb.K") if call == "gb" else ("embed.E", "embed.K", "embed.S")
+    for name, v in zip(names, (E, K, 1)):
+        rc.set_option(name, v)
+    try:
+        f = rc.growth_bound if call == "gb" else rc.embed
+        f(kind, prm, x_lo, x_hi, dt, nsteps, p_lo=p_lo, p_hi=p_hi, r_lo=r[0], r_hi=r[1])
+        return (rc.sync(),) + r
+    finally:
+        for name in names:
+            rc.set_option(name, 0)
+
+
+@pytest.mark.parametrize("call", ["gb", "embed"])
+@pytest.mark.parametrize("variant", ["rd", "ctm", "rd_cell"])
+@pytest.mark.parametrize("windows", [256, 257, 400, 512, 513, 1300])
+def test_windows_of_more_than_one_and_two_a_compute_unit(rc, call, variant, windows):
+    """FP64 windows just below, in and past the range where the sides of a window
+    are blocks of their own and a last kernel brings them together: the bits of
+    another shape, also with the results over the box, and the same flags."""
+    E, K = 8, 20
+    n = 64 * E + (windows - 1) * (64 * E - 8 * K) - 3
+    c = dev_case(variant, n, R.REACH_F64, windows)
+    for nsteps in (K, 3 * K):
+        say(f"{call} {variant} windows={windows} N={nsteps}")
+        ref = shaped(rc, call, c, nsteps, 4, 9)
+        assert ref[0] == R.REACH_OK
+        for over in (False, True):
+            got = shaped(rc, call, c, nsteps, E, K, over)
+            assert got[0] == R.REACH_OK
+            assert torch.equal(got[1], ref[1]) and torch.equal(got[2], ref[2])
+    for bad, want in ((float("inf"), R.REACH_E_NONFINITE), (None, R.REACH_E_ORDER)):
+        lo, hi = c[3].clone(), c[4].clone()
+        part = slice(n // 2, n // 2 + 700)
+        if bad is None:
+            lo[part], hi[part] = c[4][part], c[3][part]
+        else:
+            hi[n // 2] = bad
+        # (so short a time that the inputs' interval does not open the crossed part again)
+        case = c[:2] + (0.01 * c[2], lo, hi) + c[5:]
+        assert shaped(rc, call, case, K, E, K)[0] == want
+        assert shaped(rc, call, c, K, E, K)[0] == R.REACH_OK
