@@ -8,11 +8,12 @@
 // run's window in registers, exactly like the one-side embedding tiles (same
 // per-cell code, transfers, temporal blocking and halos).  The first pass forms
 // c = (lo + hi) / 2 or r = (hi - lo) / 2 as it loads the box.  The two waves of a
-// window are one block (PAIR); in the last pass they exchange their windows
-// through LDS and write [c - r, c + r] themselves: a separate combining kernel reads c and r and writes the box
-// again, 64 bytes per FP64 cell (it remains for calls whose result arrays
-// overlap what the last pass still reads, and where blocks of two waves would share
-// SIMDs, see pairs_share in the runtime).
+// window are one block (PAIR); in the last pass they exchange their windows through
+// LDS and write [c - r, c + r] themselves: a separate combining kernel reads c and r
+// and writes the box again, 64 bytes per FP64 cell.  It remains for calls whose result
+// arrays overlap what the last pass still reads, and for a last pass whose waves are
+// blocks of their own because blocks of two would share SIMDs (pairs_share in the
+// runtime has the figures).
 #include <algorithm>
 
 #include "kernels.hpp"
